@@ -419,11 +419,9 @@ pic_status expand_lattice(const pic_element* lat, int n_el, std::vector<SliceDev
   return PIC_OK;
 }
 
-// the deposit's per-tile integer windows start at zero (each deposit leaves them zero; a call
-// interrupted by a device error may not)
-hipError_t clear_tacc(pic_beam b, hipStream_t s) {
-  return launch_zero<double>((double*)b->tacc,
-                             (int64_t)b->sp.ntiles * tile_window_nodes(b->sp, b->d.shape), s);
+hipError_t call_setup(pic_beam b, hipStream_t s) {
+  return launch_call_setup(b->box, b->tacc,
+                           (int64_t)b->sp.ntiles * tile_window_nodes(b->sp, b->d.shape), s);
 }
 
 // Green spectrum of the current geometry on the auxiliary stream (joined before the solve)
@@ -456,8 +454,7 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
   const bool ids = !binned || ids_io;
   uint32_t* idA = ids ? b->idA : nullptr;
   uint32_t* idB = ids ? b->idB : nullptr;
-  HIP_OK(launch_box_reset(b->box, s), "box reset");
-  HIP_OK(clear_tacc(b, s), "clear");
+  HIP_OK(call_setup(b, s), "set-up");
   STAGE(b, PIC_STAGE_PROLOGUE, s,
         launch_prologue(b->X, A, idA, binned ? ids_io : nullptr, sl[0].first, b->c, b->box, s),
         "prologue");
@@ -499,7 +496,6 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
     const int has_next = more && (tiles || !diag);  // fuse the next step's first half map
     double* diag_j = diag ? diag + (size_t)kMomentSlots * j : nullptr;
     const SliceDev& nx = sl[(j + 1) % ns];
-    if (has_next) HIP_OK(launch_box_reset(b->box, s), "box reset");
     // a binned call's last gather-kick writes the caller's arrays (it always reads A through
     // the ranking, so X is written only if no step has flagged an error)
     const bool to_caller = binned && permuted && !more;
@@ -521,10 +517,7 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
             "gather-kick-drift");
     if (diag && !tiles) {  // moments at the end of the step, then the next first half map
       HIP_OK(launch_moments(B, b->c.n, b->mom_partial, diag_j, s), "diagnostics");
-      if (more) {
-        HIP_OK(launch_box_reset(b->box, s), "box reset");
-        HIP_OK(launch_half_box(B, nx.first, b->c, b->box, s), "diagnostics");
-      }
+      if (more) HIP_OK(launch_half_box(B, nx.first, b->c, b->box, s), "diagnostics");
     }
     // B holds the updated particles in slot order
     double* tX = A; A = B; B = tX;
@@ -768,7 +761,6 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
       HIP_OK(hipMemcpyAsync(ckpt + 6 * n * (size_t)(j / ck), b->X, 6 * sizeof(double) * n,
                             hipMemcpyDeviceToDevice, s),
              "adjoint checkpoint");
-    HIP_OK(launch_box_reset(b->box, s), "adjoint forward");
     pic_status st = forward_step_recorded<T>(b, b->X, geom(j), sl[j % nsl],
                                            direct ? (T*)b->gh3 : (T*)b->Gh, (T*)b->E,
                                            (T*)b->rho, s, b->box);
@@ -882,8 +874,7 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
 template <typename T>
 pic_status enqueue_batch(const BeamDev* tab, int nb, const BatchDims& bd, int shape, int n_steps,
                          hipStream_t s, hipStream_t aux, hipEvent_t fork, hipEvent_t join) {
-  HIP_OK(launch_batch_box_reset(tab, nb, s), "batch");
-  HIP_OK(launch_batch_clear_tacc(tab, nb, s), "batch");
+  HIP_OK(launch_batch_call_setup(tab, nb, s), "batch");
   HIP_OK(launch_batch_prologue_particles(tab, nb, bd, s), "batch");
   for (int j = 0; j < n_steps; ++j) {
     const int parity = j & 1;
@@ -898,7 +889,6 @@ pic_status enqueue_batch(const BeamDev* tab, int nb, const BatchDims& bd, int sh
     HIP_OK(launch_batch_deposit<T>(tab, nb, bd, shape, parity, j == 0, s), "batch");
     HIP_OK(hipStreamWaitEvent(s, join, 0), "batch");
     HIP_OK(launch_batch_solve<T>(tab, nb, bd, s), "batch");
-    if (j + 1 < n_steps) HIP_OK(launch_batch_box_reset(tab, nb, s), "batch");
     HIP_OK(launch_batch_gkd<T>(tab, nb, bd, shape, parity, j, n_steps, j == 0, s), "batch");
   }
   HIP_OK(launch_batch_unpermute(tab, nb, bd, n_steps & 1, s), "batch");
@@ -1022,7 +1012,7 @@ pic_status pic_beam_create(const pic_beam_desc* d, double* d_X, void* d_work, si
   hipError_t e = hipSuccess;
   for (int a = 0; a < 3 && e == hipSuccess; ++a)
     e = launch_twiddles((double2*)b->plan.tw[a], (float2*)b->plan.twf[a], b->plan.full[a].M, s);
-  if (e == hipSuccess) e = launch_box_reset(b->box, s);
+  if (e == hipSuccess) e = call_setup(b, s);
   if (e == hipSuccess) e = launch_zero<uint32_t>(b->hist, kMaxTiles, s);
   if (e == hipSuccess) e = launch_clear_status(b->geom, s);
   if (e == hipSuccess) e = make_aux(&b->aux, &b->ev_fork, &b->ev_join, &b->done.ev);
@@ -1115,12 +1105,11 @@ pic_status pic_deposit(pic_beam b, void* d_rho, void* stream) {
   MarkDone md{b->done, S(stream)};
   hipStream_t s = S(stream);
   const int64_t ng = (int64_t)b->d.nx * b->d.ny * b->d.nz;
-  HIP_OK(launch_box_reset(b->box, s), "deposit");
+  HIP_OK(call_setup(b, s), "deposit");
   HIP_OK(launch_box(b->X, b->d.n, b->box, s), "deposit");
   HIP_OK(launch_geometry(b->box, b->geom, b->c, s), "deposit");
   // binned as in the tracking loop: tile keys and the ranking of X (X itself is not moved),
   // then the tiles' integer windows, so the grid does not depend on the order of the atomics
-  HIP_OK(clear_tacc(b, s), "deposit");
   HIP_OK(launch_bin_perm(b->X, b->geom, b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks,
                          b->nchunks, b->perm, s),
          "deposit");
@@ -1321,7 +1310,7 @@ pic_status pic_track_adjoint(pic_beam b, const pic_element* lattice, int n_el, i
     return fail(PIC_ENOMEM, "reverse-sweep workspace smaller than pic_adjoint_workspace_bytes");
   hipStream_t s = S(stream);
   MarkDone md{b->done, s};
-  HIP_OK(clear_tacc(b, s), "clear");
+  HIP_OK(call_setup(b, s), "set-up");
   if (b->d.grid_fp32)
     return track_adjoint<float>(b, sl, n_el, n_steps, ckpt_every, w, (char*)d_adj_work, A,
                                 d_lam, d_xi, out_m, dJ_dk, dJ_dL, s);

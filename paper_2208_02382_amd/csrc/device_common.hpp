@@ -143,7 +143,7 @@ __device__ __forceinline__ void apply_half_T(const HalfMap& h, double lm[6], dou
   }
 }
 
-// Block-wide min/max of x, y, z, then one atomic per block and axis.
+// Block-wide min/max of x, y, z, then one atomic per block and axis on the block's slot.
 __device__ __forceinline__ void box_accumulate_block(double lo[3], double hi[3], bool bad, Box* box) {
   __shared__ double slo[3][kBoxBlock / 64], shi[3][kBoxBlock / 64];
   __shared__ int sbad;
@@ -155,6 +155,7 @@ __device__ __forceinline__ void box_accumulate_block(double lo[3], double hi[3],
       hi[a] = fmax(hi[a], __shfl_xor(hi[a], off));
     }
   }
+  BoxSlot* slot = box->slot + blockIdx.x % kBoxSlots;
   int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (lane == 0)
     for (int a = 0; a < 3; ++a) {
@@ -171,11 +172,11 @@ __device__ __forceinline__ void box_accumulate_block(double lo[3], double hi[3],
       h = fmax(h, shi[a][q]);
     }
     if (l <= h) {
-      atomicMin(&box->mn[a], ord_enc(l));
-      atomicMax(&box->mx[a], ord_enc(h));
+      atomicMin(&slot->mn[a], ord_enc(l));
+      atomicMax(&slot->mx[a], ord_enc(h));
     }
   }
-  if (threadIdx.x == 0 && sbad) atomicOr(&box->nonfinite, 1u);
+  if (threadIdx.x == 0 && sbad) atomicOr(&slot->nonfinite, 1u);
 }
 
 }  // namespace pic

@@ -17,12 +17,21 @@ struct Geom {
 };
 
 // Box accumulator: min/max of x, y, z in order-preserving uint64 encoding, and a non-finite
-// flag.  Reset by k_box_reset before each reduction.
-struct Box {
+// flag, in kBoxSlots slots of one cache line each.  Workgroup b of a reduction adds to slot
+// b mod kBoxSlots: 64-bit atomics on one address take about 4 ns each, one after another, so
+// with a single slot six of them per workgroup were the length of every short pass over the
+// particles (k_prologue at 1e6 particles: 98 us, and 21 us with the slots).  The geometry
+// kernel combines the slots with one wave and leaves them empty for the next reduction.
+constexpr int kBoxSlots = 64;  // the geometry wave takes one slot per lane
+struct BoxSlot {
   unsigned long long mn[3];
   unsigned long long mx[3];
   unsigned int nonfinite;
-  unsigned int pad[3];
+  unsigned int pad[19];
+};
+static_assert(sizeof(BoxSlot) == 128, "a slot is one cache line");
+struct Box {
+  BoxSlot slot[kBoxSlots];
 };
 
 // Problem constants passed by value to kernels.
@@ -159,9 +168,11 @@ int record_hip_failure(hipError_t e, const char* where);
   } while (0)
 
 // ---- launch wrappers (particles.hip)
-hipError_t launch_box_reset(Box* box, hipStream_t s);
+// empties the box and zeroes the deposit's integer windows: once per call (the geometry kernel
+// and each deposit leave them so; a call that ended in an error may not)
+hipError_t launch_call_setup(Box* box, unsigned long long* tacc, int64_t count, hipStream_t s);
 hipError_t launch_box(const double* X, int64_t n, Box* box, hipStream_t s);
-hipError_t launch_geometry(const Box* box, Geom* g, Consts c, hipStream_t s);
+hipError_t launch_geometry(Box* box, Geom* g, Consts c, hipStream_t s);
 hipError_t launch_init_normals(double* X, const double* xi, int64_t n, Chol L, hipStream_t s);
 // dist 0: Gaussian with a uniform halo of n_halo trailing particles; 1: Waterbag (n_halo 0)
 hipError_t launch_init_philox(double* X, int64_t n, int64_t n_halo, uint64_t seed, Chol L,
@@ -244,8 +255,8 @@ struct BatchDims {      // grid extents over the beams of a batch
 };
 hipError_t launch_batch_particles_bin(const BeamDev* beams, int nb, const BatchDims& bd, int shape,
                                       int parity, bool first, hipStream_t s);
-// every beam's per-tile integer charge windows set to zero
-hipError_t launch_batch_clear_tacc(const BeamDev* beams, int nb, hipStream_t s);
+// launch_call_setup for every beam
+hipError_t launch_batch_call_setup(const BeamDev* beams, int nb, hipStream_t s);
 // first: the call's first step, whose binning moved the particles into tile order; later steps
 // only rank them, and the deposit and the gather-kick read the step's input through the ranking
 template <typename T>
@@ -258,7 +269,6 @@ hipError_t launch_batch_unpermute(const BeamDev* beams, int nb, const BatchDims&
                                   hipStream_t s);
 hipError_t launch_batch_prologue_particles(const BeamDev* beams, int nb, const BatchDims& bd,
                                            hipStream_t s);
-hipError_t launch_batch_box_reset(const BeamDev* beams, int nb, hipStream_t s);
 hipError_t launch_batch_geometry(const BeamDev* beams, int nb, hipStream_t s);
 template <typename T>
 hipError_t launch_batch_zero_rho(const BeamDev* beams, int nb, const BatchDims& bd, hipStream_t s);

@@ -23,13 +23,25 @@ int grid_for(int64_t n) {
 
 // ---------------------------------------------------------------------------- box and geometry
 
-__global__ void k_box_reset(Box* box) {
-  int t = threadIdx.x;
-  if (t < 3) {
-    box->mn[t] = ~0ull;
-    box->mx[t] = 0ull;
+__device__ __forceinline__ void box_slot_reset(BoxSlot* slot) {
+  for (int a = 0; a < 3; ++a) {
+    slot->mn[a] = ~0ull;
+    slot->mx[a] = 0ull;
   }
-  if (t == 0) box->nonfinite = 0u;
+  slot->nonfinite = 0u;
+}
+
+__device__ __forceinline__ void call_setup_body(Box* box, unsigned long long* __restrict__ tacc,
+                                                int64_t count, int blk, int nblk) {
+  if (blk == 0 && threadIdx.x < kBoxSlots) box_slot_reset(box->slot + threadIdx.x);
+  for (int64_t i = blk * (int64_t)kBlock + threadIdx.x; i < count; i += (int64_t)nblk * kBlock)
+    tacc[i] = 0ull;
+}
+
+__global__ __launch_bounds__(kBlock) void k_call_setup(Box* box,
+                                                       unsigned long long* __restrict__ tacc,
+                                                       int64_t count) {
+  call_setup_body(box, tacc, count, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(kBlock) void k_box(const double* __restrict__ X, int64_t n, Box* box) {
@@ -53,14 +65,29 @@ __global__ __launch_bounds__(kBlock) void k_box(const double* __restrict__ X, in
 // which is sticky until the beam is initialised again.
 // The origin's product and difference are rounded separately (no fused multiply-add), as a
 // plain float64 evaluation of the same formula does.
-__device__ void geometry_from_box(const Box* box, Geom* g, const Consts& c) {
+// Run by one wave: lane t takes slot t of the box and empties it.
+__device__ void geometry_from_box(Box* box, Geom* g, const Consts& c) {
 #pragma clang fp contract(off)
   int nn[3] = {c.nx, c.ny, c.nz};
-  bool bad = box->nonfinite != 0u;
+  BoxSlot* slot = box->slot + threadIdx.x;
+  unsigned long long mn[3], mx[3];
+  for (int a = 0; a < 3; ++a) {
+    mn[a] = slot->mn[a];
+    mx[a] = slot->mx[a];
+  }
+  bool bad = __ballot(slot->nonfinite != 0u) != 0ull;
+  box_slot_reset(slot);
+  for (int off = 32; off > 0; off >>= 1)
+    for (int a = 0; a < 3; ++a) {
+      const unsigned long long l = __shfl_xor(mn[a], off), h = __shfl_xor(mx[a], off);
+      mn[a] = l < mn[a] ? l : mn[a];
+      mx[a] = h > mx[a] ? h : mx[a];
+    }
+  if (threadIdx.x != 0) return;
   double lo[3], hi[3];
   for (int a = 0; a < 3; ++a) {
-    lo[a] = ord_dec(box->mn[a]);
-    hi[a] = ord_dec(box->mx[a]);
+    lo[a] = ord_dec(mn[a]);
+    hi[a] = ord_dec(mx[a]);
     if (!(hi[a] > lo[a])) bad = true;
   }
   if (bad) {
@@ -78,8 +105,7 @@ __device__ void geometry_from_box(const Box* box, Geom* g, const Consts& c) {
   g->h_rest[2] = c.gamma * g->h[2];
 }
 
-__global__ void k_geometry(const Box* box, Geom* g, Consts c) {
-  if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(kBoxSlots) void k_geometry(Box* box, Geom* g, Consts c) {
   geometry_from_box(box, g, c);
 }
 
@@ -375,22 +401,17 @@ __global__ __launch_bounds__(kBlock) void k_zero(T* p, int64_t count) {
     p[i] = T(0);
 }
 
-// batched: thread b handles beam b
-__global__ void k_box_reset_batch(const BeamDev* __restrict__ beams, int nb) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb) return;
-  Box* box = beams[b].box;
-  for (int a = 0; a < 3; ++a) {
-    box->mn[a] = ~0ull;
-    box->mx[a] = 0ull;
-  }
-  box->nonfinite = 0u;
+__global__ __launch_bounds__(kBlock) void k_call_setup_batch(const BeamDev* __restrict__ beams) {
+  const BeamDev& d = beams[blockIdx.y];
+  const int S = d.c.shape;
+  const int64_t count = (int64_t)d.sp.ntiles * (d.sp.T[0] + S) * (d.sp.T[1] + S) * (d.sp.T[2] + S);
+  call_setup_body(d.box, d.tacc, count, blockIdx.x, gridDim.x);
 }
 
-__global__ void k_geometry_batch(const BeamDev* __restrict__ beams, int nb) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb) return;
-  geometry_from_box(beams[b].box, beams[b].geom, beams[b].c);
+// batched: workgroup b handles beam b
+__global__ __launch_bounds__(kBoxSlots) void k_geometry_batch(const BeamDev* __restrict__ beams) {
+  const BeamDev& d = beams[blockIdx.x];
+  geometry_from_box(d.box, d.geom, d.c);
 }
 
 template <typename T>
@@ -407,13 +428,13 @@ __global__ __launch_bounds__(kBlock) void k_zero_rho_batch(const BeamDev* __rest
 
 // ---------------------------------------------------------------------------- launch wrappers
 
-hipError_t launch_batch_box_reset(const BeamDev* beams, int nb, hipStream_t s) {
-  hipLaunchKernelGGL(k_box_reset_batch, dim3((nb + 63) / 64), dim3(64), 0, s, beams, nb);
+hipError_t launch_batch_call_setup(const BeamDev* beams, int nb, hipStream_t s) {
+  hipLaunchKernelGGL(k_call_setup_batch, dim3(1024, nb), dim3(kBlock), 0, s, beams);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_geometry(const BeamDev* beams, int nb, hipStream_t s) {
-  hipLaunchKernelGGL(k_geometry_batch, dim3((nb + 63) / 64), dim3(64), 0, s, beams, nb);
+  hipLaunchKernelGGL(k_geometry_batch, dim3(nb), dim3(kBoxSlots), 0, s, beams);
   return hipGetLastError();
 }
 
@@ -426,8 +447,8 @@ hipError_t launch_batch_zero_rho(const BeamDev* beams, int nb, const BatchDims& 
 template hipError_t launch_batch_zero_rho<double>(const BeamDev*, int, const BatchDims&, hipStream_t);
 template hipError_t launch_batch_zero_rho<float>(const BeamDev*, int, const BatchDims&, hipStream_t);
 
-hipError_t launch_box_reset(Box* box, hipStream_t s) {
-  hipLaunchKernelGGL(k_box_reset, dim3(1), dim3(64), 0, s, box);
+hipError_t launch_call_setup(Box* box, unsigned long long* tacc, int64_t count, hipStream_t s) {
+  hipLaunchKernelGGL(k_call_setup, dim3(grid_for(count)), dim3(kBlock), 0, s, box, tacc, count);
   return hipGetLastError();
 }
 
@@ -436,8 +457,8 @@ hipError_t launch_box(const double* X, int64_t n, Box* box, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_geometry(const Box* box, Geom* g, Consts c, hipStream_t s) {
-  hipLaunchKernelGGL(k_geometry, dim3(1), dim3(64), 0, s, box, g, c);
+hipError_t launch_geometry(Box* box, Geom* g, Consts c, hipStream_t s) {
+  hipLaunchKernelGGL(k_geometry, dim3(1), dim3(kBoxSlots), 0, s, box, g, c);
   return hipGetLastError();
 }
 

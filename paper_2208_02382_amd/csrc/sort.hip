@@ -1272,15 +1272,6 @@ __global__ __launch_bounds__(256) void k_tile_reduce_batch(const BeamDev* __rest
   tile_reduce_body<S, T>(d.geom, d.c, d.sp, d.tacc, d.tscale, (T*)d.rho, blockIdx.x, gridDim.x);
 }
 
-// every beam's per-tile integer windows set to zero (once per batch call)
-__global__ __launch_bounds__(256) void k_clear_tacc_batch(const BeamDev* __restrict__ beams) {
-  const BeamDev& d = beams[blockIdx.y];
-  const int S = d.c.shape;
-  const int64_t count = (int64_t)d.sp.ntiles * (d.sp.T[0] + S) * (d.sp.T[1] + S) * (d.sp.T[2] + S);
-  for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256)
-    d.tacc[i] = 0ull;
-}
-
 // PERM: reads cur_X (and its ids) through the ranking and writes nxt_X in slot order; else
 // updates nxt_X in place
 template <int S, typename T, bool PERM>
@@ -1661,11 +1652,6 @@ hipError_t launch_batch_deposit(const BeamDev* beams, int nb, const BatchDims& b
     if (first) PIC_DEP_BATCH(2, false); else PIC_DEP_BATCH(2, true);
   }
 #undef PIC_DEP_BATCH
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_clear_tacc(const BeamDev* beams, int nb, hipStream_t s) {
-  hipLaunchKernelGGL(k_clear_tacc_batch, dim3(1024, nb), dim3(256), 0, s, beams);
   return hipGetLastError();
 }
 
