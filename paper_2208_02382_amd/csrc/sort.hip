@@ -1154,29 +1154,33 @@ __global__ __launch_bounds__(kBlk) void k_unpermute(const double* __restrict__ A
 // Final placement through LDS.  After the bucket scatter, bucket b holds exactly the particles
 // with ids [b 2^sh, (b + 1) 2^sh) (the ids are a permutation of 0..n-1), at those same
 // positions of A.  One workgroup of kUBlk threads takes a bucket: each thread keeps the local
-// offsets (id - b 2^sh) of its kUPer items; then, row by row, the values are dropped into an
-// LDS buffer at their offsets, kUStage at a time, and written back to X contiguously, so every
-// store is coalesced.  Each pass loads the row's items eight at a time (the second pass from
-// L2) instead of holding all 32 in registers, which had spilled.  Requires 2^sh <= kUBlk *
-// kUPer (= 32768).
+// offsets (id - b 2^sh) of its PER items; then, row by row, the values are dropped into an
+// LDS buffer at their offsets, STAGE at a time, and written back to X contiguously, so every
+// store is coalesced.  Requires 2^sh <= kUBlk * PER; PER is the smallest that fits, because a
+// thread issues all PER loads (clamped into the bucket) whatever the bucket holds.  Up to PER = 8
+// a row's items stay in registers and the next row's loads are issued before this row's
+// barriers; above, a row is loaded eight items at a time in each pass (the second pass from L2).
 constexpr int kUBlk = 1024;
-constexpr int kUPer = 32;
+constexpr int kUMaxPer = 32;
 constexpr int kUStage = 16384;
 
+template <int PER>
 __global__ __launch_bounds__(kUBlk) void k_unpermute_lds(const double* __restrict__ A,
                                                          const uint32_t* __restrict__ idA,
                                                          int64_t n, int sh,
                                                          const Geom* __restrict__ g,
                                                          double* __restrict__ X) {
-  __shared__ double stage[kUStage];
+  constexpr int STAGE = PER * kUBlk < kUStage ? PER * kUBlk : kUStage;
+  constexpr int G = PER < 8 ? PER : 8;  // loads in flight per thread
+  __shared__ double stage[STAGE];
   if (g->status) return;  // after a device error X keeps the caller's input
   const int64_t b0 = (int64_t)blockIdx.x << sh;
   const int cnt = (int)min((int64_t)1 << sh, n - b0);
   // 16-bit offsets, two per register (2^sh <= 32768); 0xffff marks no item.  An id outside
   // the bucket (impossible for a permutation) is dropped, so LDS stays in bounds.
-  uint32_t offp[kUPer / 2];
+  uint32_t offp[PER / 2];
 #pragma unroll
-  for (int k = 0; k < kUPer; ++k) {
+  for (int k = 0; k < PER; ++k) {
     const int l = threadIdx.x + k * kUBlk;
     uint32_t o = 0xffffu;
     if (l < cnt) {
@@ -1188,28 +1192,51 @@ __global__ __launch_bounds__(kUBlk) void k_unpermute_lds(const double* __restric
     else
       offp[k >> 1] = o;
   }
-  const int nq = (cnt + kUStage - 1) / kUStage;
-  for (int r = 0; r < 6; ++r) {
-    for (int q = 0; q < nq; ++q) {
-      // eight loads in flight per thread, unconditional (clamped into the bucket, cnt >= 1),
-      // then the stores of the items whose offset falls in this pass
+  // G loads, unconditional (clamped into the bucket, cnt >= 1)
+  auto load = [&](int r, int k0, double* v) {
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+      v[j] = A[r * n + b0 + min((int)threadIdx.x + (k0 + j) * kUBlk, cnt - 1)];
+  };
+  auto drop = [&](int k0, int q, const double* v) {
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      const int k = k0 + j;
+      const uint32_t o = (offp[k >> 1] >> (16 * (k & 1))) & 0xffffu;
+      if (o != 0xffffu && (int)(o / STAGE) == q) stage[o % STAGE] = v[j];
+    }
+  };
+  auto flush = [&](int r, int q) {
+    const int len = min(STAGE, cnt - q * STAGE);
+    for (int t = threadIdx.x; t < len; t += kUBlk) X[r * n + b0 + q * STAGE + t] = stage[t];
+  };
+  if constexpr (PER <= 8) {  // one pass per row: the bucket fits the stage
+    double v[2][G];
+    load(0, 0, v[0]);
+#pragma unroll
+    for (int r = 0; r < 6; ++r) {
+      if (r < 5) load(r + 1, 0, v[(r + 1) & 1]);
+      drop(0, 0, v[r & 1]);
+      __syncthreads();
+      flush(r, 0);
+      __syncthreads();
+    }
+  } else {
+    const int nq = (cnt + STAGE - 1) / STAGE;
+    for (int r = 0; r < 6; ++r) {
+      for (int q = 0; q < nq; ++q) {
 #pragma unroll 1
-      for (int k0 = 0; k0 < kUPer; k0 += 8) {
-        double v[8];
+        for (int k0 = 0; k0 < PER; k0 += G) {
+          double v[G];
+          load(r, k0, v);
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          v[j] = A[r * n + b0 + min((int)threadIdx.x + (k0 + j) * kUBlk, cnt - 1)];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int k = k0 + j;
-          const uint32_t o = (offp[k >> 1] >> (16 * (k & 1))) & 0xffffu;
-          if (o != 0xffffu && (int)(o / kUStage) == q) stage[o % kUStage] = v[j];
+          for (int k1 = 0; k1 < PER; k1 += G)  // constant indices into offp
+            if (k1 == k0) drop(k1, q, v);
         }
+        __syncthreads();
+        flush(r, q);
+        __syncthreads();
       }
-      __syncthreads();
-      const int len = min(kUStage, cnt - q * kUStage);
-      for (int t = threadIdx.x; t < len; t += kUBlk) X[r * n + b0 + q * kUStage + t] = stage[t];
-      __syncthreads();
     }
   }
 }
@@ -1288,8 +1315,15 @@ __global__ __launch_bounds__(kBlk) void k_gkd_tiles_batch(const BeamDev* __restr
 }
 
 // reordering at the end: bucket keys of the ids, bucket offsets, bucket scatter, final scatter
-__device__ __forceinline__ void bucket_plan(int64_t n, int* shift, int* nb) {
-  int sh = 0;
+// Buckets of 2^shift consecutive original indices, at most kMaxTiles of them.  A single beam
+// takes at least 2^kMinShift indices per bucket: a block of the bucket scatter then writes runs
+// of many particles per bucket, and the LDS placement's workgroups are full.  A batch places
+// directly (k_unpermute_batch), for which the narrowest buckets are the best (2.4 ms of 167 less
+// per call over 256 beams than with kMinShift).
+constexpr int kMinShift = 12;
+__host__ __device__ __forceinline__ void bucket_plan(int64_t n, int min_shift, int* shift,
+                                                     int* nb) {
+  int sh = min_shift;
   while (((n - 1) >> sh) >= kMaxTiles) ++sh;
   *shift = sh;
   *nb = (int)(((n - 1) >> sh) + 1);
@@ -1300,14 +1334,14 @@ __global__ __launch_bounds__(kBlk) void k_id_hist_batch(const BeamDev* __restric
   const BeamDev& d = beams[blockIdx.y];
   if ((int64_t)blockIdx.x * kItems >= d.c.n) return;
   int sh, nb;
-  bucket_plan(d.c.n, &sh, &nb);
+  bucket_plan(d.c.n, 0, &sh, &nb);
   id_hist_body(cur_id(d, parity), d.c.n, sh, nb, d.keys, d.hist, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(1024) void k_bucket_chunks_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.x];
   int sh, nb;
-  bucket_plan(d.c.n, &sh, &nb);
+  bucket_plan(d.c.n, 0, &sh, &nb);
   SortPlan bp;
   bp.T[0] = bp.T[1] = bp.T[2] = 1;
   bp.NT[0] = nb;
@@ -1323,7 +1357,7 @@ __global__ __launch_bounds__(kBlk) void k_bucket_scatter_batch(const BeamDev* __
   const BeamDev& d = beams[blockIdx.y];
   if ((int64_t)blockIdx.x * kItems >= d.c.n) return;
   int sh, nb;
-  bucket_plan(d.c.n, &sh, &nb);
+  bucket_plan(d.c.n, 0, &sh, &nb);
   scatter_body<true>(cur_X(d, parity), cur_id(d, parity), d.keys, d.geom, d.c.n, nb, d.cursor,
                nxt_X(d, parity), nxt_id(d, parity), blockIdx.x, gridDim.x);
 }
@@ -1339,6 +1373,13 @@ int grid_wide(int64_t n) { return (int)((n + kWItems - 1) / kWItems); }
 // the wide staged scatter once it still fills every CU with a block (256 CUs); below that the
 // 4096-particle blocks of k_scatter<true> keep the device busy
 bool wide_pays(int64_t n) { return grid_wide(n) >= 256; }
+
+// Up to this count the return to the caller's order writes X directly in one launch: the state
+// (48 MB) stays in the 256 MB last-level cache, which takes the scattered 8-byte writes.  Direct
+// against histogram, bucket scatter and LDS placement, us per return: 6.3 / 75 at 1e4 particles,
+// 19 / 77 at 2e5, 81 / 94 at 1e6, 238 / 147 at 2e6, 2343 / 966 at 1.25e7.  (With buckets of 1 to
+// 256 particles the second form took 313 at 1e4, 484 at 1e6 and 1181 at 1.25e7.)
+constexpr int64_t kDirectReturn = 1 << 20;
 
 int grid_stride(int64_t n) {
   int64_t b = (n + kBlk - 1) / kBlk;
@@ -1570,9 +1611,12 @@ hipError_t launch_unpermute(const double* A, const uint32_t* idA, int64_t n, dou
                             uint32_t* keys, uint32_t* hist, uint32_t* cursor, int4* chunks,
                             uint32_t* nchunks, double* B, uint32_t* idB, const Geom* g,
                             hipStream_t s) {
-  int shift = 0;
-  while (((n - 1) >> shift) >= kMaxTiles) ++shift;
-  const int nb = (int)(((n - 1) >> shift) + 1);
+  if (n <= kDirectReturn) {
+    hipLaunchKernelGGL(k_unpermute, dim3(grid_stride(n)), dim3(kBlk), 0, s, A, idA, n, g, X);
+    return hipGetLastError();
+  }
+  int shift, nb;
+  bucket_plan(n, kMinShift, &shift, &nb);
   SortPlan bp;
   bp.T[0] = bp.T[1] = bp.T[2] = 1;
   bp.NT[0] = nb;
@@ -1596,8 +1640,14 @@ hipError_t launch_unpermute(const double* A, const uint32_t* idA, int64_t n, dou
                        nb, cursor, B, idB);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (((int64_t)1 << shift) <= (int64_t)kUBlk * kUPer)
-    hipLaunchKernelGGL(k_unpermute_lds, dim3(nb), dim3(kUBlk), 0, s, B, idB, n, shift, g, X);
+  const int64_t bucket = (int64_t)1 << shift;
+  if (bucket <= kUBlk * 4)
+    hipLaunchKernelGGL(k_unpermute_lds<4>, dim3(nb), dim3(kUBlk), 0, s, B, idB, n, shift, g, X);
+  else if (bucket <= kUBlk * 8)
+    hipLaunchKernelGGL(k_unpermute_lds<8>, dim3(nb), dim3(kUBlk), 0, s, B, idB, n, shift, g, X);
+  else if (bucket <= kUBlk * kUMaxPer)
+    hipLaunchKernelGGL(k_unpermute_lds<kUMaxPer>, dim3(nb), dim3(kUBlk), 0, s, B, idB, n, shift,
+                       g, X);
   else
     hipLaunchKernelGGL(k_unpermute, dim3(grid_stride(n)), dim3(kBlk), 0, s, B, idB, n, g, X);
   return hipGetLastError();
