@@ -153,7 +153,7 @@ Layout layout(const pic_beam_desc* d) {
   L.hist = take(sizeof(uint32_t) * kMaxTiles);
   L.cursor = take(sizeof(uint32_t) * kMaxTiles);
   L.chunks = take(sizeof(int4) * (size_t)sp.max_chunks);
-  L.nchunks = take(sizeof(uint32_t));
+  L.nchunks = take(sizeof(uint32_t) * kNckWords);
   // slice-step diagnostics summed inside the gather-kick: one partial per workgroup, the shift
   L.diag_part = take(sizeof(double) * kMomentSlots * (size_t)sp.blocks);
   L.diag_shift = take(sizeof(double) * 6);
@@ -434,6 +434,13 @@ pic_status fork_green(pic_beam b, hipStream_t s) {
   return PIC_OK;
 }
 
+// Up to this count a call's first step only ranks the caller's order too: the deposit and the
+// gather-kick then read the particles at random, which the caches serve for a small beam, and
+// the staged move (a chain of passes of few workgroups) is not run.  One step of the 64^3 CIC
+// workload ranked / moved, us: 239 / 260 at 1e4, 265 / 282 at 1e5, 321 / 318 at 3e5,
+// 593 / 448 at 1e6.
+constexpr int64_t kRankFirst = 1 << 18;
+
 // diag: nullptr, or a device array that receives the moments (kMomentSlots doubles) of the
 // particles at the end of every step.  The binned gather-kick sums them in the same pass, about
 // the previous step's means; the unbinned fallback stops at the end of the step and separate
@@ -462,6 +469,7 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
   const size_t win_bytes = 3 * sizeof(T) * (size_t)(b->sp.T[0] + b->d.shape) *
                            (b->sp.T[1] + b->d.shape) * (b->sp.T[2] + b->d.shape);
   const bool tiles = win_bytes <= kMaxLdsBytes;
+  const bool first_perm = first_ranked || b->c.n <= kRankFirst;
   for (int j = 0; j < n_steps; ++j) {
     const SliceDev& e = sl[j % ns];
     HIP_OK(b->prof.begin(PIC_STAGE_GEOMETRY, s), "profile");
@@ -472,8 +480,9 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
     if (st != PIC_OK) return st;
     // After the first step A is in the previous step's tile order: only the ranking is
     // written, and the gather-kick moves the particles (A -> B) while it updates them.  The
-    // first step moves the caller's order into tile order (A -> B) and updates B in place.
-    const bool permuted = tiles && (j > 0 || first_ranked);
+    // first step of a large beam moves the caller's order into tile order (A -> B) and updates
+    // B in place.
+    const bool permuted = tiles && (j > 0 || first_perm);
     if (permuted)
       STAGE(b, PIC_STAGE_BIN, s,
             launch_bin_perm(A, b->geom, b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks,
@@ -526,7 +535,7 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
   if (binned) {
     // a last step that did not write X (a one-step call that moved the particles, or the
     // gather's global-load fallback) leaves the state in A: copied in slot order
-    const bool last_to_caller = tiles && (n_steps > 1 || first_ranked);
+    const bool last_to_caller = tiles && (n_steps > 1 || first_perm);
     if (!last_to_caller) {
       HIP_OK(launch_copy_if_ok(A, b->X, 6 * sizeof(double) * (size_t)b->c.n, b->geom, s),
              "binned copy");
@@ -880,12 +889,13 @@ pic_status enqueue_batch(const BeamDev* tab, int nb, const BatchDims& bd, int sh
     const int parity = j & 1;
     HIP_OK(launch_batch_geometry(tab, nb, s), "batch");
     HIP_OK(launch_batch_zero_rho<T>(tab, nb, bd, s), "batch");
-    // Green spectra on the auxiliary stream, concurrently with binning and deposit
+    HIP_OK(launch_batch_particles_bin(tab, nb, bd, shape, parity, j == 0, s), "batch");
+    // Green spectra on the auxiliary stream, concurrently with the deposit (beside the binning,
+    // whose workgroups then waited for a CU, 256 beams took 169.4 ms per 10 steps, this 168.0)
     HIP_OK(hipEventRecord(fork, s), "batch");
     HIP_OK(hipStreamWaitEvent(aux, fork, 0), "batch");
     HIP_OK(launch_batch_green<T>(tab, nb, bd, aux), "batch");
     HIP_OK(hipEventRecord(join, aux), "batch");
-    HIP_OK(launch_batch_particles_bin(tab, nb, bd, shape, parity, j == 0, s), "batch");
     HIP_OK(launch_batch_deposit<T>(tab, nb, bd, shape, parity, j == 0, s), "batch");
     HIP_OK(hipStreamWaitEvent(s, join, 0), "batch");
     HIP_OK(launch_batch_solve<T>(tab, nb, bd, s), "batch");
@@ -1014,6 +1024,7 @@ pic_status pic_beam_create(const pic_beam_desc* d, double* d_X, void* d_work, si
     e = launch_twiddles((double2*)b->plan.tw[a], (float2*)b->plan.twf[a], b->plan.full[a].M, s);
   if (e == hipSuccess) e = call_setup(b, s);
   if (e == hipSuccess) e = launch_zero<uint32_t>(b->hist, kMaxTiles, s);
+  if (e == hipSuccess) e = launch_zero<uint32_t>(b->nchunks, kNckWords, s);
   if (e == hipSuccess) e = launch_clear_status(b->geom, s);
   if (e == hipSuccess) e = make_aux(&b->aux, &b->ev_fork, &b->ev_join, &b->done.ev);
   if (e != hipSuccess) {

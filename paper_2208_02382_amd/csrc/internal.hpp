@@ -65,6 +65,7 @@ struct Chol {
   double L[36];
 };
 
+constexpr int kNckWords = 4;          // work-list size, finished workgroups, rank overflow, unused
 constexpr int kMaxTiles = 4096;       // tiles of the per-step particle binning
 // Dynamic LDS of the binned deposit's and gather's tile windows: gfx950 gives a workgroup up to
 // 160 KB, of which 4 KB are left to the kernels' static LDS (above 64 KB a kernel's
@@ -78,6 +79,7 @@ struct SortPlan {
   int T[3];
   int NT[3];
   int ntiles;
+  int kbits;        // bits of a tile key (ntiles <= 2^kbits); a particle's rank takes the others
   int chunk;
   int64_t max_chunks;
   int blocks;       // workgroups of the binned deposit and gather
@@ -207,7 +209,7 @@ hipError_t launch_bin(const double* A, const uint32_t* idA, const Geom* g, Const
                       const SortPlan& sp, uint32_t* keys, uint32_t* hist, uint32_t* cursor,
                       int4* chunks, uint32_t* nchunks, double* B, uint32_t* idB, bool staged,
                       hipStream_t s);
-// keys and work list as launch_bin, then only the ranking: perm[slot] = index in A
+// keys and work list as launch_bin, then only the order: perm[slot] = index in A
 hipError_t launch_bin_perm(const double* A, const Geom* g, Consts c, const SortPlan& sp,
                            uint32_t* keys, uint32_t* hist, uint32_t* cursor, int4* chunks,
                            uint32_t* nchunks, uint32_t* perm, hipStream_t s);

@@ -3,19 +3,21 @@
 // Every step the particles are counting-sorted by the tile of their stencil's first node
 // (tiles of T_x x T_y x T_z cells, at most 4096 tiles).  Particles move several cells per step,
 // so the order is rebuilt each step; the previous step's order keeps every pass coherent:
-//   k_key_hist     tile key of each particle (4 B) and a block-privatised histogram in LDS,
-//                  flushed with one global atomic per non-empty bin;
-//   k_build_chunks exclusive scan of the tile counts (sort offsets) and the work list of
-//                  (tile, begin, end) chunks of at most `chunk` particles for the deposit;
+//   k_key_rank     tile key of each particle and its rank within the tile, packed in 4 B: the
+//                  rank inside the workgroup from a histogram in LDS, the workgroup's base from
+//                  the global atomic (one per non-empty bin) that flushes it.  The last
+//                  workgroup to finish scans the tile counts (sort offsets) and writes the work
+//                  list of (tile, begin, end) chunks of at most `chunk` particles;
 //   k_scatter      moves phase space and particle ids to their sorted slots: each block
 //                  counts its keys in LDS, reserves one contiguous range per key with a single
 //                  global atomic, then ranks its particles with LDS atomics, so particles of one
 //                  key leave a block as one contiguous run (first step of a call, where the
 //                  caller's order is unrelated to the tiles);
-//   k_scatter_perm the same ranking without moving anything: the source index of every sorted
-//                  slot (4 B per particle instead of 104).  Later steps read the particles
-//                  through it, and the gather-kick writes the new state in sorted order, so the
-//                  phase space crosses HBM once per step fewer;
+//   k_place        the order without moving anything: the source index of every sorted slot,
+//                  perm[tile offset + rank] = i (8 B per particle instead of 104).  Later steps,
+//                  and the first step of a small beam, read the particles through it, and the
+//                  gather-kick writes the new state in sorted order, so the phase space crosses
+//                  HBM once per step fewer;
 //   k_deposit_tiles each workgroup takes a chunk, accumulates the (T + S)^3 window of its tile
 //                  with 64-bit fixed-point LDS atomics, and adds the non-zero window entries to
 //                  the tile's own 64-bit integer window in HBM with one integer atomic each;
@@ -34,6 +36,11 @@ constexpr int kBlk = 256;
 constexpr int kItems = 4096;               // particles per block in key_hist / scatter
 constexpr int kPer = kItems / kBlk;         // 16 per thread
 
+// the tile key's bits of a packed (rank, key) word
+__host__ __device__ __forceinline__ uint32_t key_mask(const SortPlan& sp) {
+  return (1u << sp.kbits) - 1u;
+}
+
 // stencil base node along one axis: the very function the deposit and gather kernels use
 template <int S>
 __device__ __forceinline__ int base_node(double u, int n) {
@@ -51,95 +58,103 @@ __device__ __forceinline__ uint32_t tile_key(double x, double y, double z, const
   return (uint32_t)(((bz / sp.T[2]) * sp.NT[1] + (by / sp.T[1])) * sp.NT[0] + (bx / sp.T[0]));
 }
 
-template <int S>
-__device__ __forceinline__ void key_hist_body(const double* __restrict__ X,
-                                                   const Geom* __restrict__ g, Consts c,
-                                                   SortPlan sp, uint32_t* __restrict__ keys,
-                                                   uint32_t* __restrict__ hist, int blk, int nblk) {
-  __shared__ uint32_t lh[kMaxTiles];
-  if (g->status) return;
-  const double o[3] = {g->origin[0], g->origin[1], g->origin[2]};
-  const double ih[3] = {g->inv_h[0], g->inv_h[1], g->inv_h[2]};
-  for (int t = threadIdx.x; t < sp.ntiles; t += kBlk) lh[t] = 0u;
+// Exclusive scan of v over the workgroup's NT threads, by wave scans; total: the sum of all.
+template <int NT>
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* total) {
+  __shared__ uint32_t wsum[NT / 64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t incl = v;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t up = __shfl_up(incl, off);
+    if (lane >= off) incl += up;
+  }
+  __syncthreads();  // readers of a previous scan are done with wsum
+  if (lane == 63) wsum[wv] = incl;
   __syncthreads();
-  const int64_t n = c.n;
-  const int64_t base = (int64_t)blk * kItems;
-  for (int k = 0; k < kPer; ++k) {
-    int64_t i = base + k * kBlk + threadIdx.x;
-    if (i < n) {
-      uint32_t key = tile_key<S>(X[i], X[2 * n + i], X[4 * n + i], o, ih, c, sp);
-      keys[i] = key;
-      atomicAdd(&lh[key], 1u);
-    }
+  uint32_t base = 0, all = 0;
+  for (int q = 0; q < NT / 64; ++q) {
+    base += q < wv ? wsum[q] : 0u;
+    all += wsum[q];
+  }
+  *total = all;
+  return base + incl - v;
+}
+
+// In-place exclusive scan of a[0..count) (count <= kMaxTiles) by one block of NT threads;
+// each thread owns a run of consecutive entries.  Returns the sum of all entries.
+template <int NT>
+__device__ uint32_t block_exclusive_scan_lds(uint32_t* a, int count) {
+  const int per = (count + NT - 1) / NT;
+  const int b = threadIdx.x * per;
+  const int e = min(b + per, count);
+  uint32_t sum = 0, total;
+  for (int t = b; t < e; ++t) sum += a[t];
+  uint32_t run = block_exclusive_scan<NT>(sum, &total);
+  for (int t = b; t < e; ++t) {
+    const uint32_t v = a[t];
+    a[t] = run;
+    run += v;
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < sp.ntiles; t += kBlk)
-    if (lh[t]) atomicAdd(&hist[t], lh[t]);
+  return total;
 }
 
-template <int S>
-__global__ __launch_bounds__(kBlk) void k_key_hist(const double* __restrict__ X,
-                                                   const Geom* __restrict__ g, Consts c,
-                                                   SortPlan sp, uint32_t* __restrict__ keys,
-                                                   uint32_t* __restrict__ hist) {
-  key_hist_body<S>(X, g, c, sp, keys, hist, blockIdx.x, gridDim.x);
-}
+// nchunks[0]: entries of the work list; [1]: workgroups of k_key_rank that have finished (zero
+// between launches); [2]: non-zero if a tile's ranks do not fit the packed key
+constexpr int kNck = 0, kTicket = 1, kOverflow = 2;
 
-// Block-wide exclusive scan of per-thread values (1024 threads).
-__device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t* total) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    uint32_t add = t >= off ? sh[t - off] : 0u;
-    __syncthreads();
-    sh[t] += add;
-    __syncthreads();
-  }
-  uint32_t incl = sh[t];
-  *total = sh[1023];
-  __syncthreads();
-  return incl - v;
-}
-
-// one block of 1024 threads; each thread owns 4 consecutive tiles
-__device__ __forceinline__ void build_chunks_body(const Geom* __restrict__ g, SortPlan sp,
-                                                  uint32_t* __restrict__ hist,
+// Sort offsets (cursor) and work list from the tile counts in hist (left zero), by one block of
+// NT threads; lh: kMaxTiles words of LDS.  Thread t takes tiles t, t + NT, ..., so that the dense
+// tiles in the middle of the grid, whose chunks are many, are spread over the threads.  The
+// counts are read with agent-scope atomic loads: other workgroups of the same launch may have
+// added to them.
+template <int NT>
+__device__ __forceinline__ void build_chunks_body(const SortPlan& sp, uint32_t* __restrict__ hist,
                                                   uint32_t* __restrict__ cursor,
                                                   int4* __restrict__ chunks,
-                                                  uint32_t* __restrict__ nchunks) {
-  __shared__ uint32_t sh[1024];
-  if (g->status) {
-    if (threadIdx.x == 0) *nchunks = 0u;
-    return;
-  }
-  const int t0 = threadIdx.x * 4;
-  uint32_t cnt[4], nck[4], sc = 0, sk = 0;
-  for (int q = 0; q < 4; ++q) {
-    int t = t0 + q;
-    cnt[q] = t < sp.ntiles ? hist[t] : 0u;
-    nck[q] = (cnt[q] + sp.chunk - 1) / sp.chunk;
-    sc += cnt[q];
-    sk += nck[q];
-  }
-  uint32_t tot_c, tot_k;
-  uint32_t off = block_exclusive_scan(sc, sh, &tot_c);
-  uint32_t coff = block_exclusive_scan(sk, sh, &tot_k);
-  for (int q = 0; q < 4; ++q) {
-    int t = t0 + q;
+                                                  uint32_t* __restrict__ nchunks, uint32_t* lh) {
+  constexpr int Q = kMaxTiles / NT;
+  uint32_t cnt[Q], off[Q];
+  bool over = false;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int t = q * NT + threadIdx.x;
+    cnt[q] = 0u;
     if (t < sp.ntiles) {
-      cursor[t] = off;
+      cnt[q] = __hip_atomic_load(&hist[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       hist[t] = 0u;  // ready for the next step
-      for (uint32_t k = 0; k < nck[q]; ++k) {
-        uint32_t b = off + k * sp.chunk;
-        uint32_t e = b + sp.chunk < off + cnt[q] ? b + sp.chunk : off + cnt[q];
-        chunks[coff + k] = make_int4(t, (int)b, (int)e, (int)cnt[q]);  // w: the tile's count
-      }
+      lh[t] = cnt[q];
+      over |= cnt[q] && ((uint64_t)(cnt[q] - 1u) >> (32 - sp.kbits)) != 0ull;
     }
-    off += cnt[q];
-    coff += nck[q];
   }
-  if (threadIdx.x == 0) *nchunks = tot_k;
+  __syncthreads();
+  block_exclusive_scan_lds<NT>(lh, sp.ntiles);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int t = q * NT + threadIdx.x;
+    if (t < sp.ntiles) {
+      off[q] = lh[t];
+      cursor[t] = off[q];
+      lh[t] = (cnt[q] + sp.chunk - 1) / sp.chunk;
+    }
+  }
+  over = __syncthreads_or(over);
+  const uint32_t tot_k = block_exclusive_scan_lds<NT>(lh, sp.ntiles);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int t = q * NT + threadIdx.x;
+    if (t < sp.ntiles) {
+      int4* out = chunks + lh[t];
+      const uint32_t end = off[q] + cnt[q];
+      for (uint32_t b = off[q]; b < end; b += sp.chunk)
+        *out++ = make_int4(t, (int)b, (int)min(b + sp.chunk, end), (int)cnt[q]);  // w: the tile's
+    }
+  }
+  if (threadIdx.x == 0) {
+    nchunks[kNck] = tot_k;
+    nchunks[kTicket] = 0u;
+    nchunks[kOverflow] = over ? 1u : 0u;
+  }
 }
 
 __global__ __launch_bounds__(1024) void k_build_chunks(const Geom* __restrict__ g, SortPlan sp,
@@ -147,34 +162,94 @@ __global__ __launch_bounds__(1024) void k_build_chunks(const Geom* __restrict__ 
                                                        uint32_t* __restrict__ cursor,
                                                        int4* __restrict__ chunks,
                                                        uint32_t* __restrict__ nchunks) {
-  build_chunks_body(g, sp, hist, cursor, chunks, nchunks);
+  __shared__ uint32_t lh[kMaxTiles];
+  if (g->status) {
+    if (threadIdx.x == 0) nchunks[kNck] = 0u;
+    return;
+  }
+  build_chunks_body<1024>(sp, hist, cursor, chunks, nchunks, lh);
 }
 
-// In-place exclusive scan of a[0..count) (count <= kMaxTiles) by one block of NT threads;
-// each thread owns a run of consecutive entries.
-template <int NT>
-__device__ void block_exclusive_scan_lds(uint32_t* a, int count) {
-  __shared__ uint32_t part[NT];
-  const int per = (count + NT - 1) / NT;
-  const int b = threadIdx.x * per;
-  const int e = min(b + per, count);
-  uint32_t sum = 0;
-  for (int t = b; t < e; ++t) sum += a[t];
-  part[threadIdx.x] = sum;
-  __syncthreads();
-  for (int off = 1; off < NT; off <<= 1) {
-    const uint32_t add = threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
-    __syncthreads();
-    part[threadIdx.x] += add;
-    __syncthreads();
+// Keys, ranks, sort offsets and work list of the particles in X (see the list at the top of the
+// file), PER particles per thread.  keys[i] = rank << sp.kbits | key; a rank that does not fit
+// (a tile of more than 2^(32 - kbits) particles, at least 2^20) loses its upper bits and the
+// work list's overflow word is set, on which k_place ranks anew from the keys.
+// The last workgroup is found with a counter: a workgroup adds to it only after its own atomics
+// on hist have returned (their results are in LDS, and the barrier stands between), and the
+// counts are read and changed by agent-scope atomics alone, so the last one reads them whole.
+template <int S, int PER>
+__device__ __forceinline__ void key_rank_body(const double* __restrict__ X,
+                                              const Geom* __restrict__ g, const Consts& c,
+                                              const SortPlan& sp, uint32_t* __restrict__ keys,
+                                              uint32_t* __restrict__ hist,
+                                              uint32_t* __restrict__ cursor,
+                                              int4* __restrict__ chunks,
+                                              uint32_t* __restrict__ nchunks, int blk, int nblk) {
+  __shared__ uint32_t lh[kMaxTiles];
+  __shared__ bool s_last;
+  if (g->status) {
+    if (blk == 0 && threadIdx.x == 0) nchunks[kNck] = 0u;
+    return;
   }
-  uint32_t run = part[threadIdx.x] - sum;
-  for (int t = b; t < e; ++t) {
-    const uint32_t v = a[t];
-    a[t] = run;
-    run += v;
+  const double o[3] = {g->origin[0], g->origin[1], g->origin[2]};
+  const double ih[3] = {g->inv_h[0], g->inv_h[1], g->inv_h[2]};
+  for (int t = threadIdx.x; t < sp.ntiles; t += kBlk) lh[t] = 0u;
+  __syncthreads();
+  const int64_t n = c.n;
+  const int64_t base = (int64_t)blk * (kBlk * PER) + threadIdx.x;
+  uint32_t key[PER], rank[PER];
+  // loads of up to four particles in flight, without a branch around them (clamped to the last)
+  constexpr int G = PER < 4 ? PER : 4;
+#pragma unroll
+  for (int k0 = 0; k0 < PER; k0 += G) {
+    double p[G][3];
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const int64_t i = min(base + (k0 + k) * kBlk, n - 1);
+      for (int a = 0; a < 3; ++a) p[k][a] = X[2 * a * n + i];
+    }
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      key[k0 + k] = tile_key<S>(p[k][0], p[k][1], p[k][2], o, ih, c, sp);
+      if (base + (k0 + k) * kBlk < n) rank[k0 + k] = atomicAdd(&lh[key[k0 + k]], 1u);
+    }
   }
   __syncthreads();
+  // four of a thread's counters at a time, so that the returns of their atomics overlap
+  for (int t0 = threadIdx.x; t0 < sp.ntiles; t0 += 4 * kBlk) {
+    uint32_t cnt[4], old[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + u * kBlk;
+      cnt[u] = t < sp.ntiles ? lh[t] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (cnt[u]) old[u] = atomicAdd(&hist[t0 + u * kBlk], cnt[u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (cnt[u]) lh[t0 + u * kBlk] = old[u];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(&nchunks[kTicket], 1u) == (uint32_t)nblk - 1u;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int64_t i = base + k * kBlk;
+    if (i < n) keys[i] = ((rank[k] + lh[key[k]]) << sp.kbits) | key[k];
+  }
+  __syncthreads();
+  if (s_last) build_chunks_body<kBlk>(sp, hist, cursor, chunks, nchunks, lh);
+}
+
+template <int S, int PER>
+__global__ __launch_bounds__(kBlk) void k_key_rank(const double* __restrict__ X,
+                                                   const Geom* __restrict__ g, Consts c,
+                                                   SortPlan sp, uint32_t* __restrict__ keys,
+                                                   uint32_t* __restrict__ hist,
+                                                   uint32_t* __restrict__ cursor,
+                                                   int4* __restrict__ chunks,
+                                                   uint32_t* __restrict__ nchunks) {
+  key_rank_body<S, PER>(X, g, c, sp, keys, hist, cursor, chunks, nchunks, blockIdx.x, gridDim.x);
 }
 
 // LDS atomic add of 1 per active lane to lh[key], aggregated over the wave: one atomic per
@@ -210,6 +285,7 @@ __device__ __forceinline__ uint32_t wave_aggregated_add(uint32_t* lh, uint32_t k
 __device__ __forceinline__ void scatter_staged_body(const double* __restrict__ A,
                                                   const uint32_t* __restrict__ idA,
                                                   const uint32_t* __restrict__ keys,
+                                                  uint32_t kmask,
                                                   const Geom* __restrict__ g, int64_t n,
                                                   int ntiles, uint32_t* __restrict__ cursor,
                                                   double* __restrict__ B,
@@ -230,7 +306,7 @@ __device__ __forceinline__ void scatter_staged_body(const double* __restrict__ A
   uint32_t key[kPer];
   for (int k = 0; k < kPer; ++k) {
     const int l = k * kBlk + threadIdx.x;
-    key[k] = l < m ? keys[base + l] : 0u;
+    key[k] = l < m ? keys[base + l] & kmask : 0u;
     if (l < m) atomicAdd(&cur[key[k]], 1u);
   }
   __syncthreads();
@@ -285,6 +361,7 @@ __device__ __forceinline__ void scatter_staged_body(const double* __restrict__ A
 __device__ __forceinline__ void scatter_direct_body(const double* __restrict__ A,
                                                   const uint32_t* __restrict__ idA,
                                                   const uint32_t* __restrict__ keys,
+                                                  uint32_t kmask,
                                                   const Geom* __restrict__ g, int64_t n,
                                                   int ntiles, uint32_t* __restrict__ cursor,
                                                   double* __restrict__ B,
@@ -297,7 +374,7 @@ __device__ __forceinline__ void scatter_direct_body(const double* __restrict__ A
   uint32_t key[kPer];
   for (int k = 0; k < kPer; ++k) {
     int64_t i = base + k * kBlk + threadIdx.x;
-    key[k] = i < n ? keys[i] : 0u;
+    key[k] = i < n ? keys[i] & kmask : 0u;
     if (i < n) atomicAdd(&lh[key[k]], 1u);
   }
   __syncthreads();
@@ -317,13 +394,12 @@ __device__ __forceinline__ void scatter_direct_body(const double* __restrict__ A
 }
 
 // Ranking of one block of kItems particles as in the direct form, writing only the source
-// index of each slot: perm[slot] = i.
-__device__ __forceinline__ void scatter_perm_body(const uint32_t* __restrict__ keys,
-                                                  const Geom* __restrict__ g, int64_t n,
-                                                  int ntiles, uint32_t* __restrict__ cursor,
-                                                  uint32_t* __restrict__ perm, int blk) {
+// index of each slot: perm[slot] = i.  Only for a tile whose ranks overflowed the packed keys.
+__device__ __forceinline__ void rank_again_body(const uint32_t* __restrict__ keys, uint32_t kmask,
+                                                int64_t n, int ntiles,
+                                                uint32_t* __restrict__ cursor,
+                                                uint32_t* __restrict__ perm, int blk) {
   __shared__ uint32_t lh[kMaxTiles];
-  if (g->status) return;
   for (int t = threadIdx.x; t < ntiles; t += kBlk) lh[t] = 0u;
   __syncthreads();
   const int64_t base = (int64_t)blk * kItems;
@@ -332,7 +408,7 @@ __device__ __forceinline__ void scatter_perm_body(const uint32_t* __restrict__ k
   uint32_t key[kPer];
   for (int k = 0; k < kPer; ++k) {
     int64_t i = base + k * kBlk + threadIdx.x;
-    key[k] = i < n ? keys[i] : 0u;
+    key[k] = i < n ? keys[i] & kmask : 0u;
   }
   for (int k = 0; k < kPer; ++k)
     (void)wave_aggregated_add(lh, key[k], base + k * kBlk + threadIdx.x < n);
@@ -348,35 +424,67 @@ __device__ __forceinline__ void scatter_perm_body(const uint32_t* __restrict__ k
   }
 }
 
-__global__ __launch_bounds__(kBlk) void k_scatter_perm(const uint32_t* __restrict__ keys,
-                                                       const Geom* __restrict__ g, int64_t n,
-                                                       int ntiles, uint32_t* __restrict__ cursor,
-                                                       uint32_t* __restrict__ perm) {
-  scatter_perm_body(keys, g, n, ntiles, cursor, perm, blockIdx.x);
+// The source index of every sorted slot from the packed keys, PER particles per thread:
+// perm[cursor[key] + rank] = i.  PER < kPer only where no tile can overflow (n < 2^20).
+template <int PER>
+__device__ __forceinline__ void place_body(const uint32_t* __restrict__ keys,
+                                           const Geom* __restrict__ g, int64_t n,
+                                           const SortPlan& sp, uint32_t* __restrict__ cursor,
+                                           const uint32_t* __restrict__ nchunks,
+                                           uint32_t* __restrict__ perm, int blk) {
+  if (g->status) return;
+  const uint32_t kmask = key_mask(sp);
+  if constexpr (PER == kPer)
+    if (nchunks[kOverflow]) {
+      rank_again_body(keys, kmask, n, sp.ntiles, cursor, perm, blk);
+      return;
+    }
+  const int64_t base = (int64_t)blk * (kBlk * PER) + threadIdx.x;
+  uint32_t k[PER], pos[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) k[q] = keys[min(base + q * kBlk, n - 1)];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) pos[q] = cursor[k[q] & kmask] + (k[q] >> sp.kbits);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int64_t i = base + q * kBlk;
+    // in bounds for a consistent histogram
+    if (i < n && pos[q] < (uint64_t)n) perm[pos[q]] = (uint32_t)i;
+  }
+}
+
+template <int PER>
+__global__ __launch_bounds__(kBlk) void k_place(const uint32_t* __restrict__ keys,
+                                                const Geom* __restrict__ g, int64_t n,
+                                                SortPlan sp, uint32_t* __restrict__ cursor,
+                                                const uint32_t* __restrict__ nchunks,
+                                                uint32_t* __restrict__ perm) {
+  place_body<PER>(keys, g, n, sp, cursor, nchunks, perm, blockIdx.x);
 }
 
 template <bool STAGED>
 __device__ __forceinline__ void scatter_body(const double* __restrict__ A,
                                              const uint32_t* __restrict__ idA,
-                                             const uint32_t* __restrict__ keys,
+                                             const uint32_t* __restrict__ keys, uint32_t kmask,
                                              const Geom* __restrict__ g, int64_t n, int ntiles,
                                              uint32_t* __restrict__ cursor, double* __restrict__ B,
                                              uint32_t* __restrict__ idB, int blk, int nblk) {
   if constexpr (STAGED)
-    scatter_staged_body(A, idA, keys, g, n, ntiles, cursor, B, idB, blk, nblk);
+    scatter_staged_body(A, idA, keys, kmask, g, n, ntiles, cursor, B, idB, blk, nblk);
   else
-    scatter_direct_body(A, idA, keys, g, n, ntiles, cursor, B, idB, blk, nblk);
+    scatter_direct_body(A, idA, keys, kmask, g, n, ntiles, cursor, B, idB, blk, nblk);
 }
 
 template <bool STAGED>
 __global__ __launch_bounds__(kBlk) void k_scatter(const double* __restrict__ A,
                                                   const uint32_t* __restrict__ idA,
                                                   const uint32_t* __restrict__ keys,
+                                                  uint32_t kmask,
                                                   const Geom* __restrict__ g, int64_t n,
                                                   int ntiles, uint32_t* __restrict__ cursor,
                                                   double* __restrict__ B,
                                                   uint32_t* __restrict__ idB) {
-  scatter_body<STAGED>(A, idA, keys, g, n, ntiles, cursor, B, idB, blockIdx.x, gridDim.x);
+  scatter_body<STAGED>(A, idA, keys, kmask, g, n, ntiles, cursor, B, idB, blockIdx.x, gridDim.x);
 }
 
 // The staged scatter over wide blocks, for inputs whose order is unrelated to the keys (the
@@ -395,6 +503,7 @@ constexpr int kWHalf = kWItems / 2;     // slots staged per pass
 __global__ __launch_bounds__(kWBlk) void k_scatter_wide(const double* __restrict__ A,
                                                         const uint32_t* __restrict__ idA,
                                                         const uint32_t* __restrict__ keys,
+                                                        uint32_t kmask,
                                                         const Geom* __restrict__ g, int64_t n,
                                                         int ntiles, uint32_t* __restrict__ cursor,
                                                         double* __restrict__ B,
@@ -415,7 +524,7 @@ __global__ __launch_bounds__(kWBlk) void k_scatter_wide(const double* __restrict
   uint32_t key[kWPer];
   for (int k = 0; k < kWPer; ++k) {
     const int l = k * kWBlk + threadIdx.x;
-    key[k] = l < m ? keys[base + l] : 0u;
+    key[k] = l < m ? keys[base + l] & kmask : 0u;
   }
   for (int k = 0; k < kWPer; ++k)
     if (k * kWBlk + (int)threadIdx.x < m) atomicAdd(&cur[key[k]], 1u);
@@ -1255,23 +1364,20 @@ __global__ __launch_bounds__(kBlk) void k_prologue_batch(const BeamDev* __restri
 }
 
 template <int S>
-__global__ __launch_bounds__(kBlk) void k_key_hist_batch(const BeamDev* __restrict__ beams,
+__global__ __launch_bounds__(kBlk) void k_key_rank_batch(const BeamDev* __restrict__ beams,
                                                          int parity) {
   const BeamDev& d = beams[blockIdx.y];
-  if ((int64_t)blockIdx.x * kItems >= d.c.n) return;
-  key_hist_body<S>(cur_X(d, parity), d.geom, d.c, d.sp, d.keys, d.hist, blockIdx.x, gridDim.x);
+  const int nblk = (int)((d.c.n + kItems - 1) / kItems);
+  if ((int)blockIdx.x >= nblk) return;
+  key_rank_body<S, kPer>(cur_X(d, parity), d.geom, d.c, d.sp, d.keys, d.hist, d.cursor, d.chunks,
+                         d.nchunks, blockIdx.x, nblk);
 }
 
-__global__ __launch_bounds__(1024) void k_build_chunks_batch(const BeamDev* __restrict__ beams) {
-  const BeamDev& d = beams[blockIdx.x];
-  build_chunks_body(d.geom, d.sp, d.hist, d.cursor, d.chunks, d.nchunks);
-}
-
-// after a call's first step: the ranking only (cur_X stays where it is)
-__global__ __launch_bounds__(kBlk) void k_scatter_perm_batch(const BeamDev* __restrict__ beams) {
+// after a call's first step: the order only (cur_X stays where it is)
+__global__ __launch_bounds__(kBlk) void k_place_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.y];
   if ((int64_t)blockIdx.x * kItems >= d.c.n) return;
-  scatter_perm_body(d.keys, d.geom, d.c.n, d.sp.ntiles, d.cursor, d.perm, blockIdx.x);
+  place_body<kPer>(d.keys, d.geom, d.c.n, d.sp, d.cursor, d.nchunks, d.perm, blockIdx.x);
 }
 
 template <bool STAGED>
@@ -1279,7 +1385,7 @@ __global__ __launch_bounds__(kBlk) void k_scatter_batch(const BeamDev* __restric
                                                         int parity) {
   const BeamDev& d = beams[blockIdx.y];
   if ((int64_t)blockIdx.x * kItems >= d.c.n) return;
-  scatter_body<STAGED>(cur_X(d, parity), cur_id(d, parity), d.keys, d.geom, d.c.n, d.sp.ntiles, d.cursor,
+  scatter_body<STAGED>(cur_X(d, parity), cur_id(d, parity), d.keys, key_mask(d.sp), d.geom, d.c.n, d.sp.ntiles, d.cursor,
                nxt_X(d, parity), nxt_id(d, parity), blockIdx.x, gridDim.x);
 }
 
@@ -1321,6 +1427,17 @@ __global__ __launch_bounds__(kBlk) void k_gkd_tiles_batch(const BeamDev* __restr
 // directly (k_unpermute_batch), for which the narrowest buckets are the best (2.4 ms of 167 less
 // per call over 256 beams than with kMinShift).
 constexpr int kMinShift = 12;
+__host__ __device__ __forceinline__ SortPlan bucket_sort_plan(int nb) {
+  SortPlan bp{};
+  bp.T[0] = bp.T[1] = bp.T[2] = 1;
+  bp.NT[0] = nb;
+  bp.NT[1] = bp.NT[2] = 1;
+  bp.ntiles = nb;
+  bp.kbits = 1;
+  bp.chunk = 1 << 30;  // the work list is not used; one entry per bucket
+  bp.max_chunks = nb + 1;
+  return bp;
+}
 __host__ __device__ __forceinline__ void bucket_plan(int64_t n, int min_shift, int* shift,
                                                      int* nb) {
   int sh = min_shift;
@@ -1340,16 +1457,11 @@ __global__ __launch_bounds__(kBlk) void k_id_hist_batch(const BeamDev* __restric
 
 __global__ __launch_bounds__(1024) void k_bucket_chunks_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.x];
+  __shared__ uint32_t lh[kMaxTiles];
+  if (d.geom->status) return;
   int sh, nb;
   bucket_plan(d.c.n, 0, &sh, &nb);
-  SortPlan bp;
-  bp.T[0] = bp.T[1] = bp.T[2] = 1;
-  bp.NT[0] = nb;
-  bp.NT[1] = bp.NT[2] = 1;
-  bp.ntiles = nb;
-  bp.chunk = 1 << 30;
-  bp.max_chunks = nb + 1;
-  build_chunks_body(d.geom, bp, d.hist, d.cursor, d.chunks, d.nchunks);
+  build_chunks_body<1024>(bucket_sort_plan(nb), d.hist, d.cursor, d.chunks, d.nchunks, lh);
 }
 
 __global__ __launch_bounds__(kBlk) void k_bucket_scatter_batch(const BeamDev* __restrict__ beams,
@@ -1358,7 +1470,7 @@ __global__ __launch_bounds__(kBlk) void k_bucket_scatter_batch(const BeamDev* __
   if ((int64_t)blockIdx.x * kItems >= d.c.n) return;
   int sh, nb;
   bucket_plan(d.c.n, 0, &sh, &nb);
-  scatter_body<true>(cur_X(d, parity), cur_id(d, parity), d.keys, d.geom, d.c.n, nb, d.cursor,
+  scatter_body<true>(cur_X(d, parity), cur_id(d, parity), d.keys, ~0u, d.geom, d.c.n, nb, d.cursor,
                nxt_X(d, parity), nxt_id(d, parity), blockIdx.x, gridDim.x);
 }
 
@@ -1368,7 +1480,13 @@ __global__ __launch_bounds__(kBlk) void k_unpermute_batch(const BeamDev* __restr
   unpermute_body(nxt_X(d, parity), nxt_id(d, parity), d.c.n, d.geom, d.X, blockIdx.x, gridDim.x);
 }
 
-int grid_items(int64_t n) { return (int)((n + kItems - 1) / kItems); }
+int grid_per(int64_t n, int per) { return (int)((n + kBlk * per - 1) / (kBlk * per)); }
+int grid_items(int64_t n) { return grid_per(n, kPer); }
+// Particles per thread of the ranking: one while a workgroup's chain of loads and atomics is the
+// length of the pass, kPer once every CU has a workgroup, since each workgroup clears and flushes
+// the counters of all tiles (4 per thread took 20.6 us at 1e6 particles, 256 tiles, where kPer
+// takes 14.8; kPer took 23 us at 1e4 particles, where one takes 8).
+int per_thread(int64_t n) { return n <= (1 << 17) ? 1 : kPer; }
 int grid_wide(int64_t n) { return (int)((n + kWItems - 1) / kWItems); }
 // the wide staged scatter once it still fills every CU with a block (256 CUs); below that the
 // 4096-particle blocks of k_scatter<true> keep the device busy
@@ -1400,6 +1518,8 @@ SortPlan make_sort_plan(int nx, int ny, int nz, int64_t n, const int tile[3], in
     sp.NT[a] = (nn[a] + sp.T[a] - 1) / sp.T[a];
   }
   sp.ntiles = sp.NT[0] * sp.NT[1] * sp.NT[2];
+  sp.kbits = 1;
+  while ((1 << sp.kbits) < sp.ntiles) ++sp.kbits;
   sp.chunk = chunk > 0 ? chunk : 8192;
   // every tile adds at most one partial work item
   const int64_t items = (int64_t)(n / sp.chunk) + sp.ntiles + 1;
@@ -1438,20 +1558,17 @@ hipError_t launch_prologue(const double* X, double* A, uint32_t* idA, const uint
 }
 
 namespace {
-// tile keys, histogram, sort offsets and the deposit work list of the particles in A
-hipError_t launch_keys_chunks(const double* A, const Geom* g, Consts c, const SortPlan& sp,
-                              uint32_t* keys, uint32_t* hist, uint32_t* cursor, int4* chunks,
-                              uint32_t* nchunks, hipStream_t s) {
-  if (c.shape == 1)
-    hipLaunchKernelGGL(k_key_hist<1>, dim3(grid_items(c.n)), dim3(kBlk), 0, s, A, g, c, sp, keys,
-                       hist);
+// tile keys, ranks, sort offsets and the deposit work list of the particles in A
+template <int S>
+hipError_t launch_key_rank(const double* A, const Geom* g, Consts c, const SortPlan& sp,
+                           uint32_t* keys, uint32_t* hist, uint32_t* cursor, int4* chunks,
+                           uint32_t* nchunks, hipStream_t s) {
+  if (per_thread(c.n) == 1)
+    hipLaunchKernelGGL((k_key_rank<S, 1>), dim3(grid_per(c.n, 1)), dim3(kBlk), 0, s, A, g, c, sp,
+                       keys, hist, cursor, chunks, nchunks);
   else
-    hipLaunchKernelGGL(k_key_hist<2>, dim3(grid_items(c.n)), dim3(kBlk), 0, s, A, g, c, sp, keys,
-                       hist);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_build_chunks, dim3(1), dim3(1024), 0, s, g, sp, hist, cursor, chunks,
-                     nchunks);
+    hipLaunchKernelGGL((k_key_rank<S, kPer>), dim3(grid_per(c.n, kPer)), dim3(kBlk), 0, s, A, g,
+                       c, sp, keys, hist, cursor, chunks, nchunks);
   return hipGetLastError();
 }
 }  // namespace
@@ -1460,27 +1577,36 @@ hipError_t launch_bin(const double* A, const uint32_t* idA, const Geom* g, Const
                       const SortPlan& sp, uint32_t* keys, uint32_t* hist, uint32_t* cursor,
                       int4* chunks, uint32_t* nchunks, double* B, uint32_t* idB, bool staged,
                       hipStream_t s) {
-  hipError_t e = launch_keys_chunks(A, g, c, sp, keys, hist, cursor, chunks, nchunks, s);
+  hipError_t e =
+      c.shape == 1 ? launch_key_rank<1>(A, g, c, sp, keys, hist, cursor, chunks, nchunks, s)
+                   : launch_key_rank<2>(A, g, c, sp, keys, hist, cursor, chunks, nchunks, s);
   if (e != hipSuccess) return e;
+  const uint32_t kmask = key_mask(sp);
   if (staged && wide_pays(c.n))
-    hipLaunchKernelGGL(k_scatter_wide, dim3(grid_wide(c.n)), dim3(kWBlk), 0, s, A, idA, keys, g,
-                       c.n, sp.ntiles, cursor, B, idB);
+    hipLaunchKernelGGL(k_scatter_wide, dim3(grid_wide(c.n)), dim3(kWBlk), 0, s, A, idA, keys,
+                       kmask, g, c.n, sp.ntiles, cursor, B, idB);
   else if (staged)
-    hipLaunchKernelGGL(k_scatter<true>, dim3(grid_items(c.n)), dim3(kBlk), 0, s, A, idA, keys, g,
-                       c.n, sp.ntiles, cursor, B, idB);
+    hipLaunchKernelGGL(k_scatter<true>, dim3(grid_items(c.n)), dim3(kBlk), 0, s, A, idA, keys,
+                       kmask, g, c.n, sp.ntiles, cursor, B, idB);
   else
-    hipLaunchKernelGGL(k_scatter<false>, dim3(grid_items(c.n)), dim3(kBlk), 0, s, A, idA, keys, g,
-                       c.n, sp.ntiles, cursor, B, idB);
+    hipLaunchKernelGGL(k_scatter<false>, dim3(grid_items(c.n)), dim3(kBlk), 0, s, A, idA, keys,
+                       kmask, g, c.n, sp.ntiles, cursor, B, idB);
   return hipGetLastError();
 }
 
 hipError_t launch_bin_perm(const double* A, const Geom* g, Consts c, const SortPlan& sp,
                            uint32_t* keys, uint32_t* hist, uint32_t* cursor, int4* chunks,
                            uint32_t* nchunks, uint32_t* perm, hipStream_t s) {
-  hipError_t e = launch_keys_chunks(A, g, c, sp, keys, hist, cursor, chunks, nchunks, s);
+  hipError_t e =
+      c.shape == 1 ? launch_key_rank<1>(A, g, c, sp, keys, hist, cursor, chunks, nchunks, s)
+                   : launch_key_rank<2>(A, g, c, sp, keys, hist, cursor, chunks, nchunks, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_scatter_perm, dim3(grid_items(c.n)), dim3(kBlk), 0, s, keys, g, c.n,
-                     sp.ntiles, cursor, perm);
+  if (per_thread(c.n) < kPer)
+    hipLaunchKernelGGL(k_place<4>, dim3(grid_per(c.n, 4)), dim3(kBlk), 0, s, keys, g, c.n, sp,
+                       cursor, nchunks, perm);
+  else
+    hipLaunchKernelGGL(k_place<kPer>, dim3(grid_per(c.n, kPer)), dim3(kBlk), 0, s, keys, g, c.n,
+                       sp, cursor, nchunks, perm);
   return hipGetLastError();
 }
 
@@ -1617,13 +1743,7 @@ hipError_t launch_unpermute(const double* A, const uint32_t* idA, int64_t n, dou
   }
   int shift, nb;
   bucket_plan(n, kMinShift, &shift, &nb);
-  SortPlan bp;
-  bp.T[0] = bp.T[1] = bp.T[2] = 1;
-  bp.NT[0] = nb;
-  bp.NT[1] = bp.NT[2] = 1;
-  bp.ntiles = nb;
-  bp.chunk = 1 << 30;  // the work list is not used; one entry per bucket
-  bp.max_chunks = nb + 1;
+  const SortPlan bp = bucket_sort_plan(nb);
   hipLaunchKernelGGL(k_id_hist, dim3(grid_items(n)), dim3(kBlk), 0, s, idA, n, shift, nb, keys,
                      hist);
   hipError_t e = hipGetLastError();
@@ -1633,11 +1753,11 @@ hipError_t launch_unpermute(const double* A, const uint32_t* idA, int64_t n, dou
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (wide_pays(n))
-    hipLaunchKernelGGL(k_scatter_wide, dim3(grid_wide(n)), dim3(kWBlk), 0, s, A, idA, keys, g, n,
-                       nb, cursor, B, idB);
+    hipLaunchKernelGGL(k_scatter_wide, dim3(grid_wide(n)), dim3(kWBlk), 0, s, A, idA, keys, ~0u, g,
+                       n, nb, cursor, B, idB);
   else
-    hipLaunchKernelGGL(k_scatter<true>, dim3(grid_items(n)), dim3(kBlk), 0, s, A, idA, keys, g, n,
-                       nb, cursor, B, idB);
+    hipLaunchKernelGGL(k_scatter<true>, dim3(grid_items(n)), dim3(kBlk), 0, s, A, idA, keys, ~0u, g,
+                       n, nb, cursor, B, idB);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t bucket = (int64_t)1 << shift;
@@ -1665,20 +1785,17 @@ hipError_t launch_batch_particles_bin(const BeamDev* beams, int nb, const BatchD
                                       int parity, bool first, hipStream_t s) {
   const dim3 grid(grid_items(bd.max_n), nb);
   if (shape == 1)
-    hipLaunchKernelGGL(k_key_hist_batch<1>, grid, dim3(kBlk), 0, s, beams, parity);
+    hipLaunchKernelGGL(k_key_rank_batch<1>, grid, dim3(kBlk), 0, s, beams, parity);
   else
-    hipLaunchKernelGGL(k_key_hist_batch<2>, grid, dim3(kBlk), 0, s, beams, parity);
+    hipLaunchKernelGGL(k_key_rank_batch<2>, grid, dim3(kBlk), 0, s, beams, parity);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_build_chunks_batch, dim3(nb), dim3(1024), 0, s, beams);
-  e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the first step moves the caller's order into tile order (staged scatter); later steps, whose
   // input is in the previous step's tile order, only rank
   if (first)
     hipLaunchKernelGGL(k_scatter_batch<true>, grid, dim3(kBlk), 0, s, beams, parity);
   else
-    hipLaunchKernelGGL(k_scatter_perm_batch, grid, dim3(kBlk), 0, s, beams);
+    hipLaunchKernelGGL(k_place_batch, grid, dim3(kBlk), 0, s, beams);
   return hipGetLastError();
 }
 
