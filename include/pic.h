@@ -341,7 +341,7 @@ pic_status pic_get_geometry(pic_beam b, double out[9], void* stream);
  * caller's stream; pic_profile_read synchronises those events, writes the summed milliseconds
  * and the number of launches per stage, and stops recording.  Stages:
  *   PIC_STAGE_PROLOGUE  thin quad + half drift of the first step, with the box reduction
- *   PIC_STAGE_GEOMETRY  grid geometry from the box, clearing of the charge grid
+ *   PIC_STAGE_GEOMETRY  grid geometry from the box
  *   PIC_STAGE_GREEN     integrated Green's function and its forward FFT
  *   PIC_STAGE_DEPOSIT   the charge-deposition kernel alone
  *   PIC_STAGE_SOLVE     zero padding, forward FFT, spectral product, inverse FFT, gradient

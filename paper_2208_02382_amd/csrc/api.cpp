@@ -454,7 +454,6 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
                     hipStream_t s, bool binned = false, uint32_t* ids_io = nullptr,
                     bool first_ranked = false) {
   const int ns = (int)sl.size();
-  const int64_t ng = (int64_t)b->d.nx * b->d.ny * b->d.nz;
   double* A = b->XA;
   double* B = b->XB;
   // without labels a binned call carries no ids
@@ -474,7 +473,6 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
     const SliceDev& e = sl[j % ns];
     HIP_OK(b->prof.begin(PIC_STAGE_GEOMETRY, s), "profile");
     HIP_OK(launch_geometry(b->box, b->geom, b->c, s), "geometry");
-    HIP_OK(launch_zero<T>((T*)b->rho, ng, s), "zero rho");
     HIP_OK(b->prof.end(s), "profile");
     pic_status st = fork_green<T>(b, s);
     if (st != PIC_OK) return st;
@@ -695,10 +693,8 @@ pic_status forward_step_recorded(pic_beam b, double* X, const Geom* g, const Adj
                                T* gh, T* E, T* rho, hipStream_t s, Box* box) {
   // the slice's first half map (with the box when a geometry is to be computed), deposit into
   // rho, Green spectrum, solve, kick and the second half map; g is the step's geometry slot
-  const int64_t ng = (int64_t)b->d.nx * b->d.ny * b->d.nz;
   HIP_OK(launch_half_box(X, e.first, b->c, box, s), "adjoint forward");
   if (box) HIP_OK(launch_geometry(box, const_cast<Geom*>(g), b->c, s), "adjoint forward");
-  HIP_OK(launch_zero<T>(rho, ng, s), "adjoint forward");
   // binned deposit from a tile-sorted copy (XB) of the kick-point state
   HIP_OK(launch_bin(X, b->idA, g, b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks, b->nchunks,
                     b->XB, b->idB, true, s),
@@ -888,7 +884,6 @@ pic_status enqueue_batch(const BeamDev* tab, int nb, const BatchDims& bd, int sh
   for (int j = 0; j < n_steps; ++j) {
     const int parity = j & 1;
     HIP_OK(launch_batch_geometry(tab, nb, s), "batch");
-    HIP_OK(launch_batch_zero_rho<T>(tab, nb, bd, s), "batch");
     HIP_OK(launch_batch_particles_bin(tab, nb, bd, shape, parity, j == 0, s), "batch");
     // Green spectra on the auxiliary stream, concurrently with the deposit (beside the binning,
     // whose workgroups then waited for a CU, 256 beams took 169.4 ms per 10 steps, this 168.0)
@@ -1115,7 +1110,6 @@ pic_status pic_deposit(pic_beam b, void* d_rho, void* stream) {
   if (grid_misaligned(b, d_rho)) return fail(PIC_EINVAL, "rho must be aligned to its element");
   MarkDone md{b->done, S(stream)};
   hipStream_t s = S(stream);
-  const int64_t ng = (int64_t)b->d.nx * b->d.ny * b->d.nz;
   HIP_OK(call_setup(b, s), "deposit");
   HIP_OK(launch_box(b->X, b->d.n, b->box, s), "deposit");
   HIP_OK(launch_geometry(b->box, b->geom, b->c, s), "deposit");
@@ -1125,12 +1119,10 @@ pic_status pic_deposit(pic_beam b, void* d_rho, void* stream) {
                          b->nchunks, b->perm, s),
          "deposit");
   if (b->d.grid_fp32) {
-    HIP_OK(launch_zero<float>((float*)d_rho, ng, s), "deposit");
     HIP_OK(launch_deposit_tiles<float>(b->X, b->perm, b->geom, b->c, b->sp, b->chunks,
                                        b->nchunks, (float*)d_rho, s, b->tacc, b->tscale),
            "deposit");
   } else {
-    HIP_OK(launch_zero<double>((double*)d_rho, ng, s), "deposit");
     HIP_OK(launch_deposit_tiles<double>(b->X, b->perm, b->geom, b->c, b->sp, b->chunks,
                                         b->nchunks, (double*)d_rho, s, b->tacc, b->tscale),
            "deposit");

@@ -215,8 +215,8 @@ hipError_t launch_bin_perm(const double* A, const Geom* g, Consts c, const SortP
                            uint32_t* nchunks, uint32_t* perm, hipStream_t s);
 // perm == nullptr: B is in slot order; else slot i reads particle perm[i] of B.  Each tile's
 // window is summed exactly as integers in tacc (ntiles * (T+S)^3 64-bit entries, all zero on
-// entry and left zero; tscale: kMaxTiles exponents) and the grid rho (zeroed by the caller) is
-// formed from them in a fixed order.
+// entry and left zero; tscale: kMaxTiles exponents) and the grid rho (overwritten) is formed
+// from them in a fixed order.
 template <typename T>
 hipError_t launch_deposit_tiles(const double* B, const uint32_t* perm, const Geom* g, Consts c,
                                 const SortPlan& sp, const int4* chunks, const uint32_t* nchunks,
@@ -272,8 +272,6 @@ hipError_t launch_batch_unpermute(const BeamDev* beams, int nb, const BatchDims&
 hipError_t launch_batch_prologue_particles(const BeamDev* beams, int nb, const BatchDims& bd,
                                            hipStream_t s);
 hipError_t launch_batch_geometry(const BeamDev* beams, int nb, hipStream_t s);
-template <typename T>
-hipError_t launch_batch_zero_rho(const BeamDev* beams, int nb, const BatchDims& bd, hipStream_t s);
 hipError_t launch_batch_igf(const BeamDev* beams, int nb, int max_nx, int max_ny, int max_nz,
                             hipStream_t s);
 template <typename T>

@@ -414,16 +414,6 @@ __global__ __launch_bounds__(kBoxSlots) void k_geometry_batch(const BeamDev* __r
   geometry_from_box(d.box, d.geom, d.c);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_zero_rho_batch(const BeamDev* __restrict__ beams) {
-  const BeamDev& d = beams[blockIdx.y];
-  T* p = (T*)d.rho;
-  const int64_t count = (int64_t)d.c.nx * d.c.ny * d.c.nz;
-  for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < count;
-       i += (int64_t)gridDim.x * kBlock)
-    p[i] = T(0);
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------- launch wrappers
@@ -437,15 +427,6 @@ hipError_t launch_batch_geometry(const BeamDev* beams, int nb, hipStream_t s) {
   hipLaunchKernelGGL(k_geometry_batch, dim3(nb), dim3(kBoxSlots), 0, s, beams);
   return hipGetLastError();
 }
-
-template <typename T>
-hipError_t launch_batch_zero_rho(const BeamDev* beams, int nb, const BatchDims& bd, hipStream_t s) {
-  const int64_t ng = (int64_t)bd.max_nx * bd.max_ny * bd.max_nz;
-  hipLaunchKernelGGL((k_zero_rho_batch<T>), dim3(grid_for(ng), nb), dim3(kBlock), 0, s, beams);
-  return hipGetLastError();
-}
-template hipError_t launch_batch_zero_rho<double>(const BeamDev*, int, const BatchDims&, hipStream_t);
-template hipError_t launch_batch_zero_rho<float>(const BeamDev*, int, const BatchDims&, hipStream_t);
 
 hipError_t launch_call_setup(Box* box, unsigned long long* tacc, int64_t count, hipStream_t s) {
   hipLaunchKernelGGL(k_call_setup, dim3(grid_for(count)), dim3(kBlock), 0, s, box, tacc, count);

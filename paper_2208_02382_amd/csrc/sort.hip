@@ -713,17 +713,18 @@ __device__ __forceinline__ void deposit_tiles_body(const double* __restrict__ B,
   if (bin_fault) atomicCAS(const_cast<int*>(&g->status), 0, -7);
 }
 
-// The charge grid from the tiles' integer windows: every node adds, in ascending tile order
+// The charge grid from the tiles' integer windows: every node sums, in ascending tile order
 // (z, then y, then x), the windows of the tiles that cover it, each scaled back by its tile's
-// 2^-k, to what the deposit's direct path put there, and clears the entries it read, so that
-// tacc is zero again for the next step (entries outside the grid are never written).
+// 2^-k, and clears the entries it read, so that tacc is zero again for the next step (entries
+// outside the grid are never written).  Every node is written (zero after a device error), so
+// the grid needs no clearing pass.
 template <int S, typename T>
 __device__ __forceinline__ void tile_reduce_body(const Geom* __restrict__ g, Consts c,
                                                  SortPlan sp,
                                                  unsigned long long* __restrict__ tacc,
                                                  const int* __restrict__ tscale,
                                                  T* __restrict__ rho, int blk, int nblk) {
-  if (g->status) return;
+  const bool err = g->status != 0;
   const int Wx = sp.T[0] + S, Wy = sp.T[1] + S, Wz = sp.T[2] + S;
   const int64_t nw = (int64_t)Wx * Wy * Wz;
   const int64_t total = (int64_t)c.nx * c.ny * c.nz;
@@ -738,6 +739,10 @@ __device__ __forceinline__ void tile_reduce_body(const Geom* __restrict__ g, Con
       while (lo[a] > 0 && (lo[a] - 1) * sp.T[a] + sp.T[a] + S > p[a]) --lo[a];
     }
     double val = 0.0;
+    if (err) {
+      rho[node] = T(0);
+      continue;
+    }
     for (int tz = lo[2]; tz <= hi[2]; ++tz)
       for (int ty = lo[1]; ty <= hi[1]; ++ty)
         for (int tx = lo[0]; tx <= hi[0]; ++tx) {
@@ -751,7 +756,7 @@ __device__ __forceinline__ void tile_reduce_body(const Geom* __restrict__ g, Con
             *e = 0ull;
           }
         }
-    if (val != 0.0) rho[node] = (T)((double)rho[node] + val);
+    rho[node] = (T)val;
   }
 }
 
