@@ -1369,6 +1369,7 @@ pic_status pic_batch_create(pic_beam* beams, int n_beams, const pic_element* con
     bd.max_nx = std::max(bd.max_nx, h->d.nx);
     bd.max_ny = std::max(bd.max_ny, h->d.ny);
     bd.max_nz = std::max(bd.max_nz, h->d.nz);
+    batch_fft_dims(&bd, h->d.nx, h->d.ny, h->d.nz, fp32 != 0);
     bd.dep_lds = std::max(bd.dep_lds, sizeof(unsigned long long) * nodes);
     bd.gkd_lds = std::max(bd.gkd_lds, 3 * win);
     lat_off[b] = all.size();

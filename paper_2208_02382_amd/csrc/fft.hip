@@ -17,83 +17,24 @@
 //   c2r_x   inverse real transform of those rows, writing phi on nodes -1..n_x directly.
 // The field is then E' = -grad phi by centred differences (k_grad).
 //
-// FFT engine: a workgroup holds LB lines of length L in LDS (LB L <= 4096 complex values,
-// at most 64 KB) and runs a Stockham self-sorting decimation-in-time FFT (Govindaraju et al.,
-// SC'08 formulation) in place: each stage reads its butterfly inputs to registers, barriers,
-// writes the outputs.  Lines along y and z are batched along x, so every row load is a run of
-// LB consecutive complex values.  Twiddles come from a per-axis table exp(-2 pi i t/M) computed
-// with sincospi; a half-length transform reads every second entry.
+// FFT engines: fft_reg.hpp holds the lines in registers (the lengths it lists: 16..256 of the
+// usual grids); any other length 2^a 3^b <= 512 runs the engine below, where a workgroup holds
+// LB lines of length L in LDS (LB L <= 4096 complex values, at most 64 KB) and runs a Stockham
+// self-sorting decimation-in-time FFT (Govindaraju et al., SC'08 formulation) in place: each
+// stage reads its butterfly inputs to registers, barriers, writes the outputs.  Lines along y
+// and z are batched along x, so every row load is a run of consecutive complex values.  Twiddles
+// come from a per-axis table exp(-2 pi i t/M) computed with sincospi; a half-length transform
+// reads every second entry.
+#include <algorithm>
+
+#include "fft_reg.hpp"
 #include "internal.hpp"
 
 namespace pic {
 
 namespace {
 
-template <typename T>
-struct Cx {
-  T x, y;
-};
-
-template <typename T>
-struct TwT;
-template <>
-struct TwT<double> {
-  using type = double2;
-};
-template <>
-struct TwT<float> {
-  using type = float2;
-};
-
-// complex load through the native vector type (a struct copy of a conditional load otherwise
-// goes through scratch memory)
-template <typename T>
-__device__ __forceinline__ Cx<T> ld(const Cx<T>* p) {
-  const typename TwT<T>::type t = *reinterpret_cast<const typename TwT<T>::type*>(p);
-  return Cx<T>{t.x, t.y};
-}
-
-template <typename T>
-__device__ __forceinline__ Cx<T> cmul(Cx<T> a, Cx<T> b) {
-  return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
-}
-template <typename T>
-__device__ __forceinline__ Cx<T> cadd(Cx<T> a, Cx<T> b) { return {a.x + b.x, a.y + b.y}; }
-template <typename T>
-__device__ __forceinline__ Cx<T> csub(Cx<T> a, Cx<T> b) { return {a.x - b.x, a.y - b.y}; }
-template <typename T>
-__device__ __forceinline__ Cx<T> cconj(Cx<T> a) { return {a.x, -a.y}; }
-
 constexpr int kLdsElems = 4096;  // complex values per workgroup (64 KB for complex double)
-
-// Radix-R DFT in registers; DIR = -1 forward, +1 inverse (no scaling).  R is a template
-// parameter so that the butterfly values stay in registers (a runtime radix makes the compiler
-// place them in scratch memory).
-template <typename T, int DIR, int R>
-__device__ __forceinline__ void dft(Cx<T>* v) {
-  if constexpr (R == 2) {
-    Cx<T> a = v[0], b = v[1];
-    v[0] = cadd(a, b);
-    v[1] = csub(a, b);
-  } else if constexpr (R == 4) {
-    Cx<T> t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]);
-    Cx<T> t2 = cadd(v[1], v[3]), t3 = csub(v[1], v[3]);
-    Cx<T> jt3 = DIR < 0 ? Cx<T>{t3.y, -t3.x} : Cx<T>{-t3.y, t3.x};  // -i t3 or +i t3
-    v[0] = cadd(t0, t2);
-    v[2] = csub(t0, t2);
-    v[1] = cadd(t1, jt3);
-    v[3] = csub(t1, jt3);
-  } else {  // R == 3
-    const T s3 = (T)(DIR < 0 ? -0.86602540378443864676 : 0.86602540378443864676);
-    Cx<T> a0 = v[0], a1 = v[1], a2 = v[2];
-    Cx<T> sum = cadd(a1, a2), dif = csub(a1, a2);
-    Cx<T> m = {a0.x - (T)0.5 * sum.x, a0.y - (T)0.5 * sum.y};
-    Cx<T> jd = {-s3 * dif.y, s3 * dif.x};  // i s3 (a1 - a2)
-    v[0] = cadd(a0, sum);
-    v[1] = cadd(m, jd);
-    v[2] = csub(m, jd);
-  }
-}
 
 // One Stockham stage of radix R over LB lines of length M (line stride M + 1): butterfly bf
 // (line l, j < M/R, k = j mod Ns) reads buf[l, j + r M/R], applies the twiddles
@@ -639,9 +580,29 @@ __global__ __launch_bounds__(256) void k_grad(const Geom* __restrict__ g, const 
 }
 
 
-// ------------------------------------------------------------------------ batched wrappers
-// beam = blockIdx.z; lines per workgroup as in shape_for, per beam; blocks beyond a beam's
-// extent exit.
+// --------------------------------------------------------------- passes in registers
+// One launch covers one beam (args) or a batch (beam = blockIdx.y).  Lines are numbered through
+// all planes, so only the last workgroup of a beam can hold fewer lines than fit.  What bounds
+// them is the traffic of W (34 MB over the three passes that touch it at 64^3, from the caches)
+// and, on small grids, one workgroup's chain of loads, transform and stores.  Float64, us per
+// launch, runtime-length engine / registers, at 64^3 and 128^3: r2c 13.7 / 6.0 and 36 / 15, y
+// 13.7 / 8.0 and 45 / 35, z 37 / 10.5 and 163 / 45, y inverse 14.1 / 9.4 and 46 / 32, c2r
+// 12.0 / 5.4 and 33 / 19, one axis of the kernel spectrum 13 / 7 and 30 / 22; the z pass of 256
+// batched beams 3118 / 731.
+
+// MODE, IMAG and ODD of the kernels above as run-time values
+struct FftArgs {
+  const Geom* g;
+  int nx, ny, nz;
+  int mode;
+  int odd;          // zconv: axis along which the kernel spectrum is odd (IMAG), else -1
+  const void* src;  // r2c: source rows
+  void* W;
+  void* W2;         // zconv: where the kept rows go
+  const void* gh;
+  void* dst;        // c2r: result rows
+  const void* tw[3];
+};
 
 template <typename T>
 __device__ __forceinline__ const typename TwT<T>::type* tw_of(const FftPlan& p, int a);
@@ -649,6 +610,345 @@ template <>
 __device__ __forceinline__ const double2* tw_of<double>(const FftPlan& p, int a) { return p.tw[a]; }
 template <>
 __device__ __forceinline__ const float2* tw_of<float>(const FftPlan& p, int a) { return p.twf[a]; }
+
+// the arguments of beam blockIdx.y of a batch (a Poisson solve in place), or those given
+template <typename T>
+__device__ __forceinline__ FftArgs beam_args(const FftArgs& args, const BeamDev* beams) {
+  if (!beams) return args;
+  const BeamDev& d = beams[blockIdx.y];
+  FftArgs a;
+  a.g = d.geom;
+  a.nx = d.c.nx;
+  a.ny = d.c.ny;
+  a.nz = d.c.nz;
+  a.mode = 0;
+  a.odd = -1;
+  a.src = d.rho;
+  a.W = d.W;
+  a.W2 = d.W;
+  a.gh = d.Gh;
+  a.dst = d.phi;
+  for (int q = 0; q < 3; ++q) a.tw[q] = tw_of<T>(d.plan, q);
+  return a;
+}
+template <typename T>
+__device__ __forceinline__ const typename TwT<T>::type* tw_arg(const FftArgs& a, int axis) {
+  return reinterpret_cast<const typename TwT<T>::type*>(a.tw[axis]);
+}
+
+__host__ __device__ __forceinline__ int mode_out(int mode, int n) { return mode == 0 ? n + 2 : n; }
+__host__ __device__ __forceinline__ int mode_src(int mode, int n) { return mode == 1 ? n + 2 : n; }
+// output position of cyclic index t on the kept nodes, -1 if it is not kept
+__device__ __forceinline__ int mode_out_pos(int mode, int t, int n, int M) {
+  if (mode != 0) return t < n ? t : -1;
+  return t <= n ? t + 1 : (t == M - 1 ? 0 : -1);
+}
+__device__ __forceinline__ bool mode_src_nonzero(int mode, int p, int n, int M) {
+  return mode != 1 ? p < n : (p <= n || p == M - 1);
+}
+
+// see r2c_x_body; H = n_x
+template <typename T, int H>
+__device__ __forceinline__ void r2c_reg(const FftArgs& a, Cx<T>* buf, int blk) {
+  constexpr int LB = line_count<H>(), TPL = line_threads<H>(), M = 2 * H;
+  const int mode = a.mode;
+  const int ry = mode_src(mode, a.ny), len = mode_src(mode, H);
+  const int rows = ry * mode_src(mode, a.nz);
+  if (blk * LB >= rows) return;
+  int l, j;
+  line_pos<H, false>(&l, &j);
+  const int row = min(blk * LB + l, rows - 1);
+  const bool ok = blk * LB + l < rows;
+  const T* s = (const T*)a.src + (int64_t)row * len;
+  const auto* tw = tw_arg<T>(a, 0);
+  auto elem = [&](int t) {  // element t of the zero-padded row
+    int at = -1;
+    if (mode != 1) {
+      if (t < H) at = t;
+    } else {
+      if (t <= H) at = t + 1;
+      else if (t == M - 1) at = 0;
+    }
+    const T v = s[at >= 0 ? at : 0];
+    return at >= 0 ? v : T(0);
+  };
+  line_fft<T, -1, H, false, 2>(
+      buf, l, j, tw, [&](int p) { return Cx<T>{elem(2 * p), elem(2 * p + 1)}; },
+      [&](auto& v) {
+        __syncthreads();
+        each_output<T, H>(v, j, [&](int p, Cx<T> x) { buf[lds_at<H, false>(l, p)] = x; });
+        __syncthreads();
+      });
+  const int z = row / ry, y = row - z * ry;
+  const int My = 2 * a.ny;
+  const int cz = mode == 1 ? ghost_src(z, 2 * a.nz) : z;
+  const int cy = mode == 1 ? ghost_src(y, My) : y;
+  Cx<T>* out = (Cx<T>*)a.W + ((int64_t)cz * My + cy) * (H + 1);
+#pragma unroll
+  for (int k0 = 0; k0 <= H; k0 += TPL) {
+    const int k = k0 + j;
+    if (k > H || !ok) continue;
+    const Cx<T> zk = buf[lds_at<H, false>(l, k == H ? 0 : k)];
+    const Cx<T> zc = cconj(buf[lds_at<H, false>(l, k == 0 ? 0 : H - k)]);
+    const Cx<T> e = {(T)0.5 * (zk.x + zc.x), (T)0.5 * (zk.y + zc.y)};
+    const Cx<T> dif = csub(zk, zc);
+    const Cx<T> o = {(T)0.5 * dif.y, (T)-0.5 * dif.x};  // dif / (2i)
+    const auto w = tw[k];                              // exp(-2 pi i k / M_x)
+    out[k] = cadd(e, cmul(Cx<T>{(T)w.x, (T)w.y}, o));
+  }
+}
+
+// see c2c_y_body; M = 2 n_y
+template <typename T, int M, int DIR>
+__device__ __forceinline__ void c2c_y_reg(const FftArgs& a, Cx<T>* buf, int blk) {
+  constexpr int LB = line_count<M>();
+  const int Kx = a.nx + 1, mode = a.mode;
+  const int planes = DIR < 0 ? mode_src(mode, a.nz) : mode_out(mode, a.nz);
+  const int lines = Kx * planes;
+  if (blk * LB >= lines) return;
+  int l, j;
+  line_pos<M, true>(&l, &j);
+  const int g = min(blk * LB + l, lines - 1);
+  const bool ok = blk * LB + l < lines;
+  int b = g / Kx;
+  const int x = g - b * Kx;
+  if (DIR < 0 && mode == 1) b = ghost_src(b, 2 * a.nz);
+  Cx<T>* base = (Cx<T>*)(DIR < 0 ? a.W : a.W2) + (int64_t)b * M * Kx + x;
+  line_fft<T, DIR, M, true, 1>(
+      buf, l, j, tw_arg<T>(a, 1),
+      [&](int p) {
+        const bool use = DIR > 0 || mode_src_nonzero(mode, p, M / 2, M);
+        const Cx<T> v = ld(use ? base + (int64_t)p * Kx : base);
+        return use ? v : Cx<T>{0, 0};
+      },
+      [&](auto& v) {
+        each_output<T, M>(v, j, [&](int p, Cx<T> x) {
+          const int q = DIR < 0 ? p : mode_out_pos(mode, p, M / 2, M);
+          if (ok && q >= 0) base[(int64_t)q * Kx] = x;
+        });
+      });
+}
+
+// see zconv_body; M = 2 n_z
+template <typename T, int M, bool IMAG>
+__device__ __forceinline__ void zconv_reg(const FftArgs& a, Cx<T>* buf, int blk) {
+  constexpr int LB = line_count<M>();
+  const int Kx = a.nx + 1, My = 2 * a.ny, mode = a.mode;
+  const int lines = Kx * My;
+  if (blk * LB >= lines) return;
+  int l, j;
+  line_pos<M, true>(&l, &j);
+  const int g = min(blk * LB + l, lines - 1);
+  const bool ok = blk * LB + l < lines;
+  const int ky = g / Kx, kx = g - ky * Kx;
+  const int64_t sz = lines;
+  const Cx<T>* base = (const Cx<T>*)a.W + g;
+  Cx<T>* obase = (Cx<T>*)a.W2 + g;
+  const T* grow = (const T*)a.gh + (int64_t)fold(ky, My) * Kx + kx;
+  const int64_t gplane = (int64_t)(a.ny + 1) * Kx;
+  // signs of the folded spectrum past the Nyquist index: of this line, and along it.  As factors:
+  // a divergent `if (...) s = -s` here lost its negation in the compiled code (the lanes of one
+  // butterfly kept the unflipped sign)
+  const T sign_y = IMAG && a.odd == 1 && ky > a.ny ? T(-1) : T(1);
+  const T sign_z = IMAG && a.odd == 2 ? T(-1) : T(1);
+  const auto* tw = tw_arg<T>(a, 2);
+  using FWD = typename RadicesOf<M>::fwd;
+  using INV = typename ReverseRadices<FWD>::type;
+  line_fft<T, -1, M, true, 1>(
+      buf, l, j, tw,
+      [&](int p) {
+        const bool use = mode_src_nonzero(mode, p, M / 2, M);
+        const Cx<T> v = ld(use ? base + (int64_t)p * sz : base);
+        return use ? v : Cx<T>{0, 0};
+      },
+      [&](auto& v) {
+        constexpr int Q = sizeof(v) / sizeof(v[0]), R = sizeof(v[0]) / sizeof(v[0][0]);
+        constexpr int TPL = line_threads<M>(), NS = M / R;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const int jb = j + q * TPL < NS ? j + q * TPL : 0;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const int p = jb + r * NS;
+            T s = grow[(int64_t)fold(p, M) * gplane];
+            if constexpr (IMAG) s *= sign_y * (p > M / 2 ? sign_z : T(1));
+            const Cx<T> x = v[q][r];
+            v[q][r] = IMAG ? Cx<T>{-x.y * s, x.x * s} : Cx<T>{x.x * s, x.y * s};
+          }
+        }
+        Stages<T, +1, M, true, 1, 1, false, INV>::run(v, buf, l, j, tw, [&](auto& w) {
+          each_output<T, M>(w, j, [&](int p, Cx<T> x) {
+            const int q = mode_out_pos(mode, p, M / 2, M);
+            if (ok && q >= 0) obase[(int64_t)q * sz] = x;
+          });
+        });
+      });
+}
+
+// see c2r_x_body; H = n_x
+template <typename T, int H>
+__device__ __forceinline__ void c2r_reg(const FftArgs& a, Cx<T>* buf, int blk) {
+  constexpr int LB = line_count<H>(), M = 2 * H;
+  const int mode = a.mode;
+  const int py = mode_out(mode, a.ny), px = mode_out(mode, H);
+  const int rows = py * mode_out(mode, a.nz);
+  if (blk * LB >= rows) return;
+  int l, j;
+  line_pos<H, false>(&l, &j);
+  const int row = min(blk * LB + l, rows - 1);
+  const bool ok = blk * LB + l < rows;
+  const int z = row / py, y = row - z * py;
+  const Cx<T>* src = (const Cx<T>*)a.W2 + ((int64_t)z * 2 * a.ny + y) * (H + 1);
+  T* dst = (T*)a.dst + (int64_t)row * px;
+  const auto* tw = tw_arg<T>(a, 0);
+  line_fft<T, +1, H, false, 2>(
+      buf, l, j, tw,
+      [&](int k) {
+        const Cx<T> xk = ld(src + k), xc = cconj(ld(src + (H - k)));
+        const auto w = tw[k];
+        const Cx<T> d = cmul(Cx<T>{(T)w.x, (T)-w.y}, csub(xk, xc));  // exp(+2 pi i k / M_x)
+        return cadd(cadd(xk, xc), Cx<T>{-d.y, d.x});                 // + i d
+      },
+      [&](auto& v) {
+        each_output<T, H>(v, j, [&](int p, Cx<T> x) {
+          const int q0 = mode_out_pos(mode, 2 * p, H, M);
+          const int q1 = mode_out_pos(mode, 2 * p + 1, H, M);
+          if (ok && q0 >= 0) dst[q0] = x.x;
+          if (ok && q1 >= 0) dst[q1] = x.y;
+        });
+      });
+}
+
+template <typename T>
+__global__ __launch_bounds__(kFftThreads) void k_reg_r2c(FftArgs args, const BeamDev* beams) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const FftArgs a = beam_args<T>(args, beams);
+  if (a.g->status) return;
+  with_line_length(a.nx, [&](auto len) {
+    r2c_reg<T, decltype(len)::value>(a, reinterpret_cast<Cx<T>*>(smem_raw), blockIdx.x);
+  });
+}
+template <typename T, int DIR>
+__global__ __launch_bounds__(kFftThreads) void k_reg_y(FftArgs args, const BeamDev* beams) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const FftArgs a = beam_args<T>(args, beams);
+  if (a.g->status) return;
+  with_line_length(2 * a.ny, [&](auto len) {
+    c2c_y_reg<T, decltype(len)::value, DIR>(a, reinterpret_cast<Cx<T>*>(smem_raw), blockIdx.x);
+  });
+}
+template <typename T, bool IMAG>
+__global__ __launch_bounds__(kFftThreads) void k_reg_z(FftArgs args, const BeamDev* beams) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const FftArgs a = beam_args<T>(args, beams);
+  if (a.g->status) return;
+  with_line_length(2 * a.nz, [&](auto len) {
+    zconv_reg<T, decltype(len)::value, IMAG>(a, reinterpret_cast<Cx<T>*>(smem_raw), blockIdx.x);
+  });
+}
+template <typename T>
+__global__ __launch_bounds__(kFftThreads) void k_reg_c2r(FftArgs args, const BeamDev* beams) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const FftArgs a = beam_args<T>(args, beams);
+  if (a.g->status) return;
+  with_line_length(a.nx, [&](auto len) {
+    c2r_reg<T, decltype(len)::value>(a, reinterpret_cast<Cx<T>*>(smem_raw), blockIdx.x);
+  });
+}
+
+// One axis of the kernel spectrum (see green_dft_body): lines of gd along `axis`, two real lines
+// per complex one.  gh != nullptr (the last axis): the result times `scale` goes there in the
+// grid's precision instead of back into gd.
+struct GreenArgs {
+  const Geom* g;
+  double* gd;
+  void* gh;
+  double scale;
+  int nx, ny, nz;
+  int odd;
+  const double2* tw;
+};
+
+__host__ __device__ __forceinline__ double green_scale(int nx, int ny, int nz) {
+  return 1.0 / (4.0 * 3.14159265358979323846 * 8.8541878128e-12 * (8.0 * nx * ny * nz));
+}
+
+template <typename T, int M, int AXIS>
+__device__ __forceinline__ void green_reg(const GreenArgs& a, Cx<double>* buf, int blk) {
+  constexpr int LB = line_count<M>(), n = M / 2;
+  constexpr bool LFAST = AXIS != 0;
+  const int ex = a.nx + 1, ey = a.ny + 1, ez = a.nz + 1;
+  // real lines per plane, planes, element / line / plane strides
+  const int na = AXIS == 0 ? ey : (AXIS == 1 ? ex : ex * ey);
+  const int planes = AXIS == 2 ? 1 : ez;
+  const int64_t st = AXIS == 0 ? 1 : (AXIS == 1 ? ex : (int64_t)ex * ey);
+  const int64_t sa = AXIS == 0 ? ex : 1, sb = (int64_t)ex * ey;
+  const int ncx = (na + 1) / 2, lines = ncx * planes;
+  if (blk * LB >= lines) return;
+  int l, j;
+  line_pos<M, LFAST>(&l, &j);
+  const int g = min(blk * LB + l, lines - 1);
+  const bool ok0 = blk * LB + l < lines;
+  const int b = AXIS == 2 ? 0 : g / ncx;
+  const int c = g - b * ncx;
+  const bool ok1 = ok0 && 2 * c + 1 < na;
+  const int64_t o0 = b * sb + 2 * (int64_t)c * sa, o1 = 2 * c + 1 < na ? o0 + sa : o0;
+  const bool odd = a.odd != 0;
+  line_fft<double, -1, M, LFAST, 1>(
+      buf, l, j, a.tw,
+      [&](int p) {
+        const int t = p <= n ? p : M - p;
+        const double sgn = odd ? (p < n ? 1.0 : (p == n ? 0.0 : -1.0)) : 1.0;
+        return Cx<double>{sgn * a.gd[o0 + t * st], sgn * a.gd[o1 + t * st]};
+      },
+      [&](auto& v) {
+        // in place: the same workgroup has read the line's values by here, all of them before
+        // the first exchange
+        each_output<double, M>(v, j, [&](int p, Cx<double> x) {
+          if (p > n) return;
+          const double r0 = odd ? x.y : x.x, r1 = odd ? -x.x : x.y;
+          if (a.gh) {
+            T* gh = (T*)a.gh;
+            if (ok0) gh[o0 + p * st] = (T)(r0 * a.scale);
+            if (ok1) gh[o1 + p * st] = (T)(r1 * a.scale);
+          } else {
+            if (ok0) a.gd[o0 + p * st] = r0;
+            if (ok1) a.gd[o1 + p * st] = r1;
+          }
+        });
+      });
+}
+
+template <typename T, int AXIS>
+__global__ __launch_bounds__(kFftThreads) void k_reg_green(GreenArgs args, const BeamDev* beams) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  GreenArgs a = args;
+  if (beams) {
+    const BeamDev& d = beams[blockIdx.y];
+    a.g = d.geom;
+    a.gd = d.Gd;
+    a.nx = d.c.nx;
+    a.ny = d.c.ny;
+    a.nz = d.c.nz;
+    a.gh = AXIS == 2 ? d.Gh : nullptr;
+    a.scale = green_scale(a.nx, a.ny, a.nz);
+    a.odd = 0;
+    a.tw = d.plan.tw[AXIS];
+  }
+  if (a.g->status) return;
+  with_line_length(2 * (AXIS == 0 ? a.nx : (AXIS == 1 ? a.ny : a.nz)), [&](auto len) {
+    green_reg<T, decltype(len)::value, AXIS>(a, reinterpret_cast<Cx<double>*>(smem_raw),
+                                             blockIdx.x);
+  });
+}
+
+// ------------------------------------------------------------------------ batched wrappers
+// beam = blockIdx.z; lines per workgroup as in shape_for, per beam; blocks beyond a beam's
+// extent exit.
+
+__device__ __forceinline__ bool reg_length(int M) {
+  return with_line_length(M, [](auto) {});
+}
 
 __device__ __forceinline__ int lines_per_block(int L, int lines) {
   int lb = kLdsElems / (L + 1);
@@ -659,7 +959,7 @@ __device__ __forceinline__ int lines_per_block(int L, int lines) {
 __global__ __launch_bounds__(1024) void k_green_even_dft_batch(const BeamDev* __restrict__ beams,
                                                                int axis) {
   const BeamDev& d = beams[blockIdx.z];
-  if (d.geom->status) return;
+  if (d.geom->status || reg_length(d.plan.full[axis].M)) return;
   const int ex = d.c.nx + 1, ey = d.c.ny + 1, ez = d.c.nz + 1;
   int64_t st, sa, sb;
   int na, nplanes;
@@ -680,15 +980,16 @@ __global__ __launch_bounds__(1024) void k_green_even_dft_batch(const BeamDev* __
 template <typename T>
 __global__ __launch_bounds__(256) void k_green_finish_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.y];
+  if (reg_length(d.plan.full[2].M)) return;
   const int64_t total = (int64_t)(d.c.nx + 1) * (d.c.ny + 1) * (d.c.nz + 1);
-  const double scale = 1.0 / (4.0 * 3.14159265358979323846 * 8.8541878128e-12 *
-                              (8.0 * d.c.nx * d.c.ny * d.c.nz));
+  const double scale = green_scale(d.c.nx, d.c.ny, d.c.nz);
   green_finish_body<T>(d.geom, d.Gd, (T*)d.Gh, total, scale, blockIdx.x, 0, gridDim.x);
 }
 
 template <typename T>
 __global__ __launch_bounds__(1024) void k_r2c_x_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.z];
+  if (reg_length(d.plan.half_x.M)) return;
   const int nx = d.c.nx, ny = d.c.ny, nz = d.c.nz;
   const int LB = lines_per_block(d.plan.half_x.M, ny);
   if ((int)blockIdx.x >= (ny + LB - 1) / LB || (int)blockIdx.y >= nz) return;
@@ -699,6 +1000,7 @@ __global__ __launch_bounds__(1024) void k_r2c_x_batch(const BeamDev* __restrict_
 template <typename T, int DIR, int STAGE>
 __global__ __launch_bounds__(1024) void k_c2c_y_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.z];
+  if (reg_length(d.plan.full[1].M)) return;
   const int Kx = d.c.nx + 1, ny = d.c.ny, nz = d.c.nz;
   const int LB = lines_per_block(d.plan.full[1].M, Kx);
   const int planes = STAGE == 0 ? nz : nz + 2;
@@ -710,6 +1012,7 @@ __global__ __launch_bounds__(1024) void k_c2c_y_batch(const BeamDev* __restrict_
 template <typename T>
 __global__ __launch_bounds__(1024) void k_zconv_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.z];
+  if (reg_length(d.plan.full[2].M)) return;
   const int Kx = d.c.nx + 1, My = 2 * d.c.ny;
   const int LB = lines_per_block(d.plan.full[2].M, Kx);
   if ((int)blockIdx.x >= (Kx + LB - 1) / LB || (int)blockIdx.y >= My) return;
@@ -720,6 +1023,7 @@ __global__ __launch_bounds__(1024) void k_zconv_batch(const BeamDev* __restrict_
 template <typename T>
 __global__ __launch_bounds__(1024) void k_c2r_x_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.z];
+  if (reg_length(d.plan.half_x.M)) return;
   const int nx = d.c.nx, ny = d.c.ny, nz = d.c.nz;
   const int LB = lines_per_block(d.plan.half_x.M, ny + 2);
   if ((int)blockIdx.x >= (ny + 2 + LB - 1) / LB || (int)blockIdx.y >= nz + 2) return;
@@ -777,24 +1081,65 @@ hipError_t launch_twiddles(double2* tw, float2* twf, int M, hipStream_t s) {
 }
 
 namespace {
+// launch shape of the register transforms of a length: lines per workgroup and LDS; false if
+// the length has none
+template <typename T>
+bool reg_shape(int M, bool lfast, int* lb, size_t* lds) {
+  return with_line_length(M, [&](auto len) {
+    constexpr int V = decltype(len)::value;
+    *lb = line_count<V>();
+    *lds = sizeof(Cx<T>) * (size_t)(lfast ? lds_elems<V, true>() : lds_elems<V, false>());
+  });
+}
+
+int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// real lines per plane and planes of one axis of an octant array
+void green_lines(int axis, int nx, int ny, int nz, int* na, int* planes) {
+  const int ex = nx + 1, ey = ny + 1, ez = nz + 1;
+  *na = axis == 0 ? ey : (axis == 1 ? ex : ex * ey);
+  *planes = axis == 2 ? 1 : ez;
+}
+
+template <typename T>
+void launch_reg_green(int axis, dim3 grid, size_t lds, const GreenArgs& a, const BeamDev* beams,
+                      hipStream_t s) {
+  const dim3 nt(kFftThreads);
+  if (axis == 0)
+    hipLaunchKernelGGL((k_reg_green<double, 0>), grid, nt, lds, s, a, beams);
+  else if (axis == 1)
+    hipLaunchKernelGGL((k_reg_green<double, 1>), grid, nt, lds, s, a, beams);
+  else
+    hipLaunchKernelGGL((k_reg_green<T, 2>), grid, nt, lds, s, a, beams);
+}
+
 // The three even/odd DFT passes of one octant kernel gd (odd_axis: -1 for an even kernel) and
 // the scaled conversion into gh.
 template <typename T>
 hipError_t kernel_spectrum(const Geom* g, const FftPlan& p, int nx, int ny, int nz, double* gd,
                            T* gh, int odd_axis, hipStream_t s) {
   const int ex = nx + 1, ey = ny + 1, ez = nz + 1;
-  // (axis, element stride, line stride a, plane stride b, lines a, planes b)
-  const int64_t cfg[3][5] = {{1, ex, (int64_t)ex * ey, ey, ez},
-                             {ex, 1, (int64_t)ex * ey, ex, ez},
-                             {(int64_t)ex * ey, 1, 0, (int64_t)ex * ey, 1}};
+  const double scale = green_scale(nx, ny, nz);
   for (int a = 0; a < 3; ++a) {
-    const int na = (int)cfg[a][3];
+    int na, planes, LB, NT;
+    green_lines(a, nx, ny, nz, &na, &planes);
     const int ncx = (na + 1) / 2;  // complex lines (two real lines each)
-    int LB, NT;
+    size_t lds;
+    if (reg_shape<double>(p.full[a].M, a != 0, &LB, &lds)) {
+      const GreenArgs ga{g,  gd, a == 2 ? (void*)gh : nullptr, scale, nx, ny, nz, a == odd_axis,
+                         p.tw[a]};
+      launch_reg_green<T>(a, dim3(ceil_div(ncx * planes, LB)), lds, ga, nullptr, s);
+      PIC_TRY(hipGetLastError());
+      continue;
+    }
+    // (element stride, line stride a, plane stride b)
+    const int64_t cfg[3][3] = {{1, ex, (int64_t)ex * ey},
+                               {ex, 1, (int64_t)ex * ey},
+                               {(int64_t)ex * ey, 1, 0}};
     shape_for(p.full[a].M, ncx, &LB, &NT);
-    dim3 grid((ncx + LB - 1) / LB, (unsigned)cfg[a][4]);
-    size_t lds = (size_t)LB * (p.full[a].M + 1) * sizeof(Cx<double>) +
-                 (size_t)p.full[a].M * sizeof(double2);
+    const dim3 grid(ceil_div(ncx, LB), planes);
+    lds = (size_t)LB * (p.full[a].M + 1) * sizeof(Cx<double>) +
+          (size_t)p.full[a].M * sizeof(double2);
     if (a == odd_axis)
       hipLaunchKernelGGL(k_green_dft<true>, grid, dim3(NT), lds, s, gd, p.full[a], p.tw[a],
                          cfg[a][0], cfg[a][1], cfg[a][2], na, LB);
@@ -802,13 +1147,14 @@ hipError_t kernel_spectrum(const Geom* g, const FftPlan& p, int nx, int ny, int 
       hipLaunchKernelGGL(k_green_dft<false>, grid, dim3(NT), lds, s, gd, p.full[a], p.tw[a],
                          cfg[a][0], cfg[a][1], cfg[a][2], na, LB);
     PIC_TRY(hipGetLastError());
+    if (a == 2) {
+      const int64_t total = (int64_t)ex * ey * ez;
+      hipLaunchKernelGGL((k_green_finish<T>), dim3(grid_for(total)), dim3(256), 0, s, g, gd, gh,
+                         total, scale);
+      PIC_TRY(hipGetLastError());
+    }
   }
-  const int64_t total = (int64_t)ex * ey * ez;
-  const double scale =
-      1.0 / (4.0 * 3.14159265358979323846 * 8.8541878128e-12 * (8.0 * nx * ny * nz));
-  hipLaunchKernelGGL((k_green_finish<T>), dim3(grid_for(total)), dim3(256), 0, s, g, gd, gh,
-                     total, scale);
-  return hipGetLastError();
+  return hipSuccess;
 }
 }  // namespace
 
@@ -851,46 +1197,146 @@ hipError_t launch_green_spectrum(const Geom* g, const FftPlan& p, int nx, int ny
 
 namespace {
 
-// MODE 0: phi (nodes -1..n) from rho (nodes 0..n-1); MODE 1: chi (nodes 0..n-1) from a source
-// on nodes -1..n.  src/dst layouts as in k_r2c_x and k_c2r_x.
-template <typename T, int MODE>
-hipError_t run_passes(const Geom* g, const FftPlan& p, int nx, int ny, int nz, const T* src,
-                      Cx<T>* W, const T* gh, T* dst, hipStream_t s) {
-  const int My = 2 * ny, Kx = nx + 1;
-  const int rows_y = MODE == 0 ? ny : ny + 2, rows_z = MODE == 0 ? nz : nz + 2;
-  const int out_y = MODE == 0 ? ny + 2 : ny, out_z = MODE == 0 ? nz + 2 : nz;
+// The passes of a solve, each with the register transforms where its line length has them and
+// the runtime-length engine elsewhere (modes as in MODE; 1 and 2 keep the same outputs, 0 and 2
+// read the same inputs).
+template <typename T>
+hipError_t pass_r2c(const FftArgs& a, const FftPlan& p, hipStream_t s) {
+  const int rows_y = mode_src(a.mode, a.ny), rows_z = mode_src(a.mode, a.nz);
   int LB, NT;
   size_t lds;
+  if (reg_shape<T>(a.nx, false, &LB, &lds)) {
+    hipLaunchKernelGGL((k_reg_r2c<T>), dim3(ceil_div(rows_y * rows_z, LB)), dim3(kFftThreads),
+                       lds, s, a, nullptr);
+    return hipGetLastError();
+  }
   shape_for(p.half_x.M, rows_y, &LB, &NT);
   lds = (size_t)LB * (p.half_x.M + 1) * sizeof(Cx<T>) +
         (size_t)p.full[0].M * sizeof(typename TwT<T>::type);
-  hipLaunchKernelGGL((k_r2c_x<T, MODE>), dim3((rows_y + LB - 1) / LB, rows_z), dim3(NT), lds, s,
-                     g, src, W, p.half_x, table<T>(p, 0), nx, ny, nz, Kx, My, LB);
-  PIC_TRY(hipGetLastError());
+  const dim3 grid(ceil_div(rows_y, LB), rows_z);
+  if (a.mode == 1)
+    hipLaunchKernelGGL((k_r2c_x<T, 1>), grid, dim3(NT), lds, s, a.g, (const T*)a.src, (Cx<T>*)a.W,
+                       p.half_x, table<T>(p, 0), a.nx, a.ny, a.nz, a.nx + 1, 2 * a.ny, LB);
+  else
+    hipLaunchKernelGGL((k_r2c_x<T, 0>), grid, dim3(NT), lds, s, a.g, (const T*)a.src, (Cx<T>*)a.W,
+                       p.half_x, table<T>(p, 0), a.nx, a.ny, a.nz, a.nx + 1, 2 * a.ny, LB);
+  return hipGetLastError();
+}
+
+template <typename T, int DIR>
+hipError_t pass_y(const FftArgs& a, const FftPlan& p, hipStream_t s) {
+  const int Kx = a.nx + 1;
+  const int planes = DIR < 0 ? mode_src(a.mode, a.nz) : mode_out(a.mode, a.nz);
+  int LB, NT;
+  size_t lds;
+  if (reg_shape<T>(2 * a.ny, true, &LB, &lds)) {
+    hipLaunchKernelGGL((k_reg_y<T, DIR>), dim3(ceil_div(Kx * planes, LB)), dim3(kFftThreads), lds,
+                       s, a, nullptr);
+    return hipGetLastError();
+  }
   shape_for(p.full[1].M, Kx, &LB, &NT);
   lds = (size_t)LB * (p.full[1].M + 1) * sizeof(Cx<T>) +
         (size_t)p.full[1].M * sizeof(typename TwT<T>::type);
-  hipLaunchKernelGGL((k_c2c_y<T, -1, MODE, 0>), dim3((Kx + LB - 1) / LB, rows_z), dim3(NT), lds,
-                     s, g, W, p.full[1], table<T>(p, 1), Kx, ny, nz, LB);
-  PIC_TRY(hipGetLastError());
+  const dim3 grid(ceil_div(Kx, LB), planes);
+  Cx<T>* W = (Cx<T>*)(DIR < 0 ? a.W : a.W2);
+  constexpr int STAGE = DIR < 0 ? 0 : 1;
+  if ((DIR < 0 && a.mode == 1) || (DIR > 0 && a.mode != 0))
+    hipLaunchKernelGGL((k_c2c_y<T, DIR, 1, STAGE>), grid, dim3(NT), lds, s, a.g, W, p.full[1],
+                       table<T>(p, 1), Kx, a.ny, a.nz, LB);
+  else
+    hipLaunchKernelGGL((k_c2c_y<T, DIR, 0, STAGE>), grid, dim3(NT), lds, s, a.g, W, p.full[1],
+                       table<T>(p, 1), Kx, a.ny, a.nz, LB);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t pass_z(const FftArgs& a, const FftPlan& p, hipStream_t s) {
+  const int Kx = a.nx + 1, My = 2 * a.ny;
+  int LB, NT;
+  size_t lds;
+  if (reg_shape<T>(2 * a.nz, true, &LB, &lds)) {
+    const dim3 grid(ceil_div(Kx * My, LB));
+    if (a.odd >= 0)
+      hipLaunchKernelGGL((k_reg_z<T, true>), grid, dim3(kFftThreads), lds, s, a, nullptr);
+    else
+      hipLaunchKernelGGL((k_reg_z<T, false>), grid, dim3(kFftThreads), lds, s, a, nullptr);
+    return hipGetLastError();
+  }
   shape_for(p.full[2].M, Kx, &LB, &NT);
   lds = (size_t)LB * (p.full[2].M + 1) * sizeof(Cx<T>) +
         (size_t)p.full[2].M * sizeof(typename TwT<T>::type);
-  hipLaunchKernelGGL((k_zconv<T, MODE>), dim3((Kx + LB - 1) / LB, My), dim3(NT), lds, s, g, W,
-                     gh, p.full[2], table<T>(p, 2), Kx, My, ny, nz, LB);
-  PIC_TRY(hipGetLastError());
-  shape_for(p.full[1].M, Kx, &LB, &NT);
-  lds = (size_t)LB * (p.full[1].M + 1) * sizeof(Cx<T>) +
-        (size_t)p.full[1].M * sizeof(typename TwT<T>::type);
-  hipLaunchKernelGGL((k_c2c_y<T, +1, MODE, 1>), dim3((Kx + LB - 1) / LB, out_z), dim3(NT), lds,
-                     s, g, W, p.full[1], table<T>(p, 1), Kx, ny, nz, LB);
-  PIC_TRY(hipGetLastError());
+  const dim3 grid(ceil_div(Kx, LB), My);
+  Cx<T>* W = (Cx<T>*)a.W;
+  const T* gh = (const T*)a.gh;
+  if (a.odd >= 0)
+    hipLaunchKernelGGL((k_zconv_field<T>), grid, dim3(NT), lds, s, a.g, W, gh, p.full[2],
+                       table<T>(p, 2), Kx, My, a.ny, a.nz, LB, (Cx<T>*)a.W2, a.odd);
+  else if (a.mode == 1)
+    hipLaunchKernelGGL((k_zconv<T, 1>), grid, dim3(NT), lds, s, a.g, W, gh, p.full[2],
+                       table<T>(p, 2), Kx, My, a.ny, a.nz, LB);
+  else
+    hipLaunchKernelGGL((k_zconv<T, 0>), grid, dim3(NT), lds, s, a.g, W, gh, p.full[2],
+                       table<T>(p, 2), Kx, My, a.ny, a.nz, LB);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t pass_c2r(const FftArgs& a, const FftPlan& p, hipStream_t s) {
+  const int out_y = mode_out(a.mode, a.ny), out_z = mode_out(a.mode, a.nz);
+  int LB, NT;
+  size_t lds;
+  if (reg_shape<T>(a.nx, false, &LB, &lds)) {
+    hipLaunchKernelGGL((k_reg_c2r<T>), dim3(ceil_div(out_y * out_z, LB)), dim3(kFftThreads), lds,
+                       s, a, nullptr);
+    return hipGetLastError();
+  }
   shape_for(p.half_x.M, out_y, &LB, &NT);
   lds = (size_t)LB * (p.half_x.M + 1) * sizeof(Cx<T>) +
         (size_t)p.full[0].M * sizeof(typename TwT<T>::type);
-  hipLaunchKernelGGL((k_c2r_x<T, MODE>), dim3((out_y + LB - 1) / LB, out_z), dim3(NT), lds, s, g,
-                     W, dst, p.half_x, table<T>(p, 0), nx, ny, Kx, My, LB);
+  const dim3 grid(ceil_div(out_y, LB), out_z);
+  if (a.mode == 0)
+    hipLaunchKernelGGL((k_c2r_x<T, 0>), grid, dim3(NT), lds, s, a.g, (const Cx<T>*)a.W2,
+                       (T*)a.dst, p.half_x, table<T>(p, 0), a.nx, a.ny, a.nx + 1, 2 * a.ny, LB);
+  else
+    hipLaunchKernelGGL((k_c2r_x<T, 1>), grid, dim3(NT), lds, s, a.g, (const Cx<T>*)a.W2,
+                       (T*)a.dst, p.half_x, table<T>(p, 0), a.nx, a.ny, a.nx + 1, 2 * a.ny, LB);
   return hipGetLastError();
+}
+
+template <typename T>
+FftArgs fft_args(const Geom* g, const FftPlan& p, int nx, int ny, int nz, int mode, void* W,
+                 void* W2) {
+  return FftArgs{g, nx, ny, nz, mode, -1, nullptr, W, W2, nullptr, nullptr,
+                 {table<T>(p, 0), table<T>(p, 1), table<T>(p, 2)}};
+}
+
+// mode 0: phi (nodes -1..n) from rho (nodes 0..n-1); mode 1: chi (nodes 0..n-1) from a source
+// on nodes -1..n.  src/dst layouts as in k_r2c_x and k_c2r_x.
+template <typename T>
+hipError_t run_passes(const Geom* g, const FftPlan& p, int nx, int ny, int nz, int mode,
+                      const T* src, void* W, const T* gh, T* dst, hipStream_t s) {
+  FftArgs a = fft_args<T>(g, p, nx, ny, nz, mode, W, W);
+  a.src = src;
+  a.gh = gh;
+  a.dst = dst;
+  PIC_TRY(pass_r2c<T>(a, p, s));
+  PIC_TRY((pass_y<T, -1>(a, p, s)));
+  PIC_TRY(pass_z<T>(a, p, s));
+  PIC_TRY((pass_y<T, +1>(a, p, s)));
+  return pass_c2r<T>(a, p, s);
+}
+
+// one field component's convolution: the z pass of W with i Khat_a (odd along axis a) into W2
+// and the inverse y and x passes into dst (nodes 0..n-1)
+template <typename T>
+hipError_t field_component(FftArgs a, const FftPlan& p, int axis, const T* gh, T* dst,
+                           hipStream_t s) {
+  a.odd = axis;
+  a.gh = gh;
+  a.dst = dst;
+  PIC_TRY(pass_z<T>(a, p, s));
+  PIC_TRY((pass_y<T, +1>(a, p, s)));
+  return pass_c2r<T>(a, p, s);
 }
 
 }  // namespace
@@ -898,7 +1344,7 @@ hipError_t run_passes(const Geom* g, const FftPlan& p, int nx, int ny, int nz, c
 template <typename T>
 hipError_t launch_solve(const Geom* g, const FftPlan& p, int nx, int ny, int nz, const T* rho,
                         void* Wv, const T* gh, T* phi, T* E, hipStream_t s) {
-  PIC_TRY((run_passes<T, 0>(g, p, nx, ny, nz, rho, (Cx<T>*)Wv, gh, phi, s)));
+  PIC_TRY(run_passes<T>(g, p, nx, ny, nz, 0, rho, Wv, gh, phi, s));
   const int64_t ng = (int64_t)nx * ny * nz;
   hipLaunchKernelGGL((k_grad<T>), dim3(grid_for(ng)), dim3(256), 0, s, g, phi, E, nx, ny, nz);
   return hipGetLastError();
@@ -910,44 +1356,13 @@ template <typename T>
 hipError_t launch_solve_field(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
                               const T* rho, void* Wv, void* W2v, const T* gh3, T* E,
                               hipStream_t s) {
-  Cx<T>* W = (Cx<T>*)Wv;
-  Cx<T>* W2 = (Cx<T>*)W2v;
-  const int My = 2 * ny, Kx = nx + 1;
   const int64_t ng = (int64_t)nx * ny * nz, gtot = (int64_t)(nx + 1) * (ny + 1) * (nz + 1);
-  int LB, NT;
-  size_t lds;
-  shape_for(p.half_x.M, ny, &LB, &NT);
-  lds = (size_t)LB * (p.half_x.M + 1) * sizeof(Cx<T>) +
-        (size_t)p.full[0].M * sizeof(typename TwT<T>::type);
-  hipLaunchKernelGGL((k_r2c_x<T, 0>), dim3((ny + LB - 1) / LB, nz), dim3(NT), lds, s, g, rho, W,
-                     p.half_x, table<T>(p, 0), nx, ny, nz, Kx, My, LB);
-  PIC_TRY(hipGetLastError());
-  shape_for(p.full[1].M, Kx, &LB, &NT);
-  lds = (size_t)LB * (p.full[1].M + 1) * sizeof(Cx<T>) +
-        (size_t)p.full[1].M * sizeof(typename TwT<T>::type);
-  hipLaunchKernelGGL((k_c2c_y<T, -1, 0, 0>), dim3((Kx + LB - 1) / LB, nz), dim3(NT), lds, s, g,
-                     W, p.full[1], table<T>(p, 1), Kx, ny, nz, LB);
-  PIC_TRY(hipGetLastError());
-  for (int a = 0; a < 3; ++a) {
-    shape_for(p.full[2].M, Kx, &LB, &NT);
-    lds = (size_t)LB * (p.full[2].M + 1) * sizeof(Cx<T>) +
-          (size_t)p.full[2].M * sizeof(typename TwT<T>::type);
-    hipLaunchKernelGGL((k_zconv_field<T>), dim3((Kx + LB - 1) / LB, My), dim3(NT), lds, s, g, W,
-                       gh3 + a * gtot, p.full[2], table<T>(p, 2), Kx, My, ny, nz, LB, W2, a);
-    PIC_TRY(hipGetLastError());
-    shape_for(p.full[1].M, Kx, &LB, &NT);
-    lds = (size_t)LB * (p.full[1].M + 1) * sizeof(Cx<T>) +
-          (size_t)p.full[1].M * sizeof(typename TwT<T>::type);
-    hipLaunchKernelGGL((k_c2c_y<T, +1, 2, 1>), dim3((Kx + LB - 1) / LB, nz), dim3(NT), lds, s, g,
-                       W2, p.full[1], table<T>(p, 1), Kx, ny, nz, LB);
-    PIC_TRY(hipGetLastError());
-    shape_for(p.half_x.M, ny, &LB, &NT);
-    lds = (size_t)LB * (p.half_x.M + 1) * sizeof(Cx<T>) +
-          (size_t)p.full[0].M * sizeof(typename TwT<T>::type);
-    hipLaunchKernelGGL((k_c2r_x<T, 2>), dim3((ny + LB - 1) / LB, nz), dim3(NT), lds, s, g, W2,
-                       E + a * ng, p.half_x, table<T>(p, 0), nx, ny, Kx, My, LB);
-    PIC_TRY(hipGetLastError());
-  }
+  FftArgs a = fft_args<T>(g, p, nx, ny, nz, 2, Wv, W2v);
+  a.src = rho;
+  PIC_TRY(pass_r2c<T>(a, p, s));
+  PIC_TRY((pass_y<T, -1>(a, p, s)));
+  for (int q = 0; q < 3; ++q)
+    PIC_TRY(field_component<T>(a, p, q, gh3 + q * gtot, E + q * ng, s));
   return hipSuccess;
 }
 
@@ -970,43 +1385,13 @@ template <typename T>
 hipError_t launch_solve_field_T(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
                                 const T* e, void* Wv, void* W2v, const T* gh3, T* tmp, T* chi,
                                 hipStream_t s) {
-  Cx<T>* W = (Cx<T>*)Wv;
-  Cx<T>* W2 = (Cx<T>*)W2v;
-  const int My = 2 * ny, Kx = nx + 1;
   const int64_t ng = (int64_t)nx * ny * nz, gtot = (int64_t)(nx + 1) * (ny + 1) * (nz + 1);
-  for (int a = 0; a < 3; ++a) {
-    int LB, NT;
-    size_t lds;
-    shape_for(p.half_x.M, ny, &LB, &NT);
-    lds = (size_t)LB * (p.half_x.M + 1) * sizeof(Cx<T>) +
-          (size_t)p.full[0].M * sizeof(typename TwT<T>::type);
-    hipLaunchKernelGGL((k_r2c_x<T, 0>), dim3((ny + LB - 1) / LB, nz), dim3(NT), lds, s, g,
-                       e + a * ng, W, p.half_x, table<T>(p, 0), nx, ny, nz, Kx, My, LB);
-    PIC_TRY(hipGetLastError());
-    shape_for(p.full[1].M, Kx, &LB, &NT);
-    lds = (size_t)LB * (p.full[1].M + 1) * sizeof(Cx<T>) +
-          (size_t)p.full[1].M * sizeof(typename TwT<T>::type);
-    hipLaunchKernelGGL((k_c2c_y<T, -1, 0, 0>), dim3((Kx + LB - 1) / LB, nz), dim3(NT), lds, s, g,
-                       W, p.full[1], table<T>(p, 1), Kx, ny, nz, LB);
-    PIC_TRY(hipGetLastError());
-    shape_for(p.full[2].M, Kx, &LB, &NT);
-    lds = (size_t)LB * (p.full[2].M + 1) * sizeof(Cx<T>) +
-          (size_t)p.full[2].M * sizeof(typename TwT<T>::type);
-    hipLaunchKernelGGL((k_zconv_field<T>), dim3((Kx + LB - 1) / LB, My), dim3(NT), lds, s, g, W,
-                       gh3 + a * gtot, p.full[2], table<T>(p, 2), Kx, My, ny, nz, LB, W2, a);
-    PIC_TRY(hipGetLastError());
-    shape_for(p.full[1].M, Kx, &LB, &NT);
-    lds = (size_t)LB * (p.full[1].M + 1) * sizeof(Cx<T>) +
-          (size_t)p.full[1].M * sizeof(typename TwT<T>::type);
-    hipLaunchKernelGGL((k_c2c_y<T, +1, 2, 1>), dim3((Kx + LB - 1) / LB, nz), dim3(NT), lds, s, g,
-                       W2, p.full[1], table<T>(p, 1), Kx, ny, nz, LB);
-    PIC_TRY(hipGetLastError());
-    shape_for(p.half_x.M, ny, &LB, &NT);
-    lds = (size_t)LB * (p.half_x.M + 1) * sizeof(Cx<T>) +
-          (size_t)p.full[0].M * sizeof(typename TwT<T>::type);
-    hipLaunchKernelGGL((k_c2r_x<T, 2>), dim3((ny + LB - 1) / LB, nz), dim3(NT), lds, s, g, W2,
-                       tmp + a * ng, p.half_x, table<T>(p, 0), nx, ny, Kx, My, LB);
-    PIC_TRY(hipGetLastError());
+  FftArgs a = fft_args<T>(g, p, nx, ny, nz, 2, Wv, W2v);
+  for (int q = 0; q < 3; ++q) {
+    a.src = e + q * ng;
+    PIC_TRY(pass_r2c<T>(a, p, s));
+    PIC_TRY((pass_y<T, -1>(a, p, s)));
+    PIC_TRY(field_component<T>(a, p, q, gh3 + q * gtot, tmp + q * ng, s));
   }
   int64_t nbk = (ng + 255) / 256;
   if (nbk > 16384) nbk = 16384;
@@ -1036,7 +1421,7 @@ template hipError_t launch_green_field_spectrum<float>(const Geom*, const FftPla
 template <typename T>
 hipError_t launch_solve_ghost_source(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
                                      const T* psi, void* Wv, const T* gh, T* chi, hipStream_t s) {
-  return run_passes<T, 1>(g, p, nx, ny, nz, psi, (Cx<T>*)Wv, gh, chi, s);
+  return run_passes<T>(g, p, nx, ny, nz, 1, psi, Wv, gh, chi, s);
 }
 
 template hipError_t launch_solve_ghost_source<double>(const Geom*, const FftPlan&, int, int, int,
@@ -1048,31 +1433,74 @@ template hipError_t launch_solve_ghost_source<float>(const Geom*, const FftPlan&
 // ------------------------------------------------------------------------ batched launches
 
 namespace {
-int ceil_div(int a, int b) { return (a + b - 1) / b; }
 int lpb(int L, int lines) {
   int lb = kLdsElems / (L + 1);
   if (lb < 1) lb = 1;
   return lb > lines ? lines : lb;
 }
+// what one beam's lines of length M need of a pass: workgroups and LDS of the register
+// transforms, or the runtime-length engine
+template <typename T>
+void add_pass(BatchPass* bp, int M, bool lfast, int lines) {
+  int lb;
+  size_t lds;
+  if (!reg_shape<T>(M, lfast, &lb, &lds)) {
+    bp->generic = true;
+    return;
+  }
+  bp->blocks = std::max(bp->blocks, ceil_div(lines, lb));
+  bp->lds = std::max(bp->lds, lds);
+}
+template <typename T>
+void add_beam(BatchDims* bd, int nx, int ny, int nz) {
+  const int Kx = nx + 1;
+  add_pass<T>(&bd->r2c, nx, false, ny * nz);
+  add_pass<T>(&bd->yf, 2 * ny, true, Kx * nz);
+  add_pass<T>(&bd->z, 2 * nz, true, Kx * 2 * ny);
+  add_pass<T>(&bd->yi, 2 * ny, true, Kx * (nz + 2));
+  add_pass<T>(&bd->c2r, nx, false, (ny + 2) * (nz + 2));
+  const int M[3] = {2 * nx, 2 * ny, 2 * nz};
+  for (int a = 0; a < 3; ++a) {
+    int na, planes;
+    green_lines(a, nx, ny, nz, &na, &planes);
+    add_pass<double>(&bd->green[a], M[a], a != 0, (na + 1) / 2 * planes);
+  }
+}
 }  // namespace
 
+void batch_fft_dims(BatchDims* bd, int nx, int ny, int nz, bool fp32) {
+  if (fp32)
+    add_beam<float>(bd, nx, ny, nz);
+  else
+    add_beam<double>(bd, nx, ny, nz);
+}
+
+// Every pass: the register transforms for the beams whose line length has them (the others'
+// workgroups exit), and the runtime-length engine if the batch has other beams.
 template <typename T>
 hipError_t launch_batch_green(const BeamDev* beams, int nb, const BatchDims& bd, hipStream_t s) {
   PIC_TRY(launch_batch_igf(beams, nb, bd.max_nx, bd.max_ny, bd.max_nz, s));
   const int ex = bd.max_nx + 1, ey = bd.max_ny + 1, ez = bd.max_nz + 1;
   // grid extents over the beams: the largest grid needs the most blocks along every axis
   const int M[3] = {2 * bd.max_nx, 2 * bd.max_ny, 2 * bd.max_nz};
-  const int na[3] = {ey, ex, ex * ey}, npl[3] = {ez, ez, 1};
   for (int a = 0; a < 3; ++a) {
+    if (bd.green[a].blocks) {
+      launch_reg_green<T>(a, dim3(bd.green[a].blocks, nb), bd.green[a].lds, GreenArgs{}, beams, s);
+      PIC_TRY(hipGetLastError());
+    }
+    if (!bd.green[a].generic) continue;
     // smaller beams have shorter lines and so at least as many lines per block: the largest
     // beam bounds the block count
-    const int ncx = (na[a] + 1) / 2;
+    int na, planes;
+    green_lines(a, bd.max_nx, bd.max_ny, bd.max_nz, &na, &planes);
+    const int ncx = (na + 1) / 2;
     const int gx = ceil_div(ncx, lpb(M[a], ncx));
-    hipLaunchKernelGGL(k_green_even_dft_batch, dim3(gx, npl[a], nb), dim3(1024),
+    hipLaunchKernelGGL(k_green_even_dft_batch, dim3(gx, planes, nb), dim3(1024),
                        (size_t)kLdsElems * sizeof(Cx<double>) + 512 * sizeof(double2), s, beams,
                        a);
     PIC_TRY(hipGetLastError());
   }
+  if (!bd.green[2].generic) return hipSuccess;
   const int64_t total = (int64_t)ex * ey * ez;
   hipLaunchKernelGGL((k_green_finish_batch<T>), dim3(grid_for(total), nb), dim3(256), 0, s, beams);
   return hipGetLastError();
@@ -1084,20 +1512,37 @@ hipError_t launch_batch_solve(const BeamDev* beams, int nb, const BatchDims& bd,
   const int Kx = nx + 1, My = 2 * ny;
   // lines plus a twiddle table of at most 512 entries (2 n <= 512)
   const size_t lds = (size_t)kLdsElems * sizeof(Cx<T>) + 512 * sizeof(typename TwT<T>::type);
-  hipLaunchKernelGGL((k_r2c_x_batch<T>), dim3(ceil_div(ny, lpb(nx, ny)), nz, nb), dim3(1024), lds,
-                     s, beams);
+  const FftArgs none{};
+  const dim3 nt(kFftThreads);
+  if (bd.r2c.blocks)
+    hipLaunchKernelGGL((k_reg_r2c<T>), dim3(bd.r2c.blocks, nb), nt, bd.r2c.lds, s, none, beams);
+  if (bd.r2c.generic)
+    hipLaunchKernelGGL((k_r2c_x_batch<T>), dim3(ceil_div(ny, lpb(nx, ny)), nz, nb), dim3(1024),
+                       lds, s, beams);
   PIC_TRY(hipGetLastError());
-  hipLaunchKernelGGL((k_c2c_y_batch<T, -1, 0>), dim3(ceil_div(Kx, lpb(My, Kx)), nz, nb),
-                     dim3(1024), lds, s, beams);
+  if (bd.yf.blocks)
+    hipLaunchKernelGGL((k_reg_y<T, -1>), dim3(bd.yf.blocks, nb), nt, bd.yf.lds, s, none, beams);
+  if (bd.yf.generic)
+    hipLaunchKernelGGL((k_c2c_y_batch<T, -1, 0>), dim3(ceil_div(Kx, lpb(My, Kx)), nz, nb),
+                       dim3(1024), lds, s, beams);
   PIC_TRY(hipGetLastError());
-  hipLaunchKernelGGL((k_zconv_batch<T>), dim3(ceil_div(Kx, lpb(2 * nz, Kx)), My, nb), dim3(1024),
-                     lds, s, beams);
+  if (bd.z.blocks)
+    hipLaunchKernelGGL((k_reg_z<T, false>), dim3(bd.z.blocks, nb), nt, bd.z.lds, s, none, beams);
+  if (bd.z.generic)
+    hipLaunchKernelGGL((k_zconv_batch<T>), dim3(ceil_div(Kx, lpb(2 * nz, Kx)), My, nb),
+                       dim3(1024), lds, s, beams);
   PIC_TRY(hipGetLastError());
-  hipLaunchKernelGGL((k_c2c_y_batch<T, +1, 1>), dim3(ceil_div(Kx, lpb(My, Kx)), nz + 2, nb),
-                     dim3(1024), lds, s, beams);
+  if (bd.yi.blocks)
+    hipLaunchKernelGGL((k_reg_y<T, +1>), dim3(bd.yi.blocks, nb), nt, bd.yi.lds, s, none, beams);
+  if (bd.yi.generic)
+    hipLaunchKernelGGL((k_c2c_y_batch<T, +1, 1>), dim3(ceil_div(Kx, lpb(My, Kx)), nz + 2, nb),
+                       dim3(1024), lds, s, beams);
   PIC_TRY(hipGetLastError());
-  hipLaunchKernelGGL((k_c2r_x_batch<T>), dim3(ceil_div(ny + 2, lpb(nx, ny + 2)), nz + 2, nb),
-                     dim3(1024), lds, s, beams);
+  if (bd.c2r.blocks)
+    hipLaunchKernelGGL((k_reg_c2r<T>), dim3(bd.c2r.blocks, nb), nt, bd.c2r.lds, s, none, beams);
+  if (bd.c2r.generic)
+    hipLaunchKernelGGL((k_c2r_x_batch<T>), dim3(ceil_div(ny + 2, lpb(nx, ny + 2)), nz + 2, nb),
+                       dim3(1024), lds, s, beams);
   PIC_TRY(hipGetLastError());
   const int64_t ng = (int64_t)nx * ny * nz;
   hipLaunchKernelGGL((k_grad_batch<T>), dim3(grid_for(ng), nb), dim3(256), 0, s, beams);

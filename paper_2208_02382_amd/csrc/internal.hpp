@@ -249,12 +249,22 @@ hipError_t launch_unpermute(const double* A, const uint32_t* idA, int64_t n, dou
                             hipStream_t s);
 
 // ---- batched tracking (one launch per stage for all beams of a batch)
+// one FFT pass over the beams of a batch: workgroups (per beam, the most any needs) and LDS of
+// the register transforms, and whether some beam's line length needs the runtime-length engine
+struct BatchPass {
+  int blocks = 0;
+  size_t lds = 0;
+  bool generic = false;
+};
 struct BatchDims {      // grid extents over the beams of a batch
   int64_t max_n;        // largest particle count
   int max_nx, max_ny, max_nz;
   int max_chunks;       // work-list blocks per beam for the tiled deposit and gather
   size_t dep_lds, gkd_lds;
+  BatchPass r2c, yf, z, yi, c2r, green[3];
 };
+// adds one beam's grid to the passes of a batch
+void batch_fft_dims(BatchDims* bd, int nx, int ny, int nz, bool fp32);
 hipError_t launch_batch_particles_bin(const BeamDev* beams, int nb, const BatchDims& bd, int shape,
                                       int parity, bool first, hipStream_t s);
 // launch_call_setup for every beam
