@@ -321,7 +321,8 @@ __global__ __launch_bounds__(kBlk) void k_adj_div(const Geom* __restrict__ g,
   const double cz = 1.0 / (2.0 * g->h_rest[2]);
   for (int64_t t = blockIdx.x * (int64_t)kBlk + threadIdx.x; t < total;
        t += (int64_t)gridDim.x * kBlk) {
-    const int i = (int)(t % px) - 1, j = (int)((t / px) % py) - 1, k = (int)(t / ((int64_t)px * py)) - 1;
+    const Idx3 q3 = split3(t, px, py);
+    const int i = q3.x - 1, j = q3.y - 1, k = q3.z - 1;
     auto at = [&](int comp, int ii, int jj, int kk) -> double {
       if (ii < 0 || ii >= nx || jj < 0 || jj >= ny || kk < 0 || kk >= nz) return 0.0;
       return (double)e[comp * ng + ((int64_t)kk * ny + jj) * nx + ii];

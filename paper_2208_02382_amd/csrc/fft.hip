@@ -565,7 +565,8 @@ __device__ __forceinline__ void grad_body(const Geom* __restrict__ g, const T* _
   const T cz = (T)(1.0 / (2.0 * g->h_rest[2]));
   const int64_t sy = px, sz = (int64_t)px * py;
   for (int64_t t = bx * 256ll + threadIdx.x; t < total; t += (int64_t)nbx * 256) {
-    int i = (int)(t % nx), j = (int)((t / nx) % ny), k = (int)(t / ((int64_t)nx * ny));
+    const Idx3 q3 = split3(t, nx, ny);
+    const int i = q3.x, j = q3.y, k = q3.z;
     int64_t c = (int64_t)(k + 1) * sz + (int64_t)(j + 1) * sy + (i + 1);
     E[t] = -(phi[c + 1] - phi[c - 1]) * cx;
     E[total + t] = -(phi[c + sy] - phi[c - sy]) * cy;

@@ -24,9 +24,8 @@ __device__ __forceinline__ void igf_corners_body(const Geom* __restrict__ g, int
   const int64_t total = (int64_t)cx * cy * cz;
   const double hx = g->h_rest[0], hy = g->h_rest[1], hz = g->h_rest[2];
   for (int64_t t = blk * 256ll + threadIdx.x; t < total; t += (int64_t)nblk * 256) {
-    int mx = (int)(t % cx);
-    int my = (int)((t / cx) % cy);
-    int mz = (int)(t / ((int64_t)cx * cy));
+    const Idx3 m = split3(t, cx, cy);
+    const int mx = m.x, my = m.y, mz = m.z;
     ddv f = antiderivative(corner_coord(mx, hx), corner_coord(my, hy), corner_coord(mz, hz));
     corners[t] = make_double2(f.hi, f.lo);
   }
@@ -56,9 +55,8 @@ __device__ __forceinline__ void igf_cells_body(const Geom* __restrict__ g, int n
   const double hx = g->h_rest[0], hy = g->h_rest[1], hz = g->h_rest[2];
   const ddv vol = dd_mul_d(two_prod(hx, hy), hz);
   for (int64_t t = blk * 256ll + threadIdx.x; t < total; t += (int64_t)nblk * 256) {
-    const int i = (int)(t % ex);
-    const int j = (int)((t / ex) % ey);
-    const int k = (int)(t / ((int64_t)ex * ey));
+    const Idx3 q3 = split3(t, ex, ey);
+    const int i = q3.x, j = q3.y, k = q3.z;
     ddv dxy[2][2];
     for (int c = 0; c < 2; ++c)
       for (int b = 0; b < 2; ++b) {
@@ -95,9 +93,8 @@ __global__ __launch_bounds__(256) void k_igf_field_corners(const Geom* __restric
   const int64_t total = (int64_t)cx * cy * cz;
   const double hx = g->h_rest[0], hy = g->h_rest[1], hz = g->h_rest[2];
   for (int64_t t = blockIdx.x * 256ll + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-    const int mx = (int)(t % cx);
-    const int my = (int)((t / cx) % cy);
-    const int mz = (int)(t / ((int64_t)cx * cy));
+    const Idx3 m = split3(t, cx, cy);
+    const int mx = m.x, my = m.y, mz = m.z;
     ddv H[3];
     field_antiderivatives(corner_coord(mx, hx), corner_coord(my, hy), corner_coord(mz, hz), H);
     for (int a = 0; a < 3; ++a) hc[a * total + t] = make_double2(H[a].hi, H[a].lo);
@@ -120,9 +117,8 @@ __global__ __launch_bounds__(256) void k_igf_field_cells(const Geom* __restrict_
   const double hx = g->h_rest[0], hy = g->h_rest[1], hz = g->h_rest[2];
   const ddv vol = dd_mul_d(two_prod(hx, hy), hz);
   for (int64_t t = blockIdx.x * 256ll + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-    const int i = (int)(t % ex);
-    const int j = (int)((t / ex) % ey);
-    const int k = (int)(t / ((int64_t)ex * ey));
+    const Idx3 q3 = split3(t, ex, ey);
+    const int i = q3.x, j = q3.y, k = q3.z;
     const int idx[3] = {i, j, k};
     for (int a = 0; a < 3; ++a) {
       double w = idx[a] == 0 ? 0.0 : -1.0;
@@ -160,9 +156,8 @@ __global__ __launch_bounds__(256) void k_igf_dh_corners(const Geom* __restrict__
   const int64_t total = (int64_t)cx * cy * cz;
   const double hx = g->h_rest[0], hy = g->h_rest[1], hz = g->h_rest[2];
   for (int64_t t = blockIdx.x * 256ll + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-    const int mx = (int)(t % cx);
-    const int my = (int)((t / cx) % cy);
-    const int mz = (int)(t / ((int64_t)cx * cy));
+    const Idx3 m = split3(t, cx, cy);
+    const int mx = m.x, my = m.y, mz = m.z;
     ddv v[NF];
     dh_corner_functions<FIELD>(corner_coord(mx, hx), corner_coord(my, hy), corner_coord(mz, hz),
                                v);
@@ -185,9 +180,8 @@ __global__ __launch_bounds__(256) void k_igf_dh_cells(const Geom* __restrict__ g
   const double h[3] = {g->h_rest[0], g->h_rest[1], g->h_rest[2]};
   const ddv vol = dd_mul_d(two_prod(h[0], h[1]), h[2]);
   for (int64_t t = blockIdx.x * 256ll + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-    const int i = (int)(t % ex);
-    const int j = (int)((t / ex) % ey);
-    const int k = (int)(t / ((int64_t)ex * ey));
+    const Idx3 q3 = split3(t, ex, ey);
+    const int i = q3.x, j = q3.y, k = q3.z;
     for (int f = 0; f < NF; ++f) {
       const double2* src = dc + f * ctotal;
       ddv c[8];

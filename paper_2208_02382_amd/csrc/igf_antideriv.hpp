@@ -12,17 +12,19 @@ PIC_HD __forceinline__ ddv corner_coord(int m, double h) {
 
 PIC_HD inline ddv antiderivative(ddv x, ddv y, ddv z) {
   const bool x0 = x.hi == 0.0, y0 = y.hi == 0.0, z0 = z.hi == 0.0;
-  ddv x2 = dd_mul(x, x), y2 = dd_mul(y, y), z2 = dd_mul(z, z);
-  ddv r = dd_sqrt(dd_add(dd_add(x2, y2), z2));
+  ddv x2 = dd_sqr(x), y2 = dd_sqr(y), z2 = dd_sqr(z);
+  ddv r = dd_sqrt(dd_add_s(dd_add_s(x2, y2), z2));
   ddv xy = dd_mul(x, y), yz = dd_mul(y, z), zx = dd_mul(z, x);
   ddv zero = {0.0, 0.0};
-  ddv t1 = (x0 || y0) ? zero : dd_mul(xy, dd_log(dd_add(z, r)));
-  ddv t2 = (y0 || z0) ? zero : dd_mul(yz, dd_log(dd_add(x, r)));
-  ddv t3 = (z0 || x0) ? zero : dd_mul(zx, dd_log(dd_add(y, r)));
-  ddv t4 = x0 ? zero : dd_mul_d(dd_mul(x2, dd_atan2(yz, dd_mul(x, r))), 0.5);
-  ddv t5 = y0 ? zero : dd_mul_d(dd_mul(y2, dd_atan2(zx, dd_mul(y, r))), 0.5);
-  ddv t6 = z0 ? zero : dd_mul_d(dd_mul(z2, dd_atan2(xy, dd_mul(z, r))), 0.5);
-  return dd_sub(dd_add(dd_add(t1, t2), t3), dd_add(dd_add(t4, t5), t6));
+  // r is at least every coordinate
+  ddv t1 = (x0 || y0) ? zero : dd_mul(xy, dd_log(dd_add_f(r, z)));
+  ddv t2 = (y0 || z0) ? zero : dd_mul(yz, dd_log(dd_add_f(r, x)));
+  ddv t3 = (z0 || x0) ? zero : dd_mul(zx, dd_log(dd_add_f(r, y)));
+  ddv t4 = x0 ? zero : dd_mul(x2, dd_atan2(yz, dd_mul(x, r)));
+  ddv t5 = y0 ? zero : dd_mul(y2, dd_atan2(zx, dd_mul(y, r)));
+  ddv t6 = z0 ? zero : dd_mul(z2, dd_atan2(xy, dd_mul(z, r)));
+  const ddv s = dd_add_s(dd_add_s(t4, t5), t6);
+  return dd_add(dd_add(dd_add(t1, t2), t3), ddv{-0.5 * s.hi, -0.5 * s.lo});
 }
 
 // The field's 2-D antiderivatives at a corner (x, y, z >= 0):
@@ -33,12 +35,12 @@ PIC_HD inline ddv antiderivative(ddv x, ddv y, ddv z) {
 // logarithms and arctangents are those of F: three of each per corner.
 PIC_HD inline void field_antiderivatives(ddv x, ddv y, ddv z, ddv H[3]) {
   const bool x0 = x.hi == 0.0, y0 = y.hi == 0.0, z0 = z.hi == 0.0;
-  const ddv r = dd_sqrt(dd_add(dd_add(dd_mul(x, x), dd_mul(y, y)), dd_mul(z, z)));
+  const ddv r = dd_sqrt(dd_add_s(dd_add_s(dd_sqr(x), dd_sqr(y)), dd_sqr(z)));
   const ddv zero = {0.0, 0.0};
   // ln(u + r) is needed where one of the other two coordinates is non-zero, so r > 0 there
-  const ddv Lx = (y0 && z0) ? zero : dd_log(dd_add(x, r));
-  const ddv Ly = (z0 && x0) ? zero : dd_log(dd_add(y, r));
-  const ddv Lz = (x0 && y0) ? zero : dd_log(dd_add(z, r));
+  const ddv Lx = (y0 && z0) ? zero : dd_log(dd_add_f(r, x));
+  const ddv Ly = (z0 && x0) ? zero : dd_log(dd_add_f(r, y));
+  const ddv Lz = (x0 && y0) ? zero : dd_log(dd_add_f(r, z));
   const ddv Ax = x0 ? zero : dd_atan2(dd_mul(y, z), dd_mul(x, r));
   const ddv Ay = y0 ? zero : dd_atan2(dd_mul(z, x), dd_mul(y, r));
   const ddv Az = z0 ? zero : dd_atan2(dd_mul(x, y), dd_mul(z, r));
@@ -64,19 +66,19 @@ PIC_HD inline void field_antiderivatives(ddv x, ddv y, ddv z, ddv H[3]) {
 template <bool FIELD>
 PIC_HD inline void dh_corner_functions(ddv x, ddv y, ddv z, ddv* out) {
   const bool x0 = x.hi == 0.0, y0 = y.hi == 0.0, z0 = z.hi == 0.0;
-  const ddv r = dd_sqrt(dd_add(dd_add(dd_mul(x, x), dd_mul(y, y)), dd_mul(z, z)));
+  const ddv r = dd_sqrt(dd_add_s(dd_add_s(dd_sqr(x), dd_sqr(y)), dd_sqr(z)));
   const ddv zero = {0.0, 0.0};
-  const ddv Lx = (y0 && z0) ? zero : dd_log(dd_add(x, r));
-  const ddv Ly = (z0 && x0) ? zero : dd_log(dd_add(y, r));
-  const ddv Lz = (x0 && y0) ? zero : dd_log(dd_add(z, r));
+  const ddv Lx = (y0 && z0) ? zero : dd_log(dd_add_f(r, x));
+  const ddv Ly = (z0 && x0) ? zero : dd_log(dd_add_f(r, y));
+  const ddv Lz = (x0 && y0) ? zero : dd_log(dd_add_f(r, z));
   const ddv Ax = x0 ? zero : dd_atan2(dd_mul(y, z), dd_mul(x, r));
   const ddv Ay = y0 ? zero : dd_atan2(dd_mul(z, x), dd_mul(y, r));
   const ddv Az = z0 ? zero : dd_atan2(dd_mul(x, y), dd_mul(z, r));
   // coordinate times a logarithm / arctangent, zero with the coordinate
   auto cl = [&](ddv c, bool c0, ddv L) { return c0 ? zero : dd_mul(c, L); };
   if constexpr (!FIELD) {
-    const ddv hx2 = dd_mul_d(dd_mul(x, x), 0.5), hy2 = dd_mul_d(dd_mul(y, y), 0.5),
-              hz2 = dd_mul_d(dd_mul(z, z), 0.5);
+    const ddv hx2 = dd_mul_d(dd_sqr(x), 0.5), hy2 = dd_mul_d(dd_sqr(y), 0.5),
+              hz2 = dd_mul_d(dd_sqr(z), 0.5);
     const ddv tx = x0 ? zero : dd_mul(hx2, Ax);
     const ddv ty = y0 ? zero : dd_mul(hy2, Ay);
     const ddv tz = z0 ? zero : dd_mul(hz2, Az);

@@ -152,6 +152,17 @@ struct BeamDev {
   int* tscale;
 };
 
+// (x, y, z) of index t = (z ny + y) nx + x of a grid array.  Grids have at most 258^3 nodes, so
+// the index fits 32 bits; the 64-bit divisions of an int64_t index took longer than the rest of
+// the one-pass grid kernels.
+struct Idx3 {
+  int x, y, z;
+};
+__device__ __forceinline__ Idx3 split3(int64_t t, int nx, int ny) {
+  const unsigned u = (unsigned)t, q = u / (unsigned)nx, z = q / (unsigned)ny;
+  return {(int)(u - q * nx), (int)(q - z * ny), (int)z};
+}
+
 constexpr int kReduceBlocks = 1024;   // partial sums for the moments reduction
 constexpr int kAdjBlocks = 1024;      // grid of the reverse-sweep particle kernels
 constexpr int kMaxLattice = 1024;     // lattice elements of the reverse sweep

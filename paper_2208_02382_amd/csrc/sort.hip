@@ -729,8 +729,8 @@ __device__ __forceinline__ void tile_reduce_body(const Geom* __restrict__ g, Con
   const int64_t nw = (int64_t)Wx * Wy * Wz;
   const int64_t total = (int64_t)c.nx * c.ny * c.nz;
   for (int64_t node = blk * 256ll + threadIdx.x; node < total; node += (int64_t)nblk * 256) {
-    const int gx = (int)(node % c.nx), gy = (int)((node / c.nx) % c.ny),
-              gz = (int)(node / ((int64_t)c.nx * c.ny));
+    const Idx3 g3 = split3(node, c.nx, c.ny);
+    const int gx = g3.x, gy = g3.y, gz = g3.z;
     const int p[3] = {gx, gy, gz};
     int lo[3], hi[3];
     for (int a = 0; a < 3; ++a) {  // tiles whose window [t T, t T + T + S) holds p[a]
