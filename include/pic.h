@@ -88,7 +88,8 @@ typedef struct {
                               elements above 156 KB makes the gather fall back to global
                               loads; default
                               max(4, ceil(n_a/16)) */
-  int chunk;               /* max particles per work item of a tile, 256..2^20; default 8192 */
+  int chunk;               /* max particles per work item of a tile, 256..2^20; default n/6144
+                              rounded down to a power of two, 512..8192 (2048 in a batch) */
   int blocks;              /* workgroups of the binned deposit and gather, 1..65535; default
                               min(work items, 4096) */
   int threads;             /* threads per workgroup of the binned deposit and gather: a

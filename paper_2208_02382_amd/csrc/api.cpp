@@ -1379,6 +1379,10 @@ pic_status pic_batch_create(pic_beam* beams, int n_beams, const pic_element* con
     BeamDev& d = tab[b];
     d.c = h->c;
     d.sp = h->sp;
+    // the beams of a batch fill the device together: the default work items of one small beam
+    // would only fill and flush more windows (256 beams, 10 steps: 107.1 ms at 512, 105.9 at 2048,
+    // 106.5 at 8192)
+    if (h->d.chunk == 0) d.sp.chunk = std::max(d.sp.chunk, 2048);
     d.plan = h->plan;
     d.X = h->X;
     d.XA = h->XA;

@@ -1512,6 +1512,20 @@ int grid_stride(int64_t n) {
 
 }  // namespace
 
+// Particles per work item where the caller gives none: n / 6144 rounded down to a power of two,
+// 512..8192.  A work item is one workgroup's serial chain of rounds, and the densest tiles of a
+// bunch hold many items, so with 8192 for every size a few workgroups worked through the middle
+// of the beam while the rest of the device was idle; below 512 the window's fill and flush per
+// item outweigh that.  Deposit + gather-kick, us per step with 8192 and as chosen: 65 and 39 at
+// 1e5 TSC (48^3), 112 and 71 at 1e6 CIC and 186 and 88 at 1e6 TSC (64^3), 416 and 221 at 3e6 TSC
+// (96^3), 776 and 671 at 1.25e7 TSC and 2259 and 2220 at 4e7 TSC (128^3).  The results do not
+// depend on it.
+int default_chunk(int64_t n) {
+  int c = 512;
+  while (c < 8192 && 2 * (int64_t)c <= n / 6144) c *= 2;
+  return c;
+}
+
 SortPlan make_sort_plan(int nx, int ny, int nz, int64_t n, const int tile[3], int chunk,
                         int blocks, int threads, int deposit_threads) {
   SortPlan sp;
@@ -1525,7 +1539,7 @@ SortPlan make_sort_plan(int nx, int ny, int nz, int64_t n, const int tile[3], in
   sp.ntiles = sp.NT[0] * sp.NT[1] * sp.NT[2];
   sp.kbits = 1;
   while ((1 << sp.kbits) < sp.ntiles) ++sp.kbits;
-  sp.chunk = chunk > 0 ? chunk : 8192;
+  sp.chunk = chunk > 0 ? chunk : default_chunk(n);
   // every tile adds at most one partial work item
   const int64_t items = (int64_t)(n / sp.chunk) + sp.ntiles + 1;
   sp.max_chunks = items;
