@@ -462,7 +462,8 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
   uint32_t* idB = ids ? b->idB : nullptr;
   HIP_OK(call_setup(b, s), "set-up");
   STAGE(b, PIC_STAGE_PROLOGUE, s,
-        launch_prologue(b->X, A, idA, binned ? ids_io : nullptr, sl[0].first, b->c, b->box, s),
+        launch_prologue(b->X, A, idA, binned ? ids_io : nullptr, sl[0].first, b->c, b->box,
+                        b->geom, s),
         "prologue");
   // the E' window of a tile must fit the LDS a workgroup may use
   const size_t win_bytes = 3 * sizeof(T) * (size_t)(b->sp.T[0] + b->d.shape) *
@@ -471,9 +472,9 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
   const bool first_perm = first_ranked || b->c.n <= kRankFirst;
   for (int j = 0; j < n_steps; ++j) {
     const SliceDev& e = sl[j % ns];
-    HIP_OK(b->prof.begin(PIC_STAGE_GEOMETRY, s), "profile");
-    HIP_OK(launch_geometry(b->box, b->geom, b->c, s), "geometry");
-    HIP_OK(b->prof.end(s), "profile");
+    // the prologue and the tiled gather-kick end with the geometry; the fallback has only the box
+    if (j > 0 && !tiles)
+      STAGE(b, PIC_STAGE_GEOMETRY, s, launch_geometry(b->box, b->geom, b->c, s), "geometry");
     pic_status st = fork_green<T>(b, s);
     if (st != PIC_OK) return st;
     // After the first step A is in the previous step's tile order: only the ranking is
@@ -497,7 +498,9 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
                                   b->chunks, b->nchunks, (T*)b->rho, s, b->tacc, b->tscale),
           "deposit");
     HIP_OK(hipStreamWaitEvent(s, b->ev_join, 0), "join");
-    st = green_and_solve<T>(b, (const T*)b->rho, (T*)b->phi, (T*)b->E, s, false);
+    const bool from_phi = tiles && !b->d.direct_field;
+    st = green_and_solve<T>(b, (const T*)b->rho, (T*)b->phi, from_phi ? nullptr : (T*)b->E, s,
+                            false);
     if (st != PIC_OK) return st;
     const int more = j + 1 < n_steps;
     const int has_next = more && (tiles || !diag);  // fuse the next step's first half map
@@ -512,7 +515,8 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
       STAGE(b, PIC_STAGE_GKD, s,
             launch_gkd_tiles<T>(out, permuted ? A : nullptr, permuted ? b->perm : nullptr,
                                 permuted ? idA : nullptr, permuted ? id_out : nullptr, b->geom,
-                                (const T*)b->E, b->c, b->sp, b->chunks, b->nchunks, e.L,
+                                (const T*)b->E, from_phi ? (const T*)b->phi : nullptr, b->c,
+                                b->sp, b->chunks, b->nchunks, e.L,
                                 e.second, has_next, nx.first, b->box, s, b->diag_part,
                                 b->diag_shift, j > 0 && diag_j ? diag_j - kMomentSlots : nullptr,
                                 diag_j),
@@ -883,7 +887,6 @@ pic_status enqueue_batch(const BeamDev* tab, int nb, const BatchDims& bd, int sh
   HIP_OK(launch_batch_prologue_particles(tab, nb, bd, s), "batch");
   for (int j = 0; j < n_steps; ++j) {
     const int parity = j & 1;
-    HIP_OK(launch_batch_geometry(tab, nb, s), "batch");
     HIP_OK(launch_batch_particles_bin(tab, nb, bd, shape, parity, j == 0, s), "batch");
     // Green spectra on the auxiliary stream, concurrently with the deposit (beside the binning,
     // whose workgroups then waited for a CU, 256 beams took 169.4 ms per 10 steps, this 168.0)

@@ -143,7 +143,9 @@ __device__ __forceinline__ void apply_half_T(const HalfMap& h, double lm[6], dou
   }
 }
 
-// Block-wide min/max of x, y, z, then one atomic per block and axis on the block's slot.
+// Block-wide min/max of x, y, z, then one atomic per block and axis on the block's slot.  WAIT:
+// the first wave, which issues them, goes on only when they have returned.
+template <bool WAIT = false>
 __device__ __forceinline__ void box_accumulate_block(double lo[3], double hi[3], bool bad, Box* box) {
   __shared__ double slo[3][kBoxBlock / 64], shi[3][kBoxBlock / 64];
   __shared__ int sbad;
@@ -171,12 +173,99 @@ __device__ __forceinline__ void box_accumulate_block(double lo[3], double hi[3],
       l = fmin(l, slo[a][q]);
       h = fmax(h, shi[a][q]);
     }
+    unsigned long long was[2] = {0, 0};
     if (l <= h) {
-      atomicMin(&slot->mn[a], ord_enc(l));
-      atomicMax(&slot->mx[a], ord_enc(h));
+      was[0] = atomicMin(&slot->mn[a], ord_enc(l));
+      was[1] = atomicMax(&slot->mx[a], ord_enc(h));
     }
+    if constexpr (WAIT) asm volatile("" : : "v"(was[0]), "v"(was[1]));  // a use of the returns
   }
-  if (threadIdx.x == 0 && sbad) atomicOr(&slot->nonfinite, 1u);
+  if (threadIdx.x == 0 && sbad) {
+    const unsigned was = atomicOr(&slot->nonfinite, 1u);
+    if constexpr (WAIT) asm volatile("" : : "v"(was));
+  }
+}
+
+__device__ __forceinline__ void box_slot_reset(BoxSlot* slot) {
+  for (int a = 0; a < 3; ++a) {
+    slot->mn[a] = ~0ull;
+    slot->mx[a] = 0ull;
+  }
+  slot->nonfinite = 0u;
+  slot->done = 0u;
+}
+
+// Geometry from the box: h = (max - min)/(n - 3.5), node 0 at min - 1.25 h (the extreme
+// particles sit a quarter cell from a node and from a cell boundary: inside every stencil, on
+// no kink of the CIC or TSC weights); the rest-frame cell is (hx, hy, gamma hz).  A non-finite coordinate or a zero extent sets status = -4 (PIC_EDOMAIN),
+// which is sticky until the beam is initialised again.
+// The origin's product and difference are rounded separately (no fused multiply-add), as a
+// plain float64 evaluation of the same formula does.
+// Run by one wave: lane t takes slot t of the box and empties it.
+__device__ __forceinline__ void geometry_from_box(Box* box, Geom* g, const Consts& c) {
+#pragma clang fp contract(off)
+  int nn[3] = {c.nx, c.ny, c.nz};
+  BoxSlot* slot = box->slot + threadIdx.x;
+  unsigned long long mn[3], mx[3];
+  // agent-scope loads: in box_geometry_block other workgroups of the launch wrote the slots
+  for (int a = 0; a < 3; ++a) {
+    mn[a] = __hip_atomic_load(&slot->mn[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    mx[a] = __hip_atomic_load(&slot->mx[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  bool bad = __ballot(__hip_atomic_load(&slot->nonfinite, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT) != 0u) != 0ull;
+  box_slot_reset(slot);
+  for (int off = 32; off > 0; off >>= 1)
+    for (int a = 0; a < 3; ++a) {
+      const unsigned long long l = __shfl_xor(mn[a], off), h = __shfl_xor(mx[a], off);
+      mn[a] = l < mn[a] ? l : mn[a];
+      mx[a] = h > mx[a] ? h : mx[a];
+    }
+  if (threadIdx.x != 0) return;
+  double lo[3], hi[3];
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = ord_dec(mn[a]);
+    hi[a] = ord_dec(mx[a]);
+    if (!(hi[a] > lo[a])) bad = true;
+  }
+  if (bad) {
+    g->status = -4;
+    return;
+  }
+  for (int a = 0; a < 3; ++a) {
+    const double h = (hi[a] - lo[a]) / ((double)nn[a] - 3.5);
+    g->h[a] = h;
+    g->inv_h[a] = 1.0 / h;
+    g->origin[a] = lo[a] - 1.25 * h;
+  }
+  g->h_rest[0] = g->h[0];
+  g->h_rest[1] = g->h[1];
+  g->h_rest[2] = c.gamma * g->h[2];
+}
+
+
+// box_accumulate_block, and the geometry of the finished box by the last of nblk workgroups
+// (numbered by blockIdx.x): a step's geometry then needs no launch of its own (4.5 us and a gap
+// of the 155 us of a step of 1e6 particles on 64^3).  A workgroup counts itself, first in its
+// slot and the slot's last one then in the box (one counter for all would take their atomics one
+// after another), only after its own atomics on the slot have returned; by the time the last one
+// writes *g every workgroup of the launch has read it.  Called by all threads of all workgroups,
+// or, after a device error, by none or some: the counters are reset at the start of every call.
+__device__ __forceinline__ void box_geometry_block(double lo[3], double hi[3], bool bad, Box* box,
+                                                   Geom* g, const Consts& c, int nblk) {
+  __shared__ bool s_last;
+  box_accumulate_block<true>(lo, hi, bad, box);
+  if (threadIdx.x == 0) {
+    const int s = blockIdx.x % kBoxSlots;
+    const unsigned in_slot = (unsigned)(nblk - s + kBoxSlots - 1) / kBoxSlots;
+    const unsigned slots = (unsigned)(nblk < kBoxSlots ? nblk : kBoxSlots);
+    s_last = atomicAdd(&box->slot[s].done, 1u) == in_slot - 1u &&
+             atomicAdd(&box->done, 1u) == slots - 1u;
+  }
+  __syncthreads();
+  if (!s_last || threadIdx.x >= kBoxSlots) return;
+  if (threadIdx.x == 0) box->done = 0u;
+  geometry_from_box(box, g, c);
 }
 
 }  // namespace pic

@@ -27,11 +27,14 @@ struct BoxSlot {
   unsigned long long mn[3];
   unsigned long long mx[3];
   unsigned int nonfinite;
-  unsigned int pad[19];
+  unsigned int done;      // workgroups of the slot that have finished (box_geometry_block)
+  unsigned int pad[18];
 };
 static_assert(sizeof(BoxSlot) == 128, "a slot is one cache line");
 struct Box {
   BoxSlot slot[kBoxSlots];
+  unsigned int done;      // slots whose workgroups have all finished
+  unsigned int pad[31];
 };
 
 // Problem constants passed by value to kernels.
@@ -212,10 +215,10 @@ inline int64_t tile_window_nodes(const SortPlan& sp, int S) {
 // tile[a], chunk, blocks: 0 selects the default
 SortPlan make_sort_plan(int nx, int ny, int nz, int64_t n, const int tile[3], int chunk,
                         int blocks, int threads, int deposit_threads = 0);
-// A = the first half map of X with the box of its positions; idA (if given) = ids_in, or the
-// indices 0..n-1 when ids_in is nullptr
+// A = the first half map of X, and the geometry g of its positions' box; idA (if given) =
+// ids_in, or the indices 0..n-1 when ids_in is nullptr
 hipError_t launch_prologue(const double* X, double* A, uint32_t* idA, const uint32_t* ids_in,
-                           const HalfMap& first, Consts c, Box* box, hipStream_t s);
+                           const HalfMap& first, Consts c, Box* box, Geom* g, hipStream_t s);
 hipError_t launch_bin(const double* A, const uint32_t* idA, const Geom* g, Consts c,
                       const SortPlan& sp, uint32_t* keys, uint32_t* hist, uint32_t* cursor,
                       int4* chunks, uint32_t* nchunks, double* B, uint32_t* idB, bool staged,
@@ -237,10 +240,12 @@ hipError_t launch_deposit_tiles(const double* B, const uint32_t* perm, const Geo
 // (src != B, idsrc != iddst; iddst == nullptr: no ids).  diag_out != nullptr: the moments (kMomentSlots doubles) of the
 // state after the second half map go to diag_out, summed in the same pass into diag_part
 // (sp.blocks * kMomentSlots doubles) about diag_shift (6 doubles, set from diag_prev, the
-// previous step's moments, or from the grid centre when diag_prev is nullptr).
+// previous step's moments, or from the grid centre when diag_prev is nullptr).  phi != nullptr:
+// E' is differenced from it as the windows are filled (E unused).  has_next: g becomes the next
+// step's geometry.
 template <typename T>
 hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,
-                            const uint32_t* idsrc, uint32_t* iddst, const Geom* g, const T* E,
+                            const uint32_t* idsrc, uint32_t* iddst, Geom* g, const T* E, const T* phi,
                             Consts c, const SortPlan& sp, const int4* chunks,
                             const uint32_t* nchunks, double L, const HalfMap& second,
                             int has_next, const HalfMap& first_next, Box* box, hipStream_t s,
@@ -292,7 +297,6 @@ hipError_t launch_batch_unpermute(const BeamDev* beams, int nb, const BatchDims&
                                   hipStream_t s);
 hipError_t launch_batch_prologue_particles(const BeamDev* beams, int nb, const BatchDims& bd,
                                            hipStream_t s);
-hipError_t launch_batch_geometry(const BeamDev* beams, int nb, hipStream_t s);
 hipError_t launch_batch_igf(const BeamDev* beams, int nb, int max_nx, int max_ny, int max_nz,
                             hipStream_t s);
 template <typename T>

@@ -23,17 +23,10 @@ int grid_for(int64_t n) {
 
 // ---------------------------------------------------------------------------- box and geometry
 
-__device__ __forceinline__ void box_slot_reset(BoxSlot* slot) {
-  for (int a = 0; a < 3; ++a) {
-    slot->mn[a] = ~0ull;
-    slot->mx[a] = 0ull;
-  }
-  slot->nonfinite = 0u;
-}
-
 __device__ __forceinline__ void call_setup_body(Box* box, unsigned long long* __restrict__ tacc,
                                                 int64_t count, int blk, int nblk) {
   if (blk == 0 && threadIdx.x < kBoxSlots) box_slot_reset(box->slot + threadIdx.x);
+  if (blk == 0 && threadIdx.x == 0) box->done = 0u;
   for (int64_t i = blk * (int64_t)kBlock + threadIdx.x; i < count; i += (int64_t)nblk * kBlock)
     tacc[i] = 0ull;
 }
@@ -57,52 +50,6 @@ __global__ __launch_bounds__(kBlock) void k_box(const double* __restrict__ X, in
     }
   }
   box_accumulate_block(lo, hi, bad, box);
-}
-
-// Geometry from the box: h = (max - min)/(n - 3.5), node 0 at min - 1.25 h (the extreme
-// particles sit a quarter cell from a node and from a cell boundary: inside every stencil, on
-// no kink of the CIC or TSC weights); the rest-frame cell is (hx, hy, gamma hz).  A non-finite coordinate or a zero extent sets status = -4 (PIC_EDOMAIN),
-// which is sticky until the beam is initialised again.
-// The origin's product and difference are rounded separately (no fused multiply-add), as a
-// plain float64 evaluation of the same formula does.
-// Run by one wave: lane t takes slot t of the box and empties it.
-__device__ void geometry_from_box(Box* box, Geom* g, const Consts& c) {
-#pragma clang fp contract(off)
-  int nn[3] = {c.nx, c.ny, c.nz};
-  BoxSlot* slot = box->slot + threadIdx.x;
-  unsigned long long mn[3], mx[3];
-  for (int a = 0; a < 3; ++a) {
-    mn[a] = slot->mn[a];
-    mx[a] = slot->mx[a];
-  }
-  bool bad = __ballot(slot->nonfinite != 0u) != 0ull;
-  box_slot_reset(slot);
-  for (int off = 32; off > 0; off >>= 1)
-    for (int a = 0; a < 3; ++a) {
-      const unsigned long long l = __shfl_xor(mn[a], off), h = __shfl_xor(mx[a], off);
-      mn[a] = l < mn[a] ? l : mn[a];
-      mx[a] = h > mx[a] ? h : mx[a];
-    }
-  if (threadIdx.x != 0) return;
-  double lo[3], hi[3];
-  for (int a = 0; a < 3; ++a) {
-    lo[a] = ord_dec(mn[a]);
-    hi[a] = ord_dec(mx[a]);
-    if (!(hi[a] > lo[a])) bad = true;
-  }
-  if (bad) {
-    g->status = -4;
-    return;
-  }
-  for (int a = 0; a < 3; ++a) {
-    const double h = (hi[a] - lo[a]) / ((double)nn[a] - 3.5);
-    g->h[a] = h;
-    g->inv_h[a] = 1.0 / h;
-    g->origin[a] = lo[a] - 1.25 * h;
-  }
-  g->h_rest[0] = g->h[0];
-  g->h_rest[1] = g->h[1];
-  g->h_rest[2] = c.gamma * g->h[2];
 }
 
 __global__ __launch_bounds__(kBoxSlots) void k_geometry(Box* box, Geom* g, Consts c) {
@@ -408,23 +355,12 @@ __global__ __launch_bounds__(kBlock) void k_call_setup_batch(const BeamDev* __re
   call_setup_body(d.box, d.tacc, count, blockIdx.x, gridDim.x);
 }
 
-// batched: workgroup b handles beam b
-__global__ __launch_bounds__(kBoxSlots) void k_geometry_batch(const BeamDev* __restrict__ beams) {
-  const BeamDev& d = beams[blockIdx.x];
-  geometry_from_box(d.box, d.geom, d.c);
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------- launch wrappers
 
 hipError_t launch_batch_call_setup(const BeamDev* beams, int nb, hipStream_t s) {
   hipLaunchKernelGGL(k_call_setup_batch, dim3(1024, nb), dim3(kBlock), 0, s, beams);
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_geometry(const BeamDev* beams, int nb, hipStream_t s) {
-  hipLaunchKernelGGL(k_geometry_batch, dim3(nb), dim3(kBoxSlots), 0, s, beams);
   return hipGetLastError();
 }
 

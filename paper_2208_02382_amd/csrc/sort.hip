@@ -891,8 +891,8 @@ __device__ __forceinline__ void gkd_tiles_body(double* __restrict__ B,
                                                     const uint32_t* __restrict__ perm,
                                                     const uint32_t* __restrict__ idsrc,
                                                     uint32_t* __restrict__ iddst,
-                                                    const Geom* __restrict__ g,
-                                                    const T* __restrict__ E, Consts c,
+                                                    Geom* g, const T* __restrict__ E,
+                                                    const T* __restrict__ phi, const Consts& c,
                                                     SortPlan sp,
                                                     const int4* __restrict__ chunks,
                                                     const uint32_t* __restrict__ nchunks,
@@ -926,6 +926,8 @@ __device__ __forceinline__ void gkd_tiles_body(double* __restrict__ B,
   }
   const double o[3] = {g->origin[0], g->origin[1], g->origin[2]};
   const double ih[3] = {g->inv_h[0], g->inv_h[1], g->inv_h[2]};
+  T dif[3];  // 1/(2h) of the centred differences
+  for (int a = 0; a < 3; ++a) dif[a] = (T)(1.0 / (2.0 * g->h_rest[a]));
   const int Wx = sp.T[0] + S, Wy = sp.T[1] + S, Wz = sp.T[2] + S;
   const int nw = Wx * Wy * Wz;
   int rowoff[S + 1][S + 1];  // window offset of stencil row (a, b)
@@ -957,9 +959,23 @@ __device__ __forceinline__ void gkd_tiles_body(double* __restrict__ B,
       int gx = ox + wx_, gy = oy + wy_, gz = oz + wz_;
       bool in = gx < c.nx && gy < c.ny && gz < c.nz;
       int64_t gi = ((int64_t)gz * c.ny + gy) * c.nx + gx;
-      win[w] = in ? E[gi] : T(0);
-      win[nw + w] = in ? E[plane + gi] : T(0);
-      win[2 * nw + w] = in ? E[2 * plane + gi] : T(0);
+      if (phi) {  // the centred differences of grad_body
+        T e0 = 0, e1 = 0, e2 = 0;
+        if (in) {
+          const T* p = phi + ((int64_t)(gz + 1) * (c.ny + 2) + (gy + 1)) * (c.nx + 2) + (gx + 1);
+          const int64_t sy = c.nx + 2, sz = sy * (c.ny + 2);
+          e0 = -(p[1] - p[-1]) * dif[0];
+          e1 = -(p[sy] - p[-sy]) * dif[1];
+          e2 = -(p[sz] - p[-sz]) * dif[2];
+        }
+        win[w] = e0;
+        win[nw + w] = e1;
+        win[2 * nw + w] = e2;
+      } else {
+        win[w] = in ? E[gi] : T(0);
+        win[nw + w] = in ? E[plane + gi] : T(0);
+        win[2 * nw + w] = in ? E[2 * plane + gi] : T(0);
+      }
       wx_ += stx;
       const int cx = wx_ >= Wx;
       wx_ -= cx ? Wx : 0;
@@ -1076,7 +1092,7 @@ __device__ __forceinline__ void gkd_tiles_body(double* __restrict__ B,
     }
   }
   if (bin_fault) atomicCAS(const_cast<int*>(&g->status), 0, -7);
-  if (has_next) box_accumulate_block(lo, hi, bad, box);
+  if (has_next) box_geometry_block(lo, hi, bad, box, g, c, nblk);
   if constexpr (DIAG) {
     // wave sums, then the waves' sums through LDS (the window is free after the barrier; the
     // launch gives at least kMaxThreads / 64 * 27 doubles)
@@ -1107,8 +1123,8 @@ __global__ __launch_bounds__(DIAG ? kDiagThreads : kMaxThreads) void k_gkd_tiles
                                                     const uint32_t* __restrict__ perm,
                                                     const uint32_t* __restrict__ idsrc,
                                                     uint32_t* __restrict__ iddst,
-                                                    const Geom* __restrict__ g,
-                                                    const T* __restrict__ E, Consts c,
+                                                    Geom* g, const T* __restrict__ E,
+                                                    const T* __restrict__ phi, Consts c,
                                                     SortPlan sp,
                                                     const int4* __restrict__ chunks,
                                                     const uint32_t* __restrict__ nchunks,
@@ -1116,8 +1132,8 @@ __global__ __launch_bounds__(DIAG ? kDiagThreads : kMaxThreads) void k_gkd_tiles
                                                     HalfMap first_next, Box* box,
                                                     double* __restrict__ diag_part,
                                                     const double* __restrict__ diag_shift) {
-  gkd_tiles_body<S, T, PERM, DIAG>(B, src, perm, idsrc, iddst, g, E, c, sp, chunks, nchunks, L,
-                                   second, has_next, first_next, box, blockIdx.x, gridDim.x,
+  gkd_tiles_body<S, T, PERM, DIAG>(B, src, perm, idsrc, iddst, g, E, phi, c, sp, chunks, nchunks,
+                                   L, second, has_next, first_next, box, blockIdx.x, gridDim.x,
                                    diag_part, diag_shift);
 }
 
@@ -1181,8 +1197,8 @@ __device__ __forceinline__ void prologue_body(const double* __restrict__ X,
                                                    double* __restrict__ A,
                                                    uint32_t* __restrict__ idA,
                                                    const uint32_t* __restrict__ ids_in,
-                                                   const HalfMap& first, Consts c, Box* box,
-                                                   int blk, int nblk) {
+                                                   const HalfMap& first, const Consts& c,
+                                                   Box* box, Geom* g, int blk, int nblk) {
   const int64_t n = c.n;
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
   bool bad = false;
@@ -1200,15 +1216,16 @@ __device__ __forceinline__ void prologue_body(const double* __restrict__ X,
       hi[a] = fmax(hi[a], p[a]);
     }
   }
-  box_accumulate_block(lo, hi, bad, box);
+  box_geometry_block(lo, hi, bad, box, g, c, nblk);
 }
 
 __global__ __launch_bounds__(kBlk) void k_prologue(const double* __restrict__ X,
                                                    double* __restrict__ A,
                                                    uint32_t* __restrict__ idA,
                                                    const uint32_t* __restrict__ ids_in,
-                                                   HalfMap first, Consts c, Box* box) {
-  prologue_body(X, A, idA, ids_in, first, c, box, blockIdx.x, gridDim.x);
+                                                   HalfMap first, Consts c, Box* box,
+                                                   Geom* g) {
+  prologue_body(X, A, idA, ids_in, first, c, box, g, blockIdx.x, gridDim.x);
 }
 
 // Bucket keys for the return to the caller's order: key = id >> shift (at most 4096 buckets of
@@ -1365,7 +1382,11 @@ __device__ __forceinline__ uint32_t* nxt_id(const BeamDev& d, int parity) { retu
 
 __global__ __launch_bounds__(kBlk) void k_prologue_batch(const BeamDev* __restrict__ beams) {
   const BeamDev& d = beams[blockIdx.y];
-  prologue_body(d.X, d.XA, d.idA, nullptr, d.slices[0].first, d.c, d.box, blockIdx.x, gridDim.x);
+  // workgroups past the beam's own particles only cost their dispatch
+  const int nblk = (int)min((int64_t)gridDim.x, (d.c.n + kBlk - 1) / kBlk);
+  if ((int)blockIdx.x >= nblk) return;
+  prologue_body(d.X, d.XA, d.idA, nullptr, d.slices[0].first, d.c, d.box, d.geom, blockIdx.x,
+                nblk);
 }
 
 template <int S>
@@ -1420,8 +1441,8 @@ __global__ __launch_bounds__(kBlk) void k_gkd_tiles_batch(const BeamDev* __restr
   const SliceDev& sn = d.slices[(j + 1) % d.n_slices];
   gkd_tiles_body<S, T, PERM, false>(nxt_X(d, parity), PERM ? cur_X(d, parity) : nullptr,
                                     PERM ? d.perm : nullptr, PERM ? cur_id(d, parity) : nullptr,
-                                    PERM ? nxt_id(d, parity) : nullptr, d.geom, (const T*)d.E,
-                                    d.c, d.sp, d.chunks, d.nchunks, sl.L, sl.second,
+                                    PERM ? nxt_id(d, parity) : nullptr, d.geom, nullptr,
+                                    (const T*)d.phi, d.c, d.sp, d.chunks, d.nchunks, sl.L, sl.second,
                                     j + 1 < n_steps, sn.first, d.box, blockIdx.x, gridDim.x);
 }
 
@@ -1570,9 +1591,9 @@ hipError_t lds_optin(K kernel, size_t bytes) {
   } while (0)
 
 hipError_t launch_prologue(const double* X, double* A, uint32_t* idA, const uint32_t* ids_in,
-                           const HalfMap& first, Consts c, Box* box, hipStream_t s) {
+                           const HalfMap& first, Consts c, Box* box, Geom* g, hipStream_t s) {
   hipLaunchKernelGGL(k_prologue, dim3(grid_stride(c.n)), dim3(kBlk), 0, s, X, A, idA, ids_in,
-                     first, c, box);
+                     first, c, box, g);
   return hipGetLastError();
 }
 
@@ -1688,8 +1709,8 @@ template hipError_t launch_vdeposit_tiles<float>(const double*, const Geom*, Con
 
 template <typename T>
 hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,
-                            const uint32_t* idsrc, uint32_t* iddst, const Geom* g, const T* E,
-                            Consts c, const SortPlan& sp, const int4* chunks,
+                            const uint32_t* idsrc, uint32_t* iddst, Geom* g, const T* E,
+                            const T* phi, Consts c, const SortPlan& sp, const int4* chunks,
                             const uint32_t* nchunks, double L, const HalfMap& second,
                             int has_next, const HalfMap& first_next, Box* box, hipStream_t s,
                             double* diag_part, double* diag_shift, const double* diag_prev,
@@ -1713,8 +1734,8 @@ hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,
   do {                                                                                        \
     PIC_TRY_LDS((k_gkd_tiles<SS, T, PP, DD>), lds);                                           \
     hipLaunchKernelGGL((k_gkd_tiles<SS, T, PP, DD>), grid, block, lds, s, B, src, perm, idsrc,\
-                       iddst, g, E, c, sp, chunks, nchunks, L, second, has_next, first_next,  \
-                       box, diag_part, diag_shift);                                           \
+                       iddst, g, E, phi, c, sp, chunks, nchunks, L, second, has_next,         \
+                       first_next, box, diag_part, diag_shift);                               \
   } while (0)
   if (diag) {
     if (S == 1) {
@@ -1740,14 +1761,14 @@ hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,
 }
 
 template hipError_t launch_gkd_tiles<double>(double*, const double*, const uint32_t*,
-                                             const uint32_t*, uint32_t*, const Geom*,
+                                             const uint32_t*, uint32_t*, Geom*, const double*,
                                              const double*, Consts, const SortPlan&, const int4*,
                                              const uint32_t*, double, const HalfMap&, int,
                                              const HalfMap&, Box*, hipStream_t, double*, double*,
                                              const double*, double*);
 template hipError_t launch_gkd_tiles<float>(double*, const double*, const uint32_t*,
-                                            const uint32_t*, uint32_t*, const Geom*, const float*,
-                                            Consts, const SortPlan&, const int4*, const uint32_t*,
+                                            const uint32_t*, uint32_t*, Geom*, const float*,
+                                            const float*, Consts, const SortPlan&, const int4*, const uint32_t*,
                                             double, const HalfMap&, int, const HalfMap&, Box*,
                                             hipStream_t, double*, double*, const double*,
                                             double*);
@@ -1796,7 +1817,7 @@ hipError_t launch_unpermute(const double* A, const uint32_t* idA, int64_t n, dou
 
 hipError_t launch_batch_prologue_particles(const BeamDev* beams, int nb, const BatchDims& bd,
                                            hipStream_t s) {
-  hipLaunchKernelGGL(k_prologue_batch, dim3(grid_stride(bd.max_n), nb), dim3(kBlk), 0, s, beams);
+  hipLaunchKernelGGL(k_prologue_batch, dim3(std::min(grid_stride(bd.max_n), 1024), nb), dim3(kBlk), 0, s, beams);
   return hipGetLastError();
 }
 
