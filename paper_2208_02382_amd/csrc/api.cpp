@@ -154,8 +154,8 @@ Layout layout(const pic_beam_desc* d) {
   L.cursor = take(sizeof(uint32_t) * kMaxTiles);
   L.chunks = take(sizeof(int4) * (size_t)sp.max_chunks);
   L.nchunks = take(sizeof(uint32_t) * kNckWords);
-  // slice-step diagnostics summed inside the gather-kick: one partial per workgroup, the shift
-  L.diag_part = take(sizeof(double) * kMomentSlots * (size_t)sp.blocks);
+  // slice-step diagnostics summed inside the gather-kick: the accumulators, the shift
+  L.diag_part = take(sizeof(double) * kMomentSlots * kDiagSlots);
   L.diag_shift = take(sizeof(double) * 6);
   // the deposit's per-tile integer windows (the order-independent charge grid) and exponents
   L.tacc = take(sizeof(uint64_t) * (size_t)sp.ntiles * tile_window_nodes(sp, d->shape));
@@ -222,7 +222,7 @@ struct pic_beam_s {
   Box* box;
   double* mom_partial;
   double* mom_out;
-  double* diag_part;   // per-workgroup moment sums of the fused slice-step diagnostics
+  double* diag_part;   // moment accumulators of the fused slice-step diagnostics
   double* diag_shift;
   unsigned long long* tacc;  // per-tile integer charge windows (zero between deposits)
   int* tscale;

@@ -170,6 +170,7 @@ constexpr int kReduceBlocks = 1024;   // partial sums for the moments reduction
 constexpr int kAdjBlocks = 1024;      // grid of the reverse-sweep particle kernels
 constexpr int kMaxLattice = 1024;     // lattice elements of the reverse sweep
 constexpr int kMomentSlots = 27;      // 6 sums + 21 centred products
+constexpr int kDiagSlots = 64;        // accumulators per sum of the fused diagnostics
 
 // record a failure as the calling thread's pic_last_error() message and return `status`
 // (api.cpp); the HIP form also clears the runtime's sticky error of a rejected call
@@ -239,8 +240,9 @@ hipError_t launch_deposit_tiles(const double* B, const uint32_t* perm, const Geo
 // reads particle perm[i] of src and id idsrc[perm[i]], and writes slot i of B and iddst
 // (src != B, idsrc != iddst; iddst == nullptr: no ids).  diag_out != nullptr: the moments (kMomentSlots doubles) of the
 // state after the second half map go to diag_out, summed in the same pass into diag_part
-// (sp.blocks * kMomentSlots doubles) about diag_shift (6 doubles, set from diag_prev, the
-// previous step's moments, or from the grid centre when diag_prev is nullptr).  phi != nullptr:
+// (kMomentSlots * kDiagSlots doubles) about diag_shift (6 doubles).  diag_prev == nullptr: the
+// first such step, which empties diag_part and shifts by the grid centre; else the shift is the
+// previous step's means, which that step left in diag_shift.  phi != nullptr:
 // E' is differenced from it as the windows are filled (E unused).  has_next: g becomes the next
 // step's geometry.
 template <typename T>

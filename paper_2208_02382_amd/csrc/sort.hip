@@ -881,8 +881,8 @@ __global__ __launch_bounds__(kMaxThreads) void k_deposit_tiles(const double* __r
 // the particles likely to change tile next step lie together in a short stretch of the order:
 // neighbouring tiles then read them through the next permutation from fewer cache lines.
 // DIAG: the particles' state at the end of the step (after the second half map, before the
-// next first half map) is also summed into the block's partial moments, diag_part[blk * 27 +
-// q]: 6 sums of d = v - shift and the 21 products d_a d_b (a <= b, row-major), with the
+// next first half map) is also summed into the moment accumulators diag_part[q kDiagSlots + ...]:
+// 6 sums of d = v - shift and the 21 products d_a d_b (a <= b, row-major), with the
 // 6-double shift read from diag_shift (close to the mean, so that the centred moments formed
 // from these sums lose no digits).
 template <int S, typename T, bool PERM, bool DIAG = false>
@@ -1104,10 +1104,12 @@ __device__ __forceinline__ void gkd_tiles_body(double* __restrict__ B,
     if ((threadIdx.x & 63) == 0)
       for (int q = 0; q < kMomentSlots; ++q) red[wave * kMomentSlots + q] = acc[q];
     __syncthreads();
+    // the blocks' sums go to kDiagSlots accumulators (zero between launches), which k_diag_combine
+    // sums: one partial per block took it 16 us of a 154 us step of 1e5 particles
     if (threadIdx.x < kMomentSlots) {
       double t = 0.0;
       for (int w = 0; w < nwave; ++w) t += red[w * kMomentSlots + threadIdx.x];
-      diag_part[(int64_t)blk * kMomentSlots + threadIdx.x] = t;
+      unsafeAtomicAdd(&diag_part[threadIdx.x * kDiagSlots + blk % kDiagSlots], t);
     }
   }
 }
@@ -1137,16 +1139,16 @@ __global__ __launch_bounds__(DIAG ? kDiagThreads : kMaxThreads) void k_gkd_tiles
                                    diag_part, diag_shift);
 }
 
-// The shift of the fused moment sums: the previous step's means (prev, 6 doubles), or, for the
-// first step (prev == nullptr), the centre of the step's grid for the positions and 0 for the
-// momenta.
-__global__ void k_diag_shift(const Geom* __restrict__ g, Consts c, const double* __restrict__ prev,
-                             double* __restrict__ shift) {
+// The first step's shift of the fused moment sums: the centre of the step's grid for the positions
+// and 0 for the momenta (later steps: the previous step's means, from k_diag_combine).  Also
+// empties the accumulators.
+__global__ __launch_bounds__(256) void k_diag_start(const Geom* __restrict__ g, Consts c,
+                                                    double* __restrict__ part,
+                                                    double* __restrict__ shift) {
+  for (int t = threadIdx.x; t < kMomentSlots * kDiagSlots; t += 256) part[t] = 0.0;
   const int r = threadIdx.x;
   if (r >= 6) return;
-  if (prev) {
-    shift[r] = prev[r];
-  } else if (r & 1) {
+  if (r & 1) {
     shift[r] = 0.0;
   } else {
     const int a = r >> 1;
@@ -1155,18 +1157,18 @@ __global__ void k_diag_shift(const Geom* __restrict__ g, Consts c, const double*
   }
 }
 
-// Moments from the blocks' partial sums: one wave per slot sums the nblk partials; then
-// mean_r = shift_r + S_r / n and the centred products S_ab / n - (S_a / n)(S_b / n).  A device
-// error state (status != 0) writes NaN.
-__global__ __launch_bounds__(1024) void k_diag_combine(const Geom* __restrict__ g,
-                                                       const double* __restrict__ part, int nblk,
-                                                       const double* __restrict__ shift,
-                                                       int64_t n, double* __restrict__ out) {
+// Moments from the accumulators: one wave per sum, one lane per accumulator (left zero); then
+// mean_r = shift_r + S_r / n and the centred products S_ab / n - (S_a / n)(S_b / n), and the
+// next step's shift.  A device error state (status != 0) writes NaN.
+__global__ __launch_bounds__(1024) void k_diag_combine(const Geom* __restrict__ g, double* part,
+                                                       double* __restrict__ shift, int64_t n,
+                                                       double* __restrict__ out) {
   __shared__ double tot[kMomentSlots];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwave = (int)blockDim.x >> 6;
+  static_assert(kDiagSlots == 64, "one accumulator per lane");
   for (int q = wave; q < kMomentSlots; q += nwave) {
-    double t = 0.0;
-    for (int b = lane; b < nblk; b += 64) t += part[(int64_t)b * kMomentSlots + q];
+    double t = part[q * kDiagSlots + lane];
+    part[q * kDiagSlots + lane] = 0.0;
     for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
     if (lane == 0) tot[q] = t;
   }
@@ -1179,7 +1181,9 @@ __global__ __launch_bounds__(1024) void k_diag_combine(const Geom* __restrict__ 
   }
   const double inv = 1.0 / (double)n;
   if (q < 6) {
-    out[q] = shift[q] + tot[q] * inv;
+    const double m = shift[q] + tot[q] * inv;
+    out[q] = m;
+    shift[q] = m;
     return;
   }
   int a = 0, k = q - 6;
@@ -1718,7 +1722,12 @@ hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,
   const int S = c.shape;
   size_t lds = 3 * sizeof(T) * (size_t)(sp.T[0] + S) * (sp.T[1] + S) * (sp.T[2] + S);
   const bool diag = diag_out != nullptr;
-  const dim3 grid((unsigned)sp.blocks),
+  // With diagnostics each workgroup ends with a reduction of its 27 sums, so fewer, longer ones pay
+  // although they balance less well.  Measured, us, at 512 / 768 / 2048 / 4096 workgroups:
+  // 1e5 TSC 48^3 32 / 37 / 58 / 93; 1e6 TSC 64^3 70 / 71 / 89 / 117; 4e6 TSC 96^3 224 / 207 / 233 /
+  // 253; 1.25e7 TSC 128^3 590 / 533 / 580 / 576; 4e7 CIC 128^3 1584 / 1735 / 1781 / 1618.
+  const int diag_blocks = c.n <= (1 << 21) ? 512 : 768;
+  const dim3 grid((unsigned)(diag ? std::min(sp.blocks, diag_blocks) : sp.blocks)),
       block((unsigned)(diag ? std::min(sp.threads, kDiagThreads) : sp.threads));
   // the ids are optional, as a pair
   if (perm && (!src || src == B || (!idsrc != !iddst) || (idsrc && idsrc == iddst)))
@@ -1727,8 +1736,10 @@ hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,
     if (!diag_part || !diag_shift) return hipErrorInvalidValue;
     const size_t red = sizeof(double) * kMomentSlots * (kMaxThreads / 64);
     if (lds < red) lds = red;
-    hipLaunchKernelGGL(k_diag_shift, dim3(1), dim3(64), 0, s, g, c, diag_prev, diag_shift);
-    PIC_TRY(hipGetLastError());
+    if (!diag_prev) {
+      hipLaunchKernelGGL(k_diag_start, dim3(1), dim3(256), 0, s, g, c, diag_part, diag_shift);
+      PIC_TRY(hipGetLastError());
+    }
   }
 #define PIC_GKD(SS, PP, DD)                                                                   \
   do {                                                                                        \
@@ -1753,8 +1764,8 @@ hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,
 #undef PIC_GKD
   PIC_TRY(hipGetLastError());
   if (diag) {
-    hipLaunchKernelGGL(k_diag_combine, dim3(1), dim3(1024), 0, s, g, diag_part, sp.blocks,
-                       diag_shift, c.n, diag_out);
+    hipLaunchKernelGGL(k_diag_combine, dim3(1), dim3(1024), 0, s, g, diag_part, diag_shift, c.n,
+                       diag_out);
     PIC_TRY(hipGetLastError());
   }
   return hipSuccess;
