@@ -556,7 +556,7 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
 
 // ---- reverse sweep workspace (caller-owned, see pic_adjoint_workspace_bytes)
 struct AdjLayout {
-  size_t geoms, ckpt, segX, segE, segG, segQ, e, psi, chi, chi2, stage, dk, dk_part, dL_part,
+  size_t geoms, ckpt, segX, segE, segG, segQ, e, psi, chi, chi2, qhat, stage, dk, dk_part, dL_part,
       small;
   size_t ext_part, geo_part, dot_part, geo, dc, dgd, dgh, total;
   int nseg;
@@ -586,6 +586,7 @@ AdjLayout adj_layout(const pic_beam_desc* d, int n_steps, int ck) {
   A.psi = take(es * (nx + 2) * (ny + 2) * (nz + 2));
   A.chi = take(es * ng);
   A.chi2 = take(es * ng);
+  A.qhat = take(2 * es * (nx + 1) * 2 * ny * nz);  // the charge grid transformed along x and y
   // the geometry's terms: the kernels' h-derivatives (3 for the potential, 9 for the field:
   // corner values, octant cells, spectra), reduction partials and the per-step sums
   const size_t nf = d->direct_field ? 9 : 3;
@@ -817,14 +818,21 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
       } else {
         HIP_OK(launch_adj_a<T>(Xs, lam, geom(j), b->c, el, e, ext_part, geo, s), "adjoint");
       }
+      HIP_OK(launch_green_dh_spectra<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, direct,
+                                        (double2*)(aw + A.dc), (double*)(aw + A.dgd), dgh, s),
+             "adjoint geometry");
+      const T* Qj = segQ + ng * (size_t)q;
+      int ndots = 0;
       if (direct) {  // transposed field convolutions, b->E as their scratch
         HIP_OK(launch_solve_field_T<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, e, b->W, b->W2,
                                        segG + G3 * (size_t)q, (T*)b->E, chi, s),
                "adjoint");
       } else {
         HIP_OK(launch_adj_div<T>(geom(j), e, psi, b->d.nx, b->d.ny, b->d.nz, s), "adjoint");
-        HIP_OK(launch_solve_ghost_source<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, psi,
-                                            b->W, segG + G3 * (size_t)q, chi, s),
+        // the geometry sums through the Green's function come with it (below)
+        HIP_OK(launch_solve_ghost_dots<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, psi, b->W,
+                                          segG + G3 * (size_t)q, chi, Qj, aw + A.qhat, dgh,
+                                          dot_part, kAdjBlocks, &ndots, s),
                "adjoint");
       }
       HIP_OK(launch_adj_b<T>(Xs, lam, geom(j), b->c, el, segE + 3 * ng * (size_t)q, chi,
@@ -833,11 +841,9 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
       // the geometry's terms: dJ/dh' through the kernel (the h-derivative kernels' convolution
       // with the adjoint source, dotted with the step's charge) into geo[12..14], and through
       // the centred difference sum_n e_b E'_b into geo[15..17] (zero for the direct field)
-      const T* Qj = segQ + ng * (size_t)q;
-      HIP_OK(launch_green_dh_spectra<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, direct,
-                                        (double2*)(aw + A.dc), (double*)(aw + A.dgd), dgh, s),
-             "adjoint geometry");
-      for (int hb = 0; hb < 3; ++hb) {
+      if (ndots)
+        HIP_OK(launch_combine_cols(dot_part, ndots, 3, 1, 3, geo + 12, s), "adjoint geometry");
+      for (int hb = 0; hb < 3 && !ndots; ++hb) {
         if (direct)
           HIP_OK(launch_solve_field_T<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, e, b->W,
                                          b->W2, dgh + 3 * G1 * (size_t)hb, (T*)b->E, chi2, s),

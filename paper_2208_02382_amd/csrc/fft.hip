@@ -786,6 +786,66 @@ __device__ __forceinline__ void zconv_reg(const FftArgs& a, Cx<T>* buf, int blk)
       });
 }
 
+// Sums of three convolutions of one source against one grid, without forming them: with psi and Q
+// already transformed along x and y (a.W, a source on nodes -1..n; a.W2, one on nodes 0..n-1), the
+// z transforms of a line of each and acc[b] += sum over the line's k_z of
+// ghat_b Re(psihat conj(Qhat)), times 2 for the lines that stand for k_x and -k_x too (Parseval).
+// gh: three spectra, the stride apart, scaled as for zconv; all even.
+template <typename T, int M>
+__device__ __forceinline__ void zdot_reg(const FftArgs& a, int64_t gstride, Cx<T>* buf, int blk,
+                                         double (&acc)[3]) {
+  constexpr int LB = line_count<M>();
+  const int Kx = a.nx + 1, My = 2 * a.ny;
+  const int lines = Kx * My;
+  if (blk * LB >= lines) return;
+  int l, j;
+  line_pos<M, true>(&l, &j);
+  const int g = min(blk * LB + l, lines - 1);
+  const int ky = g / Kx, kx = g - ky * Kx;
+  const double weight = blk * LB + l < lines ? (kx == 0 || kx == a.nx ? 1.0 : 2.0) : 0.0;
+  const int64_t sz = lines;
+  const Cx<T>* psi = (const Cx<T>*)a.W + g;
+  const Cx<T>* q0 = (const Cx<T>*)a.W2 + g;
+  const T* grow = (const T*)a.gh + (int64_t)fold(ky, My) * Kx + kx;
+  const int64_t gplane = (int64_t)(a.ny + 1) * Kx;
+  const auto* tw = tw_arg<T>(a, 2);
+  line_fft<T, -1, M, true, 1>(
+      buf, l, j, tw,
+      [&](int p) {
+        const bool use = mode_src_nonzero(1, p, M / 2, M);
+        const Cx<T> v = ld(use ? psi + (int64_t)p * sz : psi);
+        return use ? v : Cx<T>{0, 0};
+      },
+      [&](auto& vp) {
+        __syncthreads();  // the second transform's first exchange writes what the first's last read
+        line_fft<T, -1, M, true, 1>(
+            buf, l, j, tw,
+            [&](int p) {
+              const bool use = p < M / 2;
+              const Cx<T> v = ld(use ? q0 + (int64_t)p * sz : q0);
+              return use ? v : Cx<T>{0, 0};
+            },
+            [&](auto& vq) {
+              constexpr int Q = sizeof(vp) / sizeof(vp[0]);
+              constexpr int R = sizeof(vp[0]) / sizeof(vp[0][0]);
+              constexpr int TPL = line_threads<M>(), NS = M / R;
+#pragma unroll
+              for (int q = 0; q < Q; ++q) {
+                const int jb = j + q * TPL;
+                if (jb >= NS) continue;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                  const Cx<T> x = vp[q][r], y = vq[q][r];
+                  const double d = weight * ((double)x.x * y.x + (double)x.y * y.y);
+                  const T* s = grow + (int64_t)fold(jb + r * NS, M) * gplane;
+                  for (int b = 0; b < 3; ++b) acc[b] += (double)s[b * gstride] * d;
+                }
+              }
+            });
+      });
+  __syncthreads();
+}
+
 // see c2r_x_body; H = n_x
 template <typename T, int H>
 __device__ __forceinline__ void c2r_reg(const FftArgs& a, Cx<T>* buf, int blk) {
@@ -847,6 +907,31 @@ __global__ __launch_bounds__(kFftThreads) void k_reg_z(FftArgs args, const BeamD
     zconv_reg<T, decltype(len)::value, IMAG>(a, reinterpret_cast<Cx<T>*>(smem_raw), blockIdx.x);
   });
 }
+// partial[blk 3 + b] = the block's share of the three sums of zdot_reg
+template <typename T>
+__global__ __launch_bounds__(kFftThreads) void k_reg_zdot(FftArgs a, int64_t gstride,
+                                                          double* __restrict__ partial) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double sh[kFftThreads / 64][3];
+  double acc[3] = {0.0, 0.0, 0.0};
+  if (a.g->status == 0)
+    with_line_length(2 * a.nz, [&](auto len) {
+      constexpr int M = decltype(len)::value;
+      const int blocks = ((a.nx + 1) * 2 * a.ny + line_count<M>() - 1) / line_count<M>();
+      for (int blk = blockIdx.x; blk < blocks; blk += gridDim.x)
+        zdot_reg<T, M>(a, gstride, reinterpret_cast<Cx<T>*>(smem_raw), blk, acc);
+    });
+  for (int b = 0; b < 3; ++b) {
+    for (int off = 32; off > 0; off >>= 1) acc[b] += __shfl_xor(acc[b], off);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][b] = acc[b];
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    double t = 0.0;
+    for (int w = 0; w < kFftThreads / 64; ++w) t += sh[w][threadIdx.x];
+    partial[blockIdx.x * 3 + threadIdx.x] = t;
+  }
+}
 template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_reg_c2r(FftArgs args, const BeamDev* beams) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -868,6 +953,7 @@ struct GreenArgs {
   int nx, ny, nz;
   int odd;
   const double2* tw;
+  int64_t stride;  // several kernels of one grid (blockIdx.y): from one to the next, gd and gh
 };
 
 __host__ __device__ __forceinline__ double green_scale(int nx, int ny, int nz) {
@@ -935,6 +1021,9 @@ __global__ __launch_bounds__(kFftThreads) void k_reg_green(GreenArgs args, const
     a.scale = green_scale(a.nx, a.ny, a.nz);
     a.odd = 0;
     a.tw = d.plan.tw[AXIS];
+  } else if (gridDim.y > 1) {
+    a.gd += blockIdx.y * a.stride;
+    if (a.gh) a.gh = (T*)a.gh + blockIdx.y * a.stride;
   }
   if (a.g->status) return;
   with_line_length(2 * (AXIS == 0 ? a.nx : (AXIS == 1 ? a.ny : a.nz)), [&](auto len) {
@@ -1107,13 +1196,47 @@ void launch_reg_green(int axis, dim3 grid, size_t lds, const GreenArgs& a, const
     hipLaunchKernelGGL((k_reg_green<T, 2>), grid, nt, lds, s, a, beams);
 }
 
-// The three even/odd DFT passes of one octant kernel gd (odd_axis: -1 for an even kernel) and
-// the scaled conversion into gh.
+// One DFT pass of an octant kernel with the runtime-length engine
+template <typename T>
+hipError_t kernel_spectrum_axis(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
+                                double* gd, T* gh, int a, bool odd, hipStream_t s) {
+  const int ex = nx + 1, ey = ny + 1, ez = nz + 1;
+  int na, planes, LB, NT;
+  green_lines(a, nx, ny, nz, &na, &planes);
+  const int ncx = (na + 1) / 2;
+  // (element stride, line stride a, plane stride b)
+  const int64_t cfg[3][3] = {{1, ex, (int64_t)ex * ey},
+                             {ex, 1, (int64_t)ex * ey},
+                             {(int64_t)ex * ey, 1, 0}};
+  shape_for(p.full[a].M, ncx, &LB, &NT);
+  const dim3 grid(ceil_div(ncx, LB), planes);
+  const size_t lds = (size_t)LB * (p.full[a].M + 1) * sizeof(Cx<double>) +
+                     (size_t)p.full[a].M * sizeof(double2);
+  if (odd)
+    hipLaunchKernelGGL(k_green_dft<true>, grid, dim3(NT), lds, s, gd, p.full[a], p.tw[a],
+                       cfg[a][0], cfg[a][1], cfg[a][2], na, LB);
+  else
+    hipLaunchKernelGGL(k_green_dft<false>, grid, dim3(NT), lds, s, gd, p.full[a], p.tw[a],
+                       cfg[a][0], cfg[a][1], cfg[a][2], na, LB);
+  PIC_TRY(hipGetLastError());
+  if (a == 2) {
+    const int64_t total = (int64_t)ex * ey * ez;
+    hipLaunchKernelGGL((k_green_finish<T>), dim3(grid_for(total)), dim3(256), 0, s, g, gd, gh,
+                       total, green_scale(nx, ny, nz));
+  }
+  return hipGetLastError();
+}
+
+// The three even/odd DFT passes of `count` octant kernels gd, consecutive (odd_axis: -1 for even
+// kernels), and the scaled conversion into gh.  The register transforms take all of them in one
+// launch per axis: one kernel's lines of a 64^3 grid fill a third of the chip, and its three
+// h-derivatives' nine launches of 6.5 us became three of 9 us.
 template <typename T>
 hipError_t kernel_spectrum(const Geom* g, const FftPlan& p, int nx, int ny, int nz, double* gd,
-                           T* gh, int odd_axis, hipStream_t s) {
+                           T* gh, int odd_axis, hipStream_t s, int count = 1) {
   const int ex = nx + 1, ey = ny + 1, ez = nz + 1;
   const double scale = green_scale(nx, ny, nz);
+  const int64_t total = (int64_t)ex * ey * ez;
   for (int a = 0; a < 3; ++a) {
     int na, planes, LB, NT;
     green_lines(a, nx, ny, nz, &na, &planes);
@@ -1121,32 +1244,14 @@ hipError_t kernel_spectrum(const Geom* g, const FftPlan& p, int nx, int ny, int 
     size_t lds;
     if (reg_shape<double>(p.full[a].M, a != 0, &LB, &lds)) {
       const GreenArgs ga{g,  gd, a == 2 ? (void*)gh : nullptr, scale, nx, ny, nz, a == odd_axis,
-                         p.tw[a]};
-      launch_reg_green<T>(a, dim3(ceil_div(ncx * planes, LB)), lds, ga, nullptr, s);
+                         p.tw[a], total};
+      launch_reg_green<T>(a, dim3(ceil_div(ncx * planes, LB), count), lds, ga, nullptr, s);
       PIC_TRY(hipGetLastError());
       continue;
     }
-    // (element stride, line stride a, plane stride b)
-    const int64_t cfg[3][3] = {{1, ex, (int64_t)ex * ey},
-                               {ex, 1, (int64_t)ex * ey},
-                               {(int64_t)ex * ey, 1, 0}};
-    shape_for(p.full[a].M, ncx, &LB, &NT);
-    const dim3 grid(ceil_div(ncx, LB), planes);
-    lds = (size_t)LB * (p.full[a].M + 1) * sizeof(Cx<double>) +
-          (size_t)p.full[a].M * sizeof(double2);
-    if (a == odd_axis)
-      hipLaunchKernelGGL(k_green_dft<true>, grid, dim3(NT), lds, s, gd, p.full[a], p.tw[a],
-                         cfg[a][0], cfg[a][1], cfg[a][2], na, LB);
-    else
-      hipLaunchKernelGGL(k_green_dft<false>, grid, dim3(NT), lds, s, gd, p.full[a], p.tw[a],
-                         cfg[a][0], cfg[a][1], cfg[a][2], na, LB);
-    PIC_TRY(hipGetLastError());
-    if (a == 2) {
-      const int64_t total = (int64_t)ex * ey * ez;
-      hipLaunchKernelGGL((k_green_finish<T>), dim3(grid_for(total)), dim3(256), 0, s, g, gd, gh,
-                         total, scale);
-      PIC_TRY(hipGetLastError());
-    }
+    for (int q = 0; q < count; ++q)
+      PIC_TRY(kernel_spectrum_axis<T>(g, p, nx, ny, nz, gd + q * total, gh + q * total, a,
+                                      a == odd_axis, s));
   }
   return hipSuccess;
 }
@@ -1166,12 +1271,8 @@ template <typename T>
 hipError_t launch_green_dh_spectra(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
                                    bool field, double2* dc, double* gd, T* gh, hipStream_t s) {
   PIC_TRY(launch_igf_dh(g, nx, ny, nz, field, dc, gd, s));
+  if (!field) return kernel_spectrum<T>(g, p, nx, ny, nz, gd, gh, -1, s, 3);
   const int64_t total = (int64_t)(nx + 1) * (ny + 1) * (nz + 1);
-  if (!field) {
-    for (int b = 0; b < 3; ++b)
-      PIC_TRY(kernel_spectrum<T>(g, p, nx, ny, nz, gd + b * total, gh + b * total, -1, s));
-    return hipSuccess;
-  }
   // kernel (a, b) = f = 3 a + b in gd; its spectrum at 3 b + a, so that the three of one b
   // are consecutive, as the transposed field solve reads them
   for (int f = 0; f < 9; ++f)
@@ -1419,6 +1520,53 @@ hipError_t launch_solve_ghost_source(const Geom* g, const FftPlan& p, int nx, in
   return run_passes<T>(g, p, nx, ny, nz, 1, psi, Wv, gh, chi, s);
 }
 
+// launch_solve_ghost_source, and the geometry sums' partials: partial[b 3 + c] (b < *nparts) adds
+// up to sum_n Q_n (dG_c * psi)_n over nodes 0..n-1 for the three spectra dgh (as gh, consecutive).
+// psi's transform is shared, and no convolution with dgh is formed: the sums are taken over the
+// spectra (zdot_reg).  At 64^3 in float64 three convolutions and grid dots took 146 us, Q's
+// transforms and the sums take 38 (the sums 24, bound by their registers: two lines are live, one
+// wave per SIMD).  Needs a line length with register transforms along z, else *nparts = 0.
+template <typename T>
+hipError_t launch_solve_ghost_dots(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
+                                   const T* psi, void* Wv, const T* gh, T* chi, const T* Q,
+                                   void* WQ, const T* dgh, double* partial, int max_parts,
+                                   int* nparts, hipStream_t s) {
+  *nparts = 0;
+  int LB;
+  size_t lds;
+  if (!reg_shape<T>(2 * nz, true, &LB, &lds))
+    return launch_solve_ghost_source<T>(g, p, nx, ny, nz, psi, Wv, gh, chi, s);
+  FftArgs q = fft_args<T>(g, p, nx, ny, nz, 0, WQ, WQ);
+  q.src = Q;
+  PIC_TRY(pass_r2c<T>(q, p, s));
+  PIC_TRY((pass_y<T, -1>(q, p, s)));
+  FftArgs a = fft_args<T>(g, p, nx, ny, nz, 1, Wv, Wv);
+  a.src = psi;
+  a.gh = gh;
+  a.dst = chi;
+  PIC_TRY(pass_r2c<T>(a, p, s));
+  PIC_TRY((pass_y<T, -1>(a, p, s)));
+  FftArgs d = a;
+  d.W2 = WQ;
+  d.gh = dgh;
+  const int nb = std::min(ceil_div((nx + 1) * 2 * ny, LB), max_parts);
+  hipLaunchKernelGGL((k_reg_zdot<T>), dim3(nb), dim3(kFftThreads), lds, s, d,
+                     (int64_t)(nx + 1) * (ny + 1) * (nz + 1), partial);
+  PIC_TRY(hipGetLastError());
+  *nparts = nb;
+  PIC_TRY(pass_z<T>(a, p, s));
+  PIC_TRY((pass_y<T, +1>(a, p, s)));
+  return pass_c2r<T>(a, p, s);
+}
+
+template hipError_t launch_solve_ghost_dots<double>(const Geom*, const FftPlan&, int, int, int,
+                                                    const double*, void*, const double*, double*,
+                                                    const double*, void*, const double*, double*,
+                                                    int, int*, hipStream_t);
+template hipError_t launch_solve_ghost_dots<float>(const Geom*, const FftPlan&, int, int, int,
+                                                   const float*, void*, const float*, float*,
+                                                   const float*, void*, const float*, double*,
+                                                   int, int*, hipStream_t);
 template hipError_t launch_solve_ghost_source<double>(const Geom*, const FftPlan&, int, int, int,
                                                       const double*, void*, const double*,
                                                       double*, hipStream_t);

@@ -327,6 +327,9 @@ hipError_t launch_adj_stage(const double* X, double* lam, const Geom* g, Consts 
 template <typename T>
 hipError_t launch_grid_dot(const T* a, const T* b, int64_t count, int ncomp, int64_t stride,
                            double* partial, double* out, hipStream_t s);
+// out[c] = sum_b partial[b sb + c sq], b < nblocks, c < ncols, in a fixed order
+hipError_t launch_combine_cols(const double* partial, int nblocks, int64_t sb, int64_t sq,
+                               int ncols, double* out, hipStream_t s);
 // the geometry's terms of a reverse step from geo (see adjoint.hip) into lam and dk
 hipError_t launch_adj_geom(const double* X, double* lam, const Geom* g, Consts c,
                            const AdjSlice& sl, const double* geo, double* dk, hipStream_t s);
@@ -396,5 +399,13 @@ hipError_t launch_solve(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
 template <typename T>
 hipError_t launch_solve_ghost_source(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
                                      const T* psi, void* W, const T* Gh, T* chi, hipStream_t s);
+// The same, and partial sums of sum_n Q_n (dG_c * psi)_n / (4 pi eps0), c < 3, over nodes 0..n-1
+// for the spectra dgh[c] (Q like rho; WQ: (nx+1) 2ny nz complex of scratch): partial[b 3 + c],
+// b < *nparts <= max_parts.  *nparts = 0: not available for this grid, only chi was formed.
+template <typename T>
+hipError_t launch_solve_ghost_dots(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
+                                   const T* psi, void* W, const T* Gh, T* chi, const T* Q,
+                                   void* WQ, const T* dgh, double* partial, int max_parts,
+                                   int* nparts, hipStream_t s);
 
 }  // namespace pic
