@@ -296,7 +296,8 @@ size_t pic_adjoint_workspace_bytes(const pic_beam_desc* d, int n_steps, int ckpt
  *   dJ_dL[36]    if d_xi (device, 6*n draws with X0 = L xi) is given: dJ/dL = sum_i lam_i xi_i^T,
  *                row-major 6x6 (host); only the lower triangle is a parameter of L.
  * The forward states are checkpointed every ckpt_every steps in the caller's workspace
- * d_adj_work (pic_adjoint_workspace_bytes, 256-byte aligned) and recomputed per segment.
+ * d_adj_work (pic_adjoint_workspace_bytes, 256-byte aligned) and recomputed per segment, except
+ * the last segment's, which the forward pass keeps.
  * Lattices as for pic_track_n_steps (thin, drift and quadrupole elements, one step per slice).
  * With desc.direct_field the charge's adjoint goes through the transposed field convolutions.
  * Needs desc.space_charge = 1 and 1 <= n_el <= 1024.  Synchronises `stream`; returns the device error flag of any step

@@ -523,12 +523,12 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
             "gather-kick-drift");
     else
       STAGE(b, PIC_STAGE_GKD, s,
-            launch_gkd<T>(B, b->geom, (const T*)b->E, e.L, e.second, has_next, nx.first, b->c,
-                          b->box, s),
+            launch_gkd<T>(B, B, b->geom, (const T*)b->E, e.L, e.second, has_next, nx.first,
+                          b->c, b->box, s),
             "gather-kick-drift");
     if (diag && !tiles) {  // moments at the end of the step, then the next first half map
       HIP_OK(launch_moments(B, b->c.n, b->mom_partial, diag_j, s), "diagnostics");
-      if (more) HIP_OK(launch_half_box(B, nx.first, b->c, b->box, s), "diagnostics");
+      if (more) HIP_OK(launch_half_box(B, B, nx.first, b->c, b->box, s), "diagnostics");
     }
     // B holds the updated particles in slot order
     double* tX = A; A = B; B = tX;
@@ -578,7 +578,7 @@ AdjLayout adj_layout(const pic_beam_desc* d, int n_steps, int ck) {
   A.nseg = (n_steps + ck - 1) / ck;
   A.geoms = take(kGeomSlot * (size_t)n_steps);
   A.ckpt = take(6 * sizeof(double) * n * (size_t)A.nseg);
-  A.segX = take(6 * sizeof(double) * n * (size_t)ck);
+  A.segX = take(6 * sizeof(double) * n * (size_t)(ck - 1));  // a segment's first is in ckpt
   A.segE = take(3 * es * ng * (size_t)ck);
   A.segG = take(es * G3 * (size_t)ck * (d->direct_field ? 3 : 1));  // the step's kernel spectra
   A.segQ = take(es * ng * (size_t)ck);                                // the step's charge grid
@@ -693,13 +693,28 @@ pic_status expand_adjoint(const pic_element* lat, int n_el, std::vector<AdjSlice
   return PIC_OK;
 }
 
+// One step of the reverse sweep's forward pass, in the caller's particle order: from the state src
+// to the state dst (b->XA in between, which holds the kick-point state; dst == nullptr: no state,
+// only the grids), keeping the charge grid rho, the field E and the kernel spectra gh.  g is the
+// step's geometry slot, computed when box is given.  The Green spectrum runs on the auxiliary
+// stream beside the binning and the deposit; what it writes was last read before the fork.
 template <typename T>
-pic_status forward_step_recorded(pic_beam b, double* X, const Geom* g, const AdjSlice& e,
-                               T* gh, T* E, T* rho, hipStream_t s, Box* box) {
-  // the slice's first half map (with the box when a geometry is to be computed), deposit into
-  // rho, Green spectrum, solve, kick and the second half map; g is the step's geometry slot
-  HIP_OK(launch_half_box(X, e.first, b->c, box, s), "adjoint forward");
-  if (box) HIP_OK(launch_geometry(box, const_cast<Geom*>(g), b->c, s), "adjoint forward");
+pic_status forward_step_recorded(pic_beam b, const double* src, double* dst, Geom* g,
+                                 const AdjSlice& e, T* gh, T* E, T* rho, hipStream_t s, Box* box) {
+  double* X = b->XA;
+  HIP_OK(launch_half_box(src, X, e.first, b->c, box, s), "adjoint forward");
+  if (box) HIP_OK(launch_geometry(box, g, b->c, s), "adjoint forward");
+  HIP_OK(hipEventRecord(b->ev_fork, s), "fork");
+  HIP_OK(hipStreamWaitEvent(b->aux, b->ev_fork, 0), "fork");
+  if (b->d.direct_field)  // gh holds the three field kernels' spectra
+    HIP_OK(launch_green_field_spectrum<T>(g, b->plan, b->d.nx, b->d.ny, b->d.nz, b->hcorners,
+                                          b->gd3, gh, b->aux),
+           "adjoint forward");
+  else
+    HIP_OK(launch_green_spectrum<T>(g, b->plan, b->d.nx, b->d.ny, b->d.nz, b->corners, b->Gd, gh,
+                                    b->aux),
+           "adjoint forward");
+  HIP_OK(hipEventRecord(b->ev_join, b->aux), "join");
   // binned deposit from a tile-sorted copy (XB) of the kick-point state
   HIP_OK(launch_bin(X, b->idA, g, b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks, b->nchunks,
                     b->XB, b->idB, true, s),
@@ -707,23 +722,18 @@ pic_status forward_step_recorded(pic_beam b, double* X, const Geom* g, const Adj
   HIP_OK(launch_deposit_tiles<T>(b->XB, nullptr, g, b->c, b->sp, b->chunks, b->nchunks, rho, s,
                                  b->tacc, b->tscale),
          "adjoint forward");
-  if (b->d.direct_field) {  // gh holds the three field kernels' spectra
-    HIP_OK(launch_green_field_spectrum<T>(g, b->plan, b->d.nx, b->d.ny, b->d.nz, b->hcorners,
-                                          b->gd3, gh, s),
-           "adjoint forward");
+  HIP_OK(hipStreamWaitEvent(s, b->ev_join, 0), "join");
+  if (b->d.direct_field)
     HIP_OK(launch_solve_field<T>(g, b->plan, b->d.nx, b->d.ny, b->d.nz, (const T*)rho, b->W,
                                  b->W2, gh, E, s),
            "adjoint forward");
-  } else {
-    HIP_OK(launch_green_spectrum<T>(g, b->plan, b->d.nx, b->d.ny, b->d.nz, b->corners, b->Gd, gh,
-                                    s),
-           "adjoint forward");
+  else
     HIP_OK(launch_solve<T>(g, b->plan, b->d.nx, b->d.ny, b->d.nz, (const T*)rho, b->W, gh,
                            (T*)b->phi, E, s),
            "adjoint forward");
-  }
-  HIP_OK(launch_gkd<T>(X, g, E, e.L, e.second, 0, half_drift(0.0), b->c, box, s),
-         "adjoint forward");
+  if (dst)
+    HIP_OK(launch_gkd<T>(X, dst, g, E, e.L, e.second, 0, half_drift(0.0), b->c, box, s),
+           "adjoint forward");
   return PIC_OK;
 }
 
@@ -765,45 +775,63 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
   HIP_OK(launch_zero<uint32_t>((uint32_t*)(aw + A.geoms), (int64_t)(kGeomSlot / 4) * n_steps, s),
          "adjoint setup");
   HIP_OK(launch_zero<double>(dk, kMaxLattice, s), "adjoint setup");
-  // forward: checkpoints at segment starts, geometry of every step kept
+  // The state at the start of step j of the segment being swept: a segment's first in its
+  // checkpoint, the others in segX; the final one in X.
+  auto state = [&](int j) -> double* {
+    if (j == n_steps) return b->X;
+    if (j % ck == 0) return ckpt + 6 * n * (size_t)(j / ck);
+    return segX + 6 * n * (size_t)(j % ck - 1);
+  };
+  auto recorded_step = [&](int j, Box* box, bool last) {
+    const size_t q = (size_t)(j % ck);
+    return forward_step_recorded<T>(b, state(j), last ? nullptr : state(j + 1), geom(j),
+                                    sl[j % nsl], segG + G3 * q, segE + 3 * ng * q, segQ + ng * q,
+                                    s, box);
+  };
+  // forward: the checkpoints and the geometry of every step kept, and all of the last segment
+  // (the first to be swept, so it need not be computed again).  1e6 particles, 64^3, 20 steps, a
+  // checkpoint every 10: 19.66 ms with every segment computed again, its states copied, and the
+  // spectra on the main stream; 15.65 so.
+  const int last_seg = (A.nseg - 1) * ck;
+  HIP_OK(hipMemcpyAsync(ckpt, b->X, 6 * sizeof(double) * n, hipMemcpyDeviceToDevice, s),
+         "adjoint checkpoint");
   for (int j = 0; j < n_steps; ++j) {
-    if (j % ck == 0)
-      HIP_OK(hipMemcpyAsync(ckpt + 6 * n * (size_t)(j / ck), b->X, 6 * sizeof(double) * n,
-                            hipMemcpyDeviceToDevice, s),
-             "adjoint checkpoint");
-    pic_status st = forward_step_recorded<T>(b, b->X, geom(j), sl[j % nsl],
-                                           direct ? (T*)b->gh3 : (T*)b->Gh, (T*)b->E,
-                                           (T*)b->rho, s, b->box);
+    pic_status st =
+        j < last_seg
+            ? forward_step_recorded<T>(b, j % ck ? b->X : state(j), (j + 1) % ck ? b->X : state(j + 1),
+                                       geom(j), sl[j % nsl], direct ? (T*)b->gh3 : (T*)b->Gh,
+                                       (T*)b->E, (T*)b->rho, s, b->box)
+            : recorded_step(j, b->box, false);
     if (st != PIC_OK) return st;
   }
   HIP_OK(launch_moments(b->X, b->d.n, b->mom_partial, b->mom_out, s), "adjoint objective");
   HIP_OK(launch_obj_grad(b->X, b->d.n, b->mom_out, w, lam, small, s), "adjoint objective");
   // reverse, one checkpoint segment at a time
-  double* XW = b->XA;
   for (int seg = A.nseg - 1; seg >= 0; --seg) {
     const int c0 = seg * ck, c1 = std::min(c0 + ck, n_steps);
-    HIP_OK(hipMemcpyAsync(XW, ckpt + 6 * n * (size_t)seg, 6 * sizeof(double) * n,
-                          hipMemcpyDeviceToDevice, s),
-           "adjoint recompute");
-    for (int j = c0; j < c1; ++j) {
-      const int q = j - c0;
-      HIP_OK(hipMemcpyAsync(segX + 6 * n * (size_t)q, XW, 6 * sizeof(double) * n,
-                            hipMemcpyDeviceToDevice, s),
-             "adjoint recompute");
-      pic_status st = forward_step_recorded<T>(b, XW, geom(j), sl[j % nsl], segG + G3 * (size_t)q,
-                                             segE + 3 * ng * (size_t)q, segQ + ng * (size_t)q, s,
-                                             nullptr);
+    for (int j = c0; j < c1 && c0 < last_seg; ++j) {
+      pic_status st = recorded_step(j, nullptr, j + 1 == c1);
       if (st != PIC_OK) return st;
     }
     for (int j = c1 - 1; j >= c0; --j) {
       const int q = j - c0;
       const AdjSlice& el = sl[j % nsl];
-      const double* Xs = segX + 6 * n * (size_t)q;
-      // the state after the step: the next stored one, the next segment's checkpoint, or the
-      // final state
-      const double* Xn = j + 1 < c1 ? segX + 6 * n * (size_t)(q + 1)
-                         : j + 1 < n_steps ? ckpt + 6 * n * (size_t)(seg + 1)
-                                           : b->X;
+      const double* Xs = state(j);
+      const double* Xn = state(j + 1);
+      // The h-derivatives' spectra and the charge grid's transform on the auxiliary stream beside
+      // the vector deposit (all of them last read by the step before the fork)
+      const T* Qj = segQ + ng * (size_t)q;
+      bool dots = false;
+      HIP_OK(hipEventRecord(b->ev_fork, s), "fork");
+      HIP_OK(hipStreamWaitEvent(b->aux, b->ev_fork, 0), "fork");
+      HIP_OK(launch_green_dh_spectra<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, direct,
+                                        (double2*)(aw + A.dc), (double*)(aw + A.dgd), dgh, b->aux),
+             "adjoint geometry");
+      if (!direct)
+        HIP_OK(launch_charge_spectrum<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, Qj,
+                                         aw + A.qhat, &dots, b->aux),
+               "adjoint geometry");
+      HIP_OK(hipEventRecord(b->ev_join, b->aux), "join");
       HIP_OK(launch_adj_dk_second(Xn, lam, b->c, el, (double*)(aw + A.dk_part), dk, s),
              "adjoint");
       HIP_OK(launch_zero<T>(e, 3 * ng, s), "adjoint");
@@ -818,10 +846,7 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
       } else {
         HIP_OK(launch_adj_a<T>(Xs, lam, geom(j), b->c, el, e, ext_part, geo, s), "adjoint");
       }
-      HIP_OK(launch_green_dh_spectra<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, direct,
-                                        (double2*)(aw + A.dc), (double*)(aw + A.dgd), dgh, s),
-             "adjoint geometry");
-      const T* Qj = segQ + ng * (size_t)q;
+      HIP_OK(hipStreamWaitEvent(s, b->ev_join, 0), "join");
       int ndots = 0;
       if (direct) {  // transposed field convolutions, b->E as their scratch
         HIP_OK(launch_solve_field_T<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, e, b->W, b->W2,
@@ -831,8 +856,9 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
         HIP_OK(launch_adj_div<T>(geom(j), e, psi, b->d.nx, b->d.ny, b->d.nz, s), "adjoint");
         // the geometry sums through the Green's function come with it (below)
         HIP_OK(launch_solve_ghost_dots<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, psi, b->W,
-                                          segG + G3 * (size_t)q, chi, Qj, aw + A.qhat, dgh,
-                                          dot_part, kAdjBlocks, &ndots, s),
+                                          segG + G3 * (size_t)q, chi,
+                                          dots ? aw + A.qhat : nullptr, dgh, dot_part,
+                                          kAdjBlocks, &ndots, s),
                "adjoint");
       }
       HIP_OK(launch_adj_b<T>(Xs, lam, geom(j), b->c, el, segE + 3 * ng * (size_t)q, chi,

@@ -1520,26 +1520,37 @@ hipError_t launch_solve_ghost_source(const Geom* g, const FftPlan& p, int nx, in
   return run_passes<T>(g, p, nx, ny, nz, 1, psi, Wv, gh, chi, s);
 }
 
-// launch_solve_ghost_source, and the geometry sums' partials: partial[b 3 + c] (b < *nparts) adds
-// up to sum_n Q_n (dG_c * psi)_n over nodes 0..n-1 for the three spectra dgh (as gh, consecutive).
-// psi's transform is shared, and no convolution with dgh is formed: the sums are taken over the
-// spectra (zdot_reg).  At 64^3 in float64 three convolutions and grid dots took 146 us, Q's
-// transforms and the sums take 38 (the sums 24, bound by their registers: two lines are live, one
-// wave per SIMD).  Needs a line length with register transforms along z, else *nparts = 0.
+// The x and y passes of the charge grid Q into WQ, for launch_solve_ghost_dots.  *done = false and
+// nothing run: no register transforms for this length along z.
 template <typename T>
-hipError_t launch_solve_ghost_dots(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
-                                   const T* psi, void* Wv, const T* gh, T* chi, const T* Q,
-                                   void* WQ, const T* dgh, double* partial, int max_parts,
-                                   int* nparts, hipStream_t s) {
-  *nparts = 0;
+hipError_t launch_charge_spectrum(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
+                                  const T* Q, void* WQ, bool* done, hipStream_t s) {
   int LB;
   size_t lds;
-  if (!reg_shape<T>(2 * nz, true, &LB, &lds))
-    return launch_solve_ghost_source<T>(g, p, nx, ny, nz, psi, Wv, gh, chi, s);
+  *done = reg_shape<T>(2 * nz, true, &LB, &lds);
+  if (!*done) return hipSuccess;
   FftArgs q = fft_args<T>(g, p, nx, ny, nz, 0, WQ, WQ);
   q.src = Q;
   PIC_TRY(pass_r2c<T>(q, p, s));
-  PIC_TRY((pass_y<T, -1>(q, p, s)));
+  return pass_y<T, -1>(q, p, s);
+}
+
+// launch_solve_ghost_source, and the geometry sums' partials: partial[b 3 + c] (b < *nparts) adds
+// up to sum_n Q_n (dG_c * psi)_n over nodes 0..n-1 for the three spectra dgh (as gh, consecutive)
+// and Q's x and y transform WQ.  psi's transform is shared, and no convolution with dgh is formed:
+// the sums are taken over the spectra (zdot_reg).  At 64^3 in float64 three convolutions and grid
+// dots took 146 us, Q's transforms and the sums take 38 (the sums 24, bound by their registers: two
+// lines are live, one wave per SIMD).  WQ == nullptr: *nparts = 0, no sums.
+template <typename T>
+hipError_t launch_solve_ghost_dots(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
+                                   const T* psi, void* Wv, const T* gh, T* chi, const void* WQ,
+                                   const T* dgh, double* partial, int max_parts, int* nparts,
+                                   hipStream_t s) {
+  *nparts = 0;
+  int LB;
+  size_t lds;
+  if (!WQ || !reg_shape<T>(2 * nz, true, &LB, &lds))
+    return launch_solve_ghost_source<T>(g, p, nx, ny, nz, psi, Wv, gh, chi, s);
   FftArgs a = fft_args<T>(g, p, nx, ny, nz, 1, Wv, Wv);
   a.src = psi;
   a.gh = gh;
@@ -1547,7 +1558,7 @@ hipError_t launch_solve_ghost_dots(const Geom* g, const FftPlan& p, int nx, int 
   PIC_TRY(pass_r2c<T>(a, p, s));
   PIC_TRY((pass_y<T, -1>(a, p, s)));
   FftArgs d = a;
-  d.W2 = WQ;
+  d.W2 = const_cast<void*>(WQ);  // read only
   d.gh = dgh;
   const int nb = std::min(ceil_div((nx + 1) * 2 * ny, LB), max_parts);
   hipLaunchKernelGGL((k_reg_zdot<T>), dim3(nb), dim3(kFftThreads), lds, s, d,
@@ -1561,12 +1572,16 @@ hipError_t launch_solve_ghost_dots(const Geom* g, const FftPlan& p, int nx, int 
 
 template hipError_t launch_solve_ghost_dots<double>(const Geom*, const FftPlan&, int, int, int,
                                                     const double*, void*, const double*, double*,
-                                                    const double*, void*, const double*, double*,
-                                                    int, int*, hipStream_t);
+                                                    const void*, const double*, double*, int,
+                                                    int*, hipStream_t);
 template hipError_t launch_solve_ghost_dots<float>(const Geom*, const FftPlan&, int, int, int,
                                                    const float*, void*, const float*, float*,
-                                                   const float*, void*, const float*, double*,
-                                                   int, int*, hipStream_t);
+                                                   const void*, const float*, double*, int, int*,
+                                                   hipStream_t);
+template hipError_t launch_charge_spectrum<double>(const Geom*, const FftPlan&, int, int, int,
+                                                   const double*, void*, bool*, hipStream_t);
+template hipError_t launch_charge_spectrum<float>(const Geom*, const FftPlan&, int, int, int,
+                                                  const float*, void*, bool*, hipStream_t);
 template hipError_t launch_solve_ghost_source<double>(const Geom*, const FftPlan&, int, int, int,
                                                       const double*, void*, const double*,
                                                       double*, hipStream_t);

@@ -201,8 +201,9 @@ hipError_t launch_gather(const double* X, const Geom* g, const T* E, T* Ep, Cons
 template <typename T>
 hipError_t launch_push(double* X, int kind, double value, const T* Ep, Consts c, hipStream_t s);
 template <typename T>
-hipError_t launch_gkd(double* X, const Geom* g, const T* E, double L, const HalfMap& second,
-                      int has_next, const HalfMap& first_next, Consts c, Box* box, hipStream_t s);
+hipError_t launch_gkd(const double* src, double* X, const Geom* g, const T* E, double L,
+                      const HalfMap& second, int has_next, const HalfMap& first_next, Consts c,
+                      Box* box, hipStream_t s);  // src may be X
 hipError_t launch_moments(const double* X, int64_t n, double* partial, double* out,
                           hipStream_t s);
 template <typename T>
@@ -260,7 +261,9 @@ hipError_t launch_copy_if_ok(const void* src, void* dst, size_t bytes, const Geo
 hipError_t launch_half_maps(double* X, const HalfMap& first, const HalfMap& second, Consts c,
                             hipStream_t s);
 // one half map in place and (box != nullptr) the box of the new positions
-hipError_t launch_half_box(double* X, const HalfMap& h, Consts c, Box* box, hipStream_t s);
+// src may be X
+hipError_t launch_half_box(const double* src, double* X, const HalfMap& h, Consts c, Box* box,
+                           hipStream_t s);
 hipError_t launch_unpermute(const double* A, const uint32_t* idA, int64_t n, double* X,
                             uint32_t* keys, uint32_t* hist, uint32_t* cursor, int4* chunks,
                             uint32_t* nchunks, double* B, uint32_t* idB, const Geom* g,
@@ -400,12 +403,15 @@ template <typename T>
 hipError_t launch_solve_ghost_source(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
                                      const T* psi, void* W, const T* Gh, T* chi, hipStream_t s);
 // The same, and partial sums of sum_n Q_n (dG_c * psi)_n / (4 pi eps0), c < 3, over nodes 0..n-1
-// for the spectra dgh[c] (Q like rho; WQ: (nx+1) 2ny nz complex of scratch): partial[b 3 + c],
-// b < *nparts <= max_parts.  *nparts = 0: not available for this grid, only chi was formed.
+// for the spectra dgh[c]: partial[b 3 + c], b < *nparts <= max_parts.  WQ: Q (laid out like rho)
+// transformed by launch_charge_spectrum ((nx+1) 2ny nz complex), or nullptr: only chi is formed.
 template <typename T>
 hipError_t launch_solve_ghost_dots(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
-                                   const T* psi, void* W, const T* Gh, T* chi, const T* Q,
-                                   void* WQ, const T* dgh, double* partial, int max_parts,
-                                   int* nparts, hipStream_t s);
+                                   const T* psi, void* W, const T* Gh, T* chi, const void* WQ,
+                                   const T* dgh, double* partial, int max_parts, int* nparts,
+                                   hipStream_t s);
+template <typename T>
+hipError_t launch_charge_spectrum(const Geom* g, const FftPlan& p, int nx, int ny, int nz,
+                                  const T* Q, void* WQ, bool* done, hipStream_t s);
 
 }  // namespace pic

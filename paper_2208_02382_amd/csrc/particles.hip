@@ -235,12 +235,21 @@ __global__ __launch_bounds__(kBlock) void k_push(double* __restrict__ X, int kin
 // kick over L, the slice's second half map; if has_next, the next slice's first half map, and
 // accumulate the box of the new positions (the next step's grid).  The two half maps act as
 // their product (half_product), as in the tiled gather-kick, so both paths compute the same bits.
+// src may be X; another src is left as it is, and in a device error state (status != 0) X is then
+// its copy.
 template <int S, typename T>
-__global__ __launch_bounds__(kBlock) void k_gkd(double* __restrict__ X, const Geom* __restrict__ g,
+__global__ __launch_bounds__(kBlock) void k_gkd(const double* src, double* X,
+                                                const Geom* __restrict__ g,
                                                 const T* __restrict__ E, double L, HalfMap second,
                                                 int has_next, HalfMap first_next, Consts c,
                                                 Box* box) {
-  if (g->status) return;
+  if (g->status) {
+    if (src != X)
+      for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < 6 * c.n;
+           i += (int64_t)gridDim.x * kBlock)
+        X[i] = src[i];
+    return;
+  }
   const HalfMap maps = half_product(second, first_next, has_next != 0);
   double o[3] = {g->origin[0], g->origin[1], g->origin[2]};
   double ih[3] = {g->inv_h[0], g->inv_h[1], g->inv_h[2]};
@@ -250,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void k_gkd(double* __restrict__ X, const Ge
   for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kBlock) {
     double v[6];
-    for (int r = 0; r < 6; ++r) v[r] = X[r * n + i];
+    for (int r = 0; r < 6; ++r) v[r] = src[r * n + i];
     T e[3];
     gather_one<S, T>(v[0], v[2], v[4], o, ih, E, c, e);
     sc_kick(v, (double)e[0], (double)e[1], (double)e[2], L, c);
@@ -413,13 +422,13 @@ hipError_t launch_push(double* X, int kind, double value, const T* Ep, Consts c,
 }
 
 template <typename T>
-hipError_t launch_gkd(double* X, const Geom* g, const T* E, double L, const HalfMap& second,
+hipError_t launch_gkd(const double* src, double* X, const Geom* g, const T* E, double L, const HalfMap& second,
                       int has_next, const HalfMap& first_next, Consts c, Box* box, hipStream_t s) {
   if (c.shape == 1)
-    hipLaunchKernelGGL((k_gkd<1, T>), dim3(grid_for(c.n)), dim3(kBlock), 0, s, X, g, E, L,
+    hipLaunchKernelGGL((k_gkd<1, T>), dim3(grid_for(c.n)), dim3(kBlock), 0, s, src, X, g, E, L,
                        second, has_next, first_next, c, box);
   else
-    hipLaunchKernelGGL((k_gkd<2, T>), dim3(grid_for(c.n)), dim3(kBlock), 0, s, X, g, E, L,
+    hipLaunchKernelGGL((k_gkd<2, T>), dim3(grid_for(c.n)), dim3(kBlock), 0, s, src, X, g, E, L,
                        second, has_next, first_next, c, box);
   return hipGetLastError();
 }
@@ -438,17 +447,17 @@ __global__ __launch_bounds__(kBlock) void k_half_maps(double* __restrict__ X, Ha
   }
 }
 
-// One half map in place, with the box of the new positions (the first half of a step when the
-// previous step's end state was needed on its own, for diagnostics).
-__global__ __launch_bounds__(kBlock) void k_half_box(double* __restrict__ X, HalfMap h, Consts c,
-                                                     Box* box) {
+// One half map from src to X (src may be X), with the box of the new positions (the first half of
+// a step when the previous step's end state is needed on its own: diagnostics, the reverse sweep).
+__global__ __launch_bounds__(kBlock) void k_half_box(const double* src, double* X, HalfMap h,
+                                                     Consts c, Box* box) {
   const int64_t n = c.n;
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
   bool bad = false;
   for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kBlock) {
     double v[6];
-    for (int r = 0; r < 6; ++r) v[r] = X[r * n + i];
+    for (int r = 0; r < 6; ++r) v[r] = src[r * n + i];
     apply_half(h, v, c.inv_gamma2);
     for (int r = 0; r < 6; ++r) X[r * n + i] = v[r];
     const double p[3] = {v[0], v[2], v[4]};
@@ -461,8 +470,9 @@ __global__ __launch_bounds__(kBlock) void k_half_box(double* __restrict__ X, Hal
   if (box) box_accumulate_block(lo, hi, bad, box);
 }
 
-hipError_t launch_half_box(double* X, const HalfMap& h, Consts c, Box* box, hipStream_t s) {
-  hipLaunchKernelGGL(k_half_box, dim3(grid_for(c.n)), dim3(kBlock), 0, s, X, h, c, box);
+hipError_t launch_half_box(const double* src, double* X, const HalfMap& h, Consts c, Box* box,
+                           hipStream_t s) {
+  hipLaunchKernelGGL(k_half_box, dim3(grid_for(c.n)), dim3(kBlock), 0, s, src, X, h, c, box);
   return hipGetLastError();
 }
 
@@ -502,9 +512,9 @@ template hipError_t launch_gather<float>(const double*, const Geom*, const float
                                          hipStream_t);
 template hipError_t launch_push<double>(double*, int, double, const double*, Consts, hipStream_t);
 template hipError_t launch_push<float>(double*, int, double, const float*, Consts, hipStream_t);
-template hipError_t launch_gkd<double>(double*, const Geom*, const double*, double, const HalfMap&,
+template hipError_t launch_gkd<double>(const double*, double*, const Geom*, const double*, double, const HalfMap&,
                                        int, const HalfMap&, Consts, Box*, hipStream_t);
-template hipError_t launch_gkd<float>(double*, const Geom*, const float*, double, const HalfMap&,
+template hipError_t launch_gkd<float>(const double*, double*, const Geom*, const float*, double, const HalfMap&,
                                       int, const HalfMap&, Consts, Box*, hipStream_t);
 template hipError_t launch_zero<double>(double*, int64_t, hipStream_t);
 template hipError_t launch_zero<float>(float*, int64_t, hipStream_t);
