@@ -336,9 +336,9 @@ hipError_t launch_combine_cols(const double* partial, int nblocks, int64_t sb, i
 // the geometry's terms of a reverse step from geo (see adjoint.hip) into lam and dk
 hipError_t launch_adj_geom(const double* X, double* lam, const Geom* g, Consts c,
                            const AdjSlice& sl, const double* geo, double* dk, hipStream_t s);
-// binned vector deposit; an error if the three float64 windows exceed the LDS a workgroup may use
+// vector deposit of P's rows through their ranking (nullptr: in slot order); an error if the three float64 windows exceed the LDS a workgroup may use
 template <typename T>
-hipError_t launch_vdeposit_tiles(const double* B, const Geom* g, Consts c, const SortPlan& sp,
+hipError_t launch_vdeposit_tiles(const double* P, const uint32_t* perm, const Geom* g, Consts c, const SortPlan& sp,
                                  const int4* chunks, const uint32_t* nchunks, T* e,
                                  hipStream_t s);
 template <typename T>
