@@ -183,29 +183,69 @@ __global__ void k_combine_cols(const double* __restrict__ partial, int nblocks, 
   if (threadIdx.x == 0) out[q] = s;
 }
 
-// block partials of ncomp grid dot products: partial[blk ncomp + c] = sum_i a[c stride + i]
-// b[c stride + i] over this block's share of i < count
+// block partials of a grid dot product
 template <typename T>
 __global__ __launch_bounds__(kBlk) void k_grid_dot(const T* __restrict__ a,
                                                    const T* __restrict__ b, int64_t count,
-                                                   int ncomp, int64_t stride,
                                                    double* __restrict__ partial) {
-  __shared__ double sh[kBlk / 64];
-  for (int c = 0; c < ncomp; ++c) {
-    double acc = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)kBlk + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * kBlk)
-      acc += (double)a[c * stride + i] * (double)b[c * stride + i];
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  double acc = 0.0;
+  for (int64_t i = blockIdx.x * (int64_t)kBlk + threadIdx.x; i < count;
+       i += (int64_t)gridDim.x * kBlk)
+    acc += (double)a[i] * (double)b[i];
+  block_partial(acc, partial);
+}
+
+// block partials of the three sums of e_c F.c over the nodes: partial[c gridDim + blk]
+template <typename T>
+__global__ __launch_bounds__(kBlk) void k_field_dot(const T* __restrict__ e,
+                                                    const Node4<T>* __restrict__ F, int64_t nodes,
+                                                    double* __restrict__ partial) {
+  double acc[3] = {0.0, 0.0, 0.0};
+  for (int64_t i = blockIdx.x * (int64_t)kBlk + threadIdx.x; i < nodes;
+       i += (int64_t)gridDim.x * kBlk) {
+    const Node4<T> f = F[i];
+    acc[0] += (double)e[i] * (double)f.x;
+    acc[1] += (double)e[nodes + i] * (double)f.y;
+    acc[2] += (double)e[2 * nodes + i] * (double)f.z;
+  }
+  for (int c = 0; c < 3; ++c) {
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = 0.0;
-      for (int w = 0; w < kBlk / 64; ++w) t += sh[w];
-      partial[blockIdx.x * ncomp + c] = t;
+    block_partial(acc[c], partial + c * (int64_t)gridDim.x);
+  }
+}
+
+// see launch_pack_field; GRAD: from phi, the centred differences of k_grad
+template <typename T, bool GRAD>
+__global__ __launch_bounds__(kBlk) void k_pack_field(const Geom* __restrict__ g,
+                                                     const T* __restrict__ src,
+                                                     Node4<T>* __restrict__ F, int nx, int ny,
+                                                     int nz) {
+  if (g->status) return;
+  const int64_t total = (int64_t)nx * ny * nz;
+  const T cx = (T)(1.0 / (2.0 * g->h_rest[0]));
+  const T cy = (T)(1.0 / (2.0 * g->h_rest[1]));
+  const T cz = (T)(1.0 / (2.0 * g->h_rest[2]));
+  const int64_t sy = nx + 2, sz = sy * (ny + 2);
+  for (int64_t t = blockIdx.x * (int64_t)kBlk + threadIdx.x; t < total;
+       t += (int64_t)gridDim.x * kBlk) {
+    if constexpr (GRAD) {
+      const Idx3 q = split3(t, nx, ny);
+      const T* p = src + (q.z + 1) * sz + (q.y + 1) * sy + (q.x + 1);
+      F[t] = {-(p[1] - p[-1]) * cx, -(p[sy] - p[-sy]) * cy, -(p[sz] - p[-sz]) * cz, T(0)};
+    } else {
+      F[t] = {src[t], src[total + t], src[2 * total + t], T(0)};
     }
   }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlk) void k_pack_chi(const Geom* __restrict__ g,
+                                                   const T* __restrict__ chi,
+                                                   Node4<T>* __restrict__ F, int64_t nodes) {
+  if (g->status) return;
+  for (int64_t t = blockIdx.x * (int64_t)kBlk + threadIdx.x; t < nodes;
+       t += (int64_t)gridDim.x * kBlk)
+    F[t].w = chi[t];
 }
 
 // The second half map's strength term of a quadrupole slice: sum_i lam_i . DG x_next,i with
@@ -275,12 +315,14 @@ __global__ __launch_bounds__(kBlk) void k_adj_a(const double* __restrict__ X,
 }
 
 // Pass A for the binned vector deposit: lam <- (second half map)^T lam, and the particle's
-// kick-point position and a = (C L lam_px, C L lam_py, gamma C L lam_delta) written as the rows
-// (r_x, a_x, r_y, a_y, r_z, a_z) of P, the layout the binning and the tiled deposit read.
+// kick-point position and a = (C L lam_px, C L lam_py, gamma C L lam_delta) written as a record for
+// the deposit, which reads them in another order; the positions also as the rows 0, 2, 4 of P,
+// which the ranking reads.
 __global__ __launch_bounds__(kBlk) void k_adj_stage(const double* __restrict__ X,
                                                     double* __restrict__ lam,
                                                     const Geom* __restrict__ g, Consts c,
                                                     AdjSlice sl, double* __restrict__ P,
+                                                    AdjRecord* __restrict__ recs,
                                                     double* __restrict__ ext_partial) {
   if (g->status) return;
   const int64_t n = c.n;
@@ -296,12 +338,9 @@ __global__ __launch_bounds__(kBlk) void k_adj_stage(const double* __restrict__ X
     for (int q = 0; q < 6; ++q) lm[q] = lam[q * n + i];
     apply_half_T(sl.second, lm, c.inv_gamma2);
     for (int q = 0; q < 6; ++q) lam[q * n + i] = lm[q];
-    P[i] = r[0];
-    P[n + i] = c.C * L * lm[1];
-    P[2 * n + i] = r[1];
-    P[3 * n + i] = c.C * L * lm[3];
-    P[4 * n + i] = r[2];
-    P[5 * n + i] = c.gamma * c.C * L * lm[5];
+    const double a[3] = {c.C * L * lm[1], c.C * L * lm[3], c.gamma * c.C * L * lm[5]};
+    for (int q = 0; q < 3; ++q) P[2 * q * n + i] = r[q];
+    recs[i] = {{r[0], r[1], r[2]}, {a[0], a[1], a[2]}};
   }
   ext_block_partial(ex, ext_partial);
 }
@@ -342,8 +381,7 @@ template <int S, typename T>
 __global__ __launch_bounds__(kBlk) void k_adj_b(const double* __restrict__ X,
                                                 double* __restrict__ lam,
                                                 const Geom* __restrict__ g, Consts c,
-                                                AdjSlice sl, const T* __restrict__ E,
-                                                const T* __restrict__ chi,
+                                                AdjSlice sl, const Node4<T>* __restrict__ F,
                                                 double* __restrict__ dk_partial,
                                                 double* __restrict__ geo_partial) {
   double acc = 0.0;
@@ -352,7 +390,6 @@ __global__ __launch_bounds__(kBlk) void k_adj_b(const double* __restrict__ X,
     const double o[3] = {g->origin[0], g->origin[1], g->origin[2]};
     const double ih[3] = {g->inv_h[0], g->inv_h[1], g->inv_h[2]};
     const int64_t n = c.n;
-    const int64_t ng = (int64_t)c.nx * c.ny * c.nz;
     const double L = sl.L;
     for (int64_t i = blockIdx.x * (int64_t)kBlk + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kBlk) {
@@ -370,9 +407,9 @@ __global__ __launch_bounds__(kBlk) void k_adj_b(const double* __restrict__ X,
         for (int yb = 0; yb <= S; ++yb) {
           const int64_t row = ((int64_t)(bz + za) * c.ny + (by + yb)) * c.nx + bx;
           for (int q = 0; q <= S; ++q) {
-            const int64_t node = row + q;
-            const double s = a[0] * (double)E[node] + a[1] * (double)E[ng + node] +
-                             a[2] * (double)E[2 * ng + node] + c.q_macro * (double)chi[node];
+            const Node4<T> f = F[row + q];
+            const double s = a[0] * (double)f.x + a[1] * (double)f.y + a[2] * (double)f.z +
+                             c.q_macro * (double)f.w;
             gx += (dx[q] * ih[0]) * wy[yb] * wz[za] * s;
             gy += wx[q] * (dy[yb] * ih[1]) * wz[za] * s;
             gz += wx[q] * wy[yb] * (dz[za] * ih[2]) * s;
@@ -602,10 +639,11 @@ hipError_t launch_adj_a(const double* X, double* lam, const Geom* g, Consts c,
 }
 
 hipError_t launch_adj_stage(const double* X, double* lam, const Geom* g, Consts c,
-                            const AdjSlice& sl, double* P, double* ext_partial, double* geo,
-                            hipStream_t s) {
+                            const AdjSlice& sl, double* P, AdjRecord* recs, double* ext_partial,
+                            double* geo, hipStream_t s) {
   const int nb = grid_for(c.n);
-  hipLaunchKernelGGL(k_adj_stage, dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, P, ext_partial);
+  hipLaunchKernelGGL(k_adj_stage, dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, P, recs,
+                     ext_partial);
   PIC_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_ext_combine, dim3(6), dim3(64), 0, s, ext_partial, nb, geo);
   return hipGetLastError();
@@ -618,13 +656,42 @@ hipError_t launch_combine_cols(const double* partial, int nblocks, int64_t sb, i
 }
 
 template <typename T>
-hipError_t launch_grid_dot(const T* a, const T* b, int64_t count, int ncomp, int64_t stride,
-                           double* partial, double* out, hipStream_t s) {
+hipError_t launch_grid_dot(const T* a, const T* b, int64_t count, double* partial, double* out,
+                           hipStream_t s) {
   const int nb = grid_for(count);
-  hipLaunchKernelGGL((k_grid_dot<T>), dim3(nb), dim3(kBlk), 0, s, a, b, count, ncomp, stride,
+  hipLaunchKernelGGL((k_grid_dot<T>), dim3(nb), dim3(kBlk), 0, s, a, b, count, partial);
+  PIC_TRY(hipGetLastError());
+  return launch_combine_cols(partial, nb, 1, 0, 1, out, s);
+}
+
+template <typename T>
+hipError_t launch_field_dot(const T* e, const T* F, int64_t nodes, double* partial, double* out,
+                            hipStream_t s) {
+  const int nb = grid_for(nodes);
+  hipLaunchKernelGGL((k_field_dot<T>), dim3(nb), dim3(kBlk), 0, s, e, (const Node4<T>*)F, nodes,
                      partial);
   PIC_TRY(hipGetLastError());
-  return launch_combine_cols(partial, nb, ncomp, 1, ncomp, out, s);
+  return launch_combine_cols(partial, nb, 1, nb, 3, out, s);
+}
+
+template <typename T>
+hipError_t launch_pack_field(const Geom* g, const T* phi, const T* E, T* F, int nx, int ny, int nz,
+                             hipStream_t s) {
+  const dim3 grid(grid_for((int64_t)nx * ny * nz));
+  if (phi)
+    hipLaunchKernelGGL((k_pack_field<T, true>), grid, dim3(kBlk), 0, s, g, phi, (Node4<T>*)F, nx,
+                       ny, nz);
+  else
+    hipLaunchKernelGGL((k_pack_field<T, false>), grid, dim3(kBlk), 0, s, g, E, (Node4<T>*)F, nx,
+                       ny, nz);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_pack_chi(const Geom* g, const T* chi, T* F, int64_t nodes, hipStream_t s) {
+  hipLaunchKernelGGL((k_pack_chi<T>), dim3(grid_for(nodes)), dim3(kBlk), 0, s, g, chi,
+                     (Node4<T>*)F, nodes);
+  return hipGetLastError();
 }
 
 hipError_t launch_adj_geom(const double* X, double* lam, const Geom* g, Consts c,
@@ -644,15 +711,15 @@ hipError_t launch_adj_div(const Geom* g, const T* e, T* psi, int nx, int ny, int
 
 template <typename T>
 hipError_t launch_adj_b(const double* X, double* lam, const Geom* g, Consts c, const AdjSlice& sl,
-                        const T* E, const T* chi, double* dk_partial, double* dk,
+                        const T* F, double* dk_partial, double* dk,
                         double* geo_partial, double* geo, hipStream_t s) {
   const int nb = grid_for(c.n);
   if (c.shape == 1)
-    hipLaunchKernelGGL((k_adj_b<1, T>), dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, E, chi,
-                       dk_partial, geo_partial);
+    hipLaunchKernelGGL((k_adj_b<1, T>), dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl,
+                       (const Node4<T>*)F, dk_partial, geo_partial);
   else
-    hipLaunchKernelGGL((k_adj_b<2, T>), dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, E, chi,
-                       dk_partial, geo_partial);
+    hipLaunchKernelGGL((k_adj_b<2, T>), dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl,
+                       (const Node4<T>*)F, dk_partial, geo_partial);
   PIC_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_adj_dk_combine, dim3(1), dim3(64), 0, s, dk_partial, nb, dk, sl.elem);
   PIC_TRY(hipGetLastError());
@@ -687,19 +754,29 @@ template hipError_t launch_adj_a<double>(const double*, double*, const Geom*, Co
                                          const AdjSlice&, double*, double*, double*, hipStream_t);
 template hipError_t launch_adj_a<float>(const double*, double*, const Geom*, Consts,
                                         const AdjSlice&, float*, double*, double*, hipStream_t);
-template hipError_t launch_grid_dot<double>(const double*, const double*, int64_t, int, int64_t,
-                                            double*, double*, hipStream_t);
-template hipError_t launch_grid_dot<float>(const float*, const float*, int64_t, int, int64_t,
-                                           double*, double*, hipStream_t);
+template hipError_t launch_grid_dot<double>(const double*, const double*, int64_t, double*, double*,
+                                            hipStream_t);
+template hipError_t launch_field_dot<double>(const double*, const double*, int64_t, double*, double*,
+                                             hipStream_t);
+template hipError_t launch_pack_field<double>(const Geom*, const double*, const double*, double*, int, int,
+                                              int, hipStream_t);
+template hipError_t launch_pack_chi<double>(const Geom*, const double*, double*, int64_t, hipStream_t);
+template hipError_t launch_grid_dot<float>(const float*, const float*, int64_t, double*, double*,
+                                            hipStream_t);
+template hipError_t launch_field_dot<float>(const float*, const float*, int64_t, double*, double*,
+                                             hipStream_t);
+template hipError_t launch_pack_field<float>(const Geom*, const float*, const float*, float*, int, int,
+                                              int, hipStream_t);
+template hipError_t launch_pack_chi<float>(const Geom*, const float*, float*, int64_t, hipStream_t);
 template hipError_t launch_adj_div<double>(const Geom*, const double*, double*, int, int, int,
                                            hipStream_t);
 template hipError_t launch_adj_div<float>(const Geom*, const float*, float*, int, int, int,
                                           hipStream_t);
 template hipError_t launch_adj_b<double>(const double*, double*, const Geom*, Consts,
-                                         const AdjSlice&, const double*, const double*, double*,
-                                         double*, double*, double*, hipStream_t);
+                                         const AdjSlice&, const double*, double*, double*,
+                                         double*, double*, hipStream_t);
 template hipError_t launch_adj_b<float>(const double*, double*, const Geom*, Consts,
-                                        const AdjSlice&, const float*, const float*, double*,
-                                        double*, double*, double*, hipStream_t);
+                                        const AdjSlice&, const float*, double*, double*, double*,
+                                        double*, hipStream_t);
 
 }  // namespace pic

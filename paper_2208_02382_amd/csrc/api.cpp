@@ -523,8 +523,8 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
             "gather-kick-drift");
     else
       STAGE(b, PIC_STAGE_GKD, s,
-            launch_gkd<T>(B, B, b->geom, (const T*)b->E, e.L, e.second, has_next, nx.first,
-                          b->c, b->box, s),
+            launch_gkd<T>(B, B, b->geom, (const T*)b->E, false, e.L, e.second, has_next,
+                          nx.first, b->c, b->box, s),
             "gather-kick-drift");
     if (diag && !tiles) {  // moments at the end of the step, then the next first half map
       HIP_OK(launch_moments(B, b->c.n, b->mom_partial, diag_j, s), "diagnostics");
@@ -579,7 +579,7 @@ AdjLayout adj_layout(const pic_beam_desc* d, int n_steps, int ck) {
   A.geoms = take(kGeomSlot * (size_t)n_steps);
   A.ckpt = take(6 * sizeof(double) * n * (size_t)A.nseg);
   A.segX = take(6 * sizeof(double) * n * (size_t)(ck - 1));  // a segment's first is in ckpt
-  A.segE = take(3 * es * ng * (size_t)ck);
+  A.segE = take(4 * es * ng * (size_t)ck);  // the step's field and chi, packed per node
   A.segG = take(es * G3 * (size_t)ck * (d->direct_field ? 3 : 1));  // the step's kernel spectra
   A.segQ = take(es * ng * (size_t)ck);                                // the step's charge grid
   A.e = take(3 * es * ng);
@@ -693,39 +693,14 @@ pic_status expand_adjoint(const pic_element* lat, int n_el, std::vector<AdjSlice
   return PIC_OK;
 }
 
-// Binning of a state in the caller's order for the deposits of the reverse sweep: a ranking that
-// they read the state through while its rows (*P = X, *perm) fit the 256 MB of memory-side cache,
-// else a staged copy in tile order (*P = b->XB, *perm = nullptr).  A sweep ranked / copied, ms:
-// 20 steps of 1e5 CIC 32^3 6.19 / 8.25, 1e6 CIC 64^3 15.2 / 15.7, 1e6 TSC 24.4 / 26.3; 6 steps of
-// 4e6 TSC 64^3 19.7 / 20.9, of 1e7 CIC 128^3 32.6 / 31.1.
-constexpr int64_t kRankedAdjoint = (256ll << 20) / (6 * sizeof(double));
-
-pic_status bin_adjoint(pic_beam b, const double* X, const Geom* g, const double** P,
-                       const uint32_t** perm, hipStream_t s) {
-  if (b->c.n <= kRankedAdjoint) {
-    HIP_OK(launch_bin_perm(X, g, b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks, b->nchunks,
-                           b->perm, s),
-           "adjoint binning");
-    *P = X;
-    *perm = b->perm;
-  } else {
-    HIP_OK(launch_bin(X, b->idA, g, b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks,
-                      b->nchunks, b->XB, b->idB, true, s),
-           "adjoint binning");
-    *P = b->XB;
-    *perm = nullptr;
-  }
-  return PIC_OK;
-}
-
 // One step of the reverse sweep's forward pass, in the caller's particle order: from the state src
 // to the state dst (b->XA in between, which holds the kick-point state; dst == nullptr: no state,
-// only the grids), keeping the charge grid rho, the field E and the kernel spectra gh.  g is the
+// only the grids), keeping the charge grid rho, the packed field F and the kernel spectra gh.  g is the
 // step's geometry slot, computed when box is given.  The Green spectrum runs on the auxiliary
 // stream beside the binning and the deposit; what it writes was last read before the fork.
 template <typename T>
 pic_status forward_step_recorded(pic_beam b, const double* src, double* dst, Geom* g,
-                                 const AdjSlice& e, T* gh, T* E, T* rho, hipStream_t s, Box* box) {
+                                 const AdjSlice& e, T* gh, T* F, T* rho, hipStream_t s, Box* box) {
   double* X = b->XA;
   HIP_OK(launch_half_box(src, X, e.first, b->c, box, s), "adjoint forward");
   if (box) HIP_OK(launch_geometry(box, g, b->c, s), "adjoint forward");
@@ -740,24 +715,29 @@ pic_status forward_step_recorded(pic_beam b, const double* src, double* dst, Geo
                                     b->aux),
            "adjoint forward");
   HIP_OK(hipEventRecord(b->ev_join, b->aux), "join");
-  const uint32_t* perm;
-  const double* P;
-  pic_status st = bin_adjoint(b, X, g, &P, &perm, s);
-  if (st != PIC_OK) return st;
-  HIP_OK(launch_deposit_tiles<T>(P, perm, g, b->c, b->sp, b->chunks, b->nchunks, rho, s, b->tacc,
-                                 b->tscale),
+  // The deposit reads the caller's order through its ranking: a copy in tile order cost more at
+  // every size (a sweep ranked / copied, ms: 20 steps of 1e5 CIC 32^3 6.2 / 8.2, of 1e6 CIC 64^3
+  // 15.2 / 15.7, 6 steps of 4e6 TSC 64^3 19.7 / 20.9; with AdjRecord of 1e7 CIC 128^3 27.5 / 28.8).
+  HIP_OK(launch_bin_perm(X, g, b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks, b->nchunks,
+                         b->perm, s),
+         "adjoint forward");
+  HIP_OK(launch_deposit_tiles<T>(X, b->perm, g, b->c, b->sp, b->chunks, b->nchunks, rho, s,
+                                 b->tacc, b->tscale),
          "adjoint forward");
   HIP_OK(hipStreamWaitEvent(s, b->ev_join, 0), "join");
   if (b->d.direct_field)
     HIP_OK(launch_solve_field<T>(g, b->plan, b->d.nx, b->d.ny, b->d.nz, (const T*)rho, b->W,
-                                 b->W2, gh, E, s),
+                                 b->W2, gh, (T*)b->E, s),
            "adjoint forward");
   else
     HIP_OK(launch_solve<T>(g, b->plan, b->d.nx, b->d.ny, b->d.nz, (const T*)rho, b->W, gh,
-                           (T*)b->phi, E, s),
+                           (T*)b->phi, nullptr, s),
            "adjoint forward");
+  HIP_OK(launch_pack_field<T>(g, b->d.direct_field ? nullptr : (const T*)b->phi, (const T*)b->E, F,
+                              b->d.nx, b->d.ny, b->d.nz, s),
+         "adjoint forward");
   if (dst)
-    HIP_OK(launch_gkd<T>(X, dst, g, E, e.L, e.second, 0, half_drift(0.0), b->c, box, s),
+    HIP_OK(launch_gkd<T>(X, dst, g, F, true, e.L, e.second, 0, half_drift(0.0), b->c, box, s),
            "adjoint forward");
   return PIC_OK;
 }
@@ -810,7 +790,7 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
   auto recorded_step = [&](int j, Box* box, bool last) {
     const size_t q = (size_t)(j % ck);
     return forward_step_recorded<T>(b, state(j), last ? nullptr : state(j + 1), geom(j),
-                                    sl[j % nsl], segG + G3 * q, segE + 3 * ng * q, segQ + ng * q,
+                                    sl[j % nsl], segG + G3 * q, segE + 4 * ng * q, segQ + ng * q,
                                     s, box);
   };
   // forward: the checkpoints and the geometry of every step kept, and all of the last segment
@@ -825,7 +805,7 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
         j < last_seg
             ? forward_step_recorded<T>(b, j % ck ? b->X : state(j), (j + 1) % ck ? b->X : state(j + 1),
                                        geom(j), sl[j % nsl], direct ? (T*)b->gh3 : (T*)b->Gh,
-                                       (T*)b->E, (T*)b->rho, s, b->box)
+                                       segE, (T*)b->rho, s, b->box)
             : recorded_step(j, b->box, false);
     if (st != PIC_OK) return st;
   }
@@ -861,14 +841,16 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
              "adjoint");
       HIP_OK(launch_zero<T>(e, 3 * ng, s), "adjoint");
       if (vtiles) {
-        // kick-point positions and deposit values, binned, then the vector deposit
-        HIP_OK(launch_adj_stage(Xs, lam, geom(j), b->c, el, P, ext_part, geo, s), "adjoint");
-        const uint32_t* perm;
-        const double* rows;
-        pic_status st = bin_adjoint(b, P, geom(j), &rows, &perm, s);
-        if (st != PIC_OK) return st;
-        HIP_OK(launch_vdeposit_tiles<T>(rows, perm, geom(j), b->c, b->sp, b->chunks, b->nchunks, e,
-                                        s),
+        // kick-point positions and deposit values (the records in XB, free here), their ranking,
+        // then the binned vector deposit
+        AdjRecord* recs = (AdjRecord*)b->XB;
+        HIP_OK(launch_adj_stage(Xs, lam, geom(j), b->c, el, P, recs, ext_part, geo, s),
+               "adjoint");
+        HIP_OK(launch_bin_perm(P, geom(j), b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks,
+                               b->nchunks, b->perm, s),
+               "adjoint");
+        HIP_OK(launch_vdeposit_tiles<T>(recs, b->perm, geom(j), b->c, b->sp, b->chunks,
+                                        b->nchunks, e, s),
                "adjoint");
       } else {
         HIP_OK(launch_adj_a<T>(Xs, lam, geom(j), b->c, el, e, ext_part, geo, s), "adjoint");
@@ -888,8 +870,10 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
                                           kAdjBlocks, &ndots, s),
                "adjoint");
       }
-      HIP_OK(launch_adj_b<T>(Xs, lam, geom(j), b->c, el, segE + 3 * ng * (size_t)q, chi,
-                             (double*)(aw + A.dk_part), dk, geo_part, geo, s),
+      T* F = segE + 4 * ng * (size_t)q;
+      HIP_OK(launch_pack_chi<T>(geom(j), chi, F, ng, s), "adjoint");
+      HIP_OK(launch_adj_b<T>(Xs, lam, geom(j), b->c, el, F, (double*)(aw + A.dk_part), dk, geo_part,
+                             geo, s),
              "adjoint");
       // the geometry's terms: dJ/dh' through the kernel (the h-derivative kernels' convolution
       // with the adjoint source, dotted with the step's charge) into geo[12..14], and through
@@ -905,13 +889,13 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
           HIP_OK(launch_solve_ghost_source<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, psi,
                                               b->W, dgh + G1 * (size_t)hb, chi2, s),
                  "adjoint geometry");
-        HIP_OK(launch_grid_dot<T>(Qj, chi2, ng, 1, 0, dot_part, geo + 12 + hb, s),
+        HIP_OK(launch_grid_dot<T>(Qj, chi2, ng, dot_part, geo + 12 + hb, s),
                "adjoint geometry");
       }
       if (direct)
         HIP_OK(launch_zero<double>(geo + 15, 3, s), "adjoint geometry");
       else
-        HIP_OK(launch_grid_dot<T>(e, segE + 3 * ng * (size_t)q, ng, 3, ng, dot_part, geo + 15, s),
+        HIP_OK(launch_field_dot<T>(e, F, ng, dot_part, geo + 15, s),
                "adjoint geometry");
       HIP_OK(launch_adj_geom(Xs, lam, geom(j), b->c, el, geo, dk, s), "adjoint geometry");
     }

@@ -201,9 +201,9 @@ hipError_t launch_gather(const double* X, const Geom* g, const T* E, T* Ep, Cons
 template <typename T>
 hipError_t launch_push(double* X, int kind, double value, const T* Ep, Consts c, hipStream_t s);
 template <typename T>
-hipError_t launch_gkd(const double* src, double* X, const Geom* g, const T* E, double L,
-                      const HalfMap& second, int has_next, const HalfMap& first_next, Consts c,
-                      Box* box, hipStream_t s);  // src may be X
+hipError_t launch_gkd(const double* src, double* X, const Geom* g, const T* E, bool packed,
+                      double L, const HalfMap& second, int has_next, const HalfMap& first_next,
+                      Consts c, Box* box, hipStream_t s);  // src may be X; packed: see Node4
 hipError_t launch_moments(const double* X, int64_t n, double* partial, double* out,
                           hipStream_t s);
 template <typename T>
@@ -310,11 +310,33 @@ template <typename T>
 hipError_t launch_batch_solve(const BeamDev* beams, int nb, const BatchDims& bd, hipStream_t s);
 
 // ---- adjoint.hip
+// The field at a node, and the reverse sweep's chi there, in one aligned group: a gather in the
+// caller's order then touches a line or two per row of its stencil instead of one per component
+// and row.  1e6 particles in random order, float64: CIC gather-kick 58 -> 50 us, k_adj_b 91 -> 71;
+// with AdjRecord 20 steps of a TSC sweep 24.4 -> 19.4 ms.
+template <typename T>
+struct alignas(16) Node4 {
+  T x, y, z, w;
+};
+// F = (E', 0) per node: -grad of phi (nodes -1..n, as k_grad), or the components E ([3][nodes])
+// when phi is nullptr
+template <typename T>
+hipError_t launch_pack_field(const Geom* g, const T* phi, const T* E, T* F, int nx, int ny, int nz,
+                             hipStream_t s);
+// the w of F's nodes = chi
+template <typename T>
+hipError_t launch_pack_chi(const Geom* g, const T* chi, T* F, int64_t nodes, hipStream_t s);
 // dk[sl.elem] += sum_i lam_i . DG Xnext_i (the second half map's strength derivative, from the
 // state after it), for quadrupole slices; no-op otherwise
 hipError_t launch_adj_dk_second(const double* Xnext, const double* lam, Consts c,
                                 const AdjSlice& sl, double* dk_partial, double* dk,
                                 hipStream_t s);
+// position and deposit values of a particle, for reads in another order: one or two lines instead
+// of one per row (the vector deposit of 1e6 particles in random order 99 -> 42 us, k_adj_stage,
+// which writes them, 39 -> 52)
+struct alignas(16) AdjRecord {
+  double r[3], a[3];
+};
 // launch_adj_a and launch_adj_stage also find the particles at the box's min and max of the
 // kick-point positions (the first index for a tie): their indices into geo[0..5] (x, y, z min,
 // then max), ext_partial (12 doubles per block) as scratch
@@ -323,32 +345,35 @@ hipError_t launch_adj_a(const double* X, double* lam, const Geom* g, Consts c,
                         const AdjSlice& sl, T* e, double* ext_partial, double* geo,
                         hipStream_t s);
 hipError_t launch_adj_stage(const double* X, double* lam, const Geom* g, Consts c,
-                            const AdjSlice& sl, double* P, double* ext_partial, double* geo,
-                            hipStream_t s);
-// out[c] = sum_i a[c stride + i] b[c stride + i], i < count, c < ncomp (at most 64), in a fixed
-// order; partial holds ncomp doubles per block
+                            const AdjSlice& sl, double* P, AdjRecord* recs, double* ext_partial,
+                            double* geo, hipStream_t s);
+// *out = sum_i a[i] b[i], i < count, in a fixed order; partial holds a double per block
 template <typename T>
-hipError_t launch_grid_dot(const T* a, const T* b, int64_t count, int ncomp, int64_t stride,
-                           double* partial, double* out, hipStream_t s);
+hipError_t launch_grid_dot(const T* a, const T* b, int64_t count, double* partial, double* out,
+                           hipStream_t s);
+// out[c] = sum_i e[c nodes + i] F_i.c, c < 3; partial holds 3 doubles per block
+template <typename T>
+hipError_t launch_field_dot(const T* e, const T* F, int64_t nodes, double* partial, double* out,
+                            hipStream_t s);
 // out[c] = sum_b partial[b sb + c sq], b < nblocks, c < ncols, in a fixed order
 hipError_t launch_combine_cols(const double* partial, int nblocks, int64_t sb, int64_t sq,
                                int ncols, double* out, hipStream_t s);
 // the geometry's terms of a reverse step from geo (see adjoint.hip) into lam and dk
 hipError_t launch_adj_geom(const double* X, double* lam, const Geom* g, Consts c,
                            const AdjSlice& sl, const double* geo, double* dk, hipStream_t s);
-// vector deposit of P's rows through their ranking (nullptr: in slot order); an error if the three float64 windows exceed the LDS a workgroup may use
+// vector deposit of the records through their ranking; an error if the three float64 windows exceed the LDS a workgroup may use
 template <typename T>
-hipError_t launch_vdeposit_tiles(const double* P, const uint32_t* perm, const Geom* g, Consts c, const SortPlan& sp,
-                                 const int4* chunks, const uint32_t* nchunks, T* e,
-                                 hipStream_t s);
+hipError_t launch_vdeposit_tiles(const AdjRecord* recs, const uint32_t* perm,
+                                 const Geom* g, Consts c, const SortPlan& sp, const int4* chunks,
+                                 const uint32_t* nchunks, T* e, hipStream_t s);
 template <typename T>
 hipError_t launch_adj_div(const Geom* g, const T* e, T* psi, int nx, int ny, int nz,
                           hipStream_t s);
-// also the per-block sums of g_a and g_a u_a (6 kAdjBlocks doubles of geo_partial) into
-// geo[6..11]
+// F: (E', chi) per node.  Also the per-block sums of g_a and g_a u_a (6 kAdjBlocks doubles of
+// geo_partial) into geo[6..11]
 template <typename T>
 hipError_t launch_adj_b(const double* X, double* lam, const Geom* g, Consts c, const AdjSlice& sl,
-                        const T* E, const T* chi, double* dk_partial, double* dk,
+                        const T* F, double* dk_partial, double* dk,
                         double* geo_partial, double* geo, hipStream_t s);
 // (sigma_x, sigma_y, eps_x, eps_y) from the moments mom (mean 6, covariance upper 21) into
 // the device array out_m[4]

@@ -147,8 +147,9 @@ __global__ __launch_bounds__(kBlock) void k_init_philox(double* __restrict__ X, 
 
 // ---------------------------------------------------------------------------- gather
 
-// Field at the particles from E'[3][nz][ny][nx] with the deposit's weights.
-template <int S, typename T>
+// Field at the particles from E'[3][nz][ny][nx], or (PACKED) from one Node4 per node, with the
+// deposit's weights.
+template <int S, typename T, bool PACKED = false>
 __device__ __forceinline__ void gather_one(double x, double y, double z, const double* o,
                                            const double* ih, const T* __restrict__ E, Consts c,
                                            T out[3]) {
@@ -164,6 +165,13 @@ __device__ __forceinline__ void gather_one(double x, double y, double z, const d
       int64_t row = ((int64_t)(bz + a) * c.ny + (by + b)) * c.nx + bx;
       for (int q = 0; q <= S; ++q) {
         T w = (T)(wzy * wx[q]);
+        if constexpr (PACKED) {
+          const Node4<T> f = reinterpret_cast<const Node4<T>*>(E)[row + q];
+          ex += w * f.x;
+          ey += w * f.y;
+          ez += w * f.z;
+          continue;
+        }
         ex += w * E[row + q];
         ey += w * E[plane + row + q];
         ez += w * E[2 * plane + row + q];
@@ -236,8 +244,8 @@ __global__ __launch_bounds__(kBlock) void k_push(double* __restrict__ X, int kin
 // accumulate the box of the new positions (the next step's grid).  The two half maps act as
 // their product (half_product), as in the tiled gather-kick, so both paths compute the same bits.
 // src may be X; another src is left as it is, and in a device error state (status != 0) X is then
-// its copy.
-template <int S, typename T>
+// its copy.  PACKED: E is one Node4 per node.
+template <int S, typename T, bool PACKED>
 __global__ __launch_bounds__(kBlock) void k_gkd(const double* src, double* X,
                                                 const Geom* __restrict__ g,
                                                 const T* __restrict__ E, double L, HalfMap second,
@@ -261,7 +269,7 @@ __global__ __launch_bounds__(kBlock) void k_gkd(const double* src, double* X,
     double v[6];
     for (int r = 0; r < 6; ++r) v[r] = src[r * n + i];
     T e[3];
-    gather_one<S, T>(v[0], v[2], v[4], o, ih, E, c, e);
+    gather_one<S, T, PACKED>(v[0], v[2], v[4], o, ih, E, c, e);
     sc_kick(v, (double)e[0], (double)e[1], (double)e[2], L, c);
     apply_matrix(maps, v, c.inv_gamma2);
     if (has_next) {
@@ -422,14 +430,18 @@ hipError_t launch_push(double* X, int kind, double value, const T* Ep, Consts c,
 }
 
 template <typename T>
-hipError_t launch_gkd(const double* src, double* X, const Geom* g, const T* E, double L, const HalfMap& second,
-                      int has_next, const HalfMap& first_next, Consts c, Box* box, hipStream_t s) {
-  if (c.shape == 1)
-    hipLaunchKernelGGL((k_gkd<1, T>), dim3(grid_for(c.n)), dim3(kBlock), 0, s, src, X, g, E, L,
-                       second, has_next, first_next, c, box);
-  else
-    hipLaunchKernelGGL((k_gkd<2, T>), dim3(grid_for(c.n)), dim3(kBlock), 0, s, src, X, g, E, L,
-                       second, has_next, first_next, c, box);
+hipError_t launch_gkd(const double* src, double* X, const Geom* g, const T* E, bool packed,
+                      double L, const HalfMap& second, int has_next, const HalfMap& first_next,
+                      Consts c, Box* box, hipStream_t s) {
+#define PIC_GKD(SS, PP)                                                                        \
+  hipLaunchKernelGGL((k_gkd<SS, T, PP>), dim3(grid_for(c.n)), dim3(kBlock), 0, s, src, X, g, E, \
+                     L, second, has_next, first_next, c, box)
+  if (c.shape == 1) {
+    if (packed) PIC_GKD(1, true); else PIC_GKD(1, false);
+  } else {
+    if (packed) PIC_GKD(2, true); else PIC_GKD(2, false);
+  }
+#undef PIC_GKD
   return hipGetLastError();
 }
 
@@ -512,9 +524,9 @@ template hipError_t launch_gather<float>(const double*, const Geom*, const float
                                          hipStream_t);
 template hipError_t launch_push<double>(double*, int, double, const double*, Consts, hipStream_t);
 template hipError_t launch_push<float>(double*, int, double, const float*, Consts, hipStream_t);
-template hipError_t launch_gkd<double>(const double*, double*, const Geom*, const double*, double, const HalfMap&,
+template hipError_t launch_gkd<double>(const double*, double*, const Geom*, const double*, bool, double, const HalfMap&,
                                        int, const HalfMap&, Consts, Box*, hipStream_t);
-template hipError_t launch_gkd<float>(const double*, double*, const Geom*, const float*, double, const HalfMap&,
+template hipError_t launch_gkd<float>(const double*, double*, const Geom*, const float*, bool, double, const HalfMap&,
                                       int, const HalfMap&, Consts, Box*, hipStream_t);
 template hipError_t launch_zero<double>(double*, int64_t, hipStream_t);
 template hipError_t launch_zero<float>(float*, int64_t, hipStream_t);

@@ -769,12 +769,11 @@ __global__ __launch_bounds__(256) void k_tile_reduce(const Geom* __restrict__ g,
   tile_reduce_body<S, T>(g, c, sp, tacc, tscale, rho, blockIdx.x, gridDim.x);
 }
 
-// Vector deposit e_c(node) = sum_i W(r_i - node) v_c,i of the rows (r_x, v_x, r_y, v_y, r_z, v_z)
-// of P, read through their ranking perm or (nullptr) in slot order (the reverse sweep's transposed
-// gather), one chunk per workgroup: three
+// Vector deposit e_c(node) = sum_i W(r_i - node) a_c,i of the records, read through their ranking
+// perm (the reverse sweep's transposed gather), one chunk per workgroup: three
 // float64 LDS windows (the values have both signs), flushed with global atomics.
 template <int S, typename T>
-__device__ __forceinline__ void vdeposit_tiles_body(const double* __restrict__ P,
+__device__ __forceinline__ void vdeposit_tiles_body(const AdjRecord* __restrict__ recs,
                                                     const uint32_t* __restrict__ perm,
                                                     const Geom* __restrict__ g, Consts c,
                                                     SortPlan sp,
@@ -788,7 +787,6 @@ __device__ __forceinline__ void vdeposit_tiles_body(const double* __restrict__ P
   const double ih[3] = {g->inv_h[0], g->inv_h[1], g->inv_h[2]};
   const int Wx = sp.T[0] + S, Wy = sp.T[1] + S, Wz = sp.T[2] + S;
   const int nw = Wx * Wy * Wz;
-  const int64_t n = c.n;
   const int64_t ng = (int64_t)c.nx * c.ny * c.nz;
   const uint32_t nck = *nchunks;
   for (uint32_t ci = blk; ci < nck; ci += nblk) {
@@ -799,12 +797,12 @@ __device__ __forceinline__ void vdeposit_tiles_body(const double* __restrict__ P
     for (int w = threadIdx.x; w < 3 * nw; w += (int)blockDim.x) win[w] = 0.0;
     __syncthreads();
     for (int64_t slot = ch.y + threadIdx.x; slot < ch.z; slot += (int)blockDim.x) {
-      const int64_t i = perm ? perm[slot] : slot;
+      const AdjRecord p = recs[perm[slot]];
+      const double* v = p.a;
       double wx[S + 1], wy[S + 1], wz[S + 1];
-      const int bx = stencil<S>((P[i] - o[0]) * ih[0], c.nx, wx);
-      const int by = stencil<S>((P[2 * n + i] - o[1]) * ih[1], c.ny, wy);
-      const int bz = stencil<S>((P[4 * n + i] - o[2]) * ih[2], c.nz, wz);
-      const double v[3] = {P[n + i], P[3 * n + i], P[5 * n + i]};
+      const int bx = stencil<S>((p.r[0] - o[0]) * ih[0], c.nx, wx);
+      const int by = stencil<S>((p.r[1] - o[1]) * ih[1], c.ny, wy);
+      const int bz = stencil<S>((p.r[2] - o[2]) * ih[2], c.nz, wz);
       const int lx = bx - ox, ly = by - oy, lz = bz - oz;
       const bool inside = lx >= 0 && lx < sp.T[0] && ly >= 0 && ly < sp.T[1] && lz >= 0 &&
                           lz < sp.T[2];
@@ -840,14 +838,14 @@ __device__ __forceinline__ void vdeposit_tiles_body(const double* __restrict__ P
 }
 
 template <int S, typename T>
-__global__ __launch_bounds__(kMaxThreads) void k_vdeposit_tiles(const double* __restrict__ P,
+__global__ __launch_bounds__(kMaxThreads) void k_vdeposit_tiles(const AdjRecord* __restrict__ recs,
                                                          const uint32_t* __restrict__ perm,
                                                          const Geom* __restrict__ g, Consts c,
                                                          SortPlan sp,
                                                          const int4* __restrict__ chunks,
                                                          const uint32_t* __restrict__ nchunks,
                                                          T* __restrict__ e) {
-  vdeposit_tiles_body<S, T>(P, perm, g, c, sp, chunks, nchunks, e, blockIdx.x, gridDim.x);
+  vdeposit_tiles_body<S, T>(recs, perm, g, c, sp, chunks, nchunks, e, blockIdx.x, gridDim.x);
 }
 
 template <int S, typename T>
@@ -1690,30 +1688,32 @@ hipError_t launch_deposit_tiles(const double* B, const uint32_t* perm, const Geo
 }
 
 template <typename T>
-hipError_t launch_vdeposit_tiles(const double* P, const uint32_t* perm, const Geom* g, Consts c, const SortPlan& sp,
-                                 const int4* chunks, const uint32_t* nchunks, T* e,
-                                 hipStream_t s) {
+hipError_t launch_vdeposit_tiles(const AdjRecord* recs, const uint32_t* perm,
+                                 const Geom* g, Consts c, const SortPlan& sp, const int4* chunks,
+                                 const uint32_t* nchunks, T* e, hipStream_t s) {
   const int S = c.shape;
   const size_t lds = 3 * sizeof(double) * (size_t)(sp.T[0] + S) * (sp.T[1] + S) * (sp.T[2] + S);
   const dim3 grid((unsigned)sp.blocks), block((unsigned)sp.threads);
   if (S == 1) {
     PIC_TRY_LDS((k_vdeposit_tiles<1, T>), lds);
-    hipLaunchKernelGGL((k_vdeposit_tiles<1, T>), grid, block, lds, s, P, perm, g, c, sp, chunks, nchunks,
+    hipLaunchKernelGGL((k_vdeposit_tiles<1, T>), grid, block, lds, s, recs, perm, g, c, sp, chunks, nchunks,
                        e);
   } else {
     PIC_TRY_LDS((k_vdeposit_tiles<2, T>), lds);
-    hipLaunchKernelGGL((k_vdeposit_tiles<2, T>), grid, block, lds, s, P, perm, g, c, sp, chunks, nchunks,
+    hipLaunchKernelGGL((k_vdeposit_tiles<2, T>), grid, block, lds, s, recs, perm, g, c, sp, chunks, nchunks,
                        e);
   }
   return hipGetLastError();
 }
 
-template hipError_t launch_vdeposit_tiles<double>(const double*, const uint32_t*, const Geom*, Consts,
-                                                  const SortPlan&, const int4*, const uint32_t*,
-                                                  double*, hipStream_t);
-template hipError_t launch_vdeposit_tiles<float>(const double*, const uint32_t*, const Geom*, Consts,
-                                                 const SortPlan&, const int4*, const uint32_t*,
-                                                 float*, hipStream_t);
+template hipError_t launch_vdeposit_tiles<double>(const AdjRecord*, const uint32_t*,
+                                                  const Geom*, Consts, const SortPlan&,
+                                                  const int4*, const uint32_t*, double*,
+                                                  hipStream_t);
+template hipError_t launch_vdeposit_tiles<float>(const AdjRecord*, const uint32_t*,
+                                                 const Geom*, Consts, const SortPlan&,
+                                                 const int4*, const uint32_t*, float*,
+                                                 hipStream_t);
 
 template <typename T>
 hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,

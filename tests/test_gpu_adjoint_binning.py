@@ -1,5 +1,5 @@
-"""The reverse sweep on both sides of the particle count up to which its deposits read the caller's
-order through a ranking (beyond it a copy in tile order), against the oracle.
+"""The reverse sweep of millions of particles, whose deposits read them through their ranking as
+records, against the oracle; on both sides of the count whose rows fill the memory-side cache.
 
 A wrong order is an error of order one.  Bar 1e-10: the rounding of sums over 5.6e6 particles (chains
 of at most about 2000 terms here, 2e-13, pairwise in the oracle), times 100 for the geometry terms,
@@ -18,7 +18,7 @@ EDGE = (256 << 20) // 48
 
 
 @pytest.mark.parametrize("n", [EDGE, EDGE + 1])
-def test_reverse_sweep_on_both_sides_of_the_ranking_limit(n):
+def test_reverse_sweep_of_millions_of_particles(n):
     import paper_2208_02382_amd as lib
     cfg = workloads.SMALL
     nodes, w4 = (12, 12, 12), np.array([0.7, -0.4, 1.3, 0.9])
