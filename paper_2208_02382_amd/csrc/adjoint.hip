@@ -23,7 +23,7 @@
 //                    the rest-frame cell (h'_z = gamma h_z).  Through h = (max - min)/(n - 3.5)
 //                    and origin = min - 1.25 h these go to the kick-point coordinate of the
 //                    particle at the box's min (the first such index) and of the one at its
-//                    max (k_adj_geom, which also carries them through the first half map).
+//                    max (k_adj_finish, which also carries them through the first half map).
 // The kick-point positions are rebuilt from the stored step-start state with the same
 // expressions as the forward kernels (the slice's first half map).
 #include "device_common.hpp"
@@ -151,24 +151,6 @@ __device__ __forceinline__ void ext_block_partial(Extremes& ex, double* __restri
     partial[blockIdx.x * 12 + q] = bv;
     partial[blockIdx.x * 12 + 6 + q] = (double)bi;
   }
-}
-
-// out[q] = the index of extreme q = blockIdx.x over the block partials: one wave per slot, lane
-// l merging blocks l, l + 64, ..., then a butterfly; the merge (better value, lower index on a
-// tie) is a total order, so the result does not depend on the order of the merges
-__global__ void k_ext_combine(const double* __restrict__ partial, int nblocks,
-                              double* __restrict__ out) {
-  const int q = blockIdx.x;
-  double bv = q < 3 ? INFINITY : -INFINITY;
-  int64_t bi = INT64_MAX;
-  for (int b = threadIdx.x; b < nblocks; b += 64)
-    ext_merge1(q < 3, bv, bi, partial[b * 12 + q], (int64_t)partial[b * 12 + 6 + q]);
-  for (int off = 32; off > 0; off >>= 1) {
-    const double v = __shfl_xor(bv, off);
-    const int64_t i = __shfl_xor(bi, off);
-    ext_merge1(q < 3, bv, bi, v, i);
-  }
-  if (threadIdx.x == 0) out[q] = (double)bi;
 }
 
 // out[q] = sum over b < nblocks of partial[b sb + q sq] for column q = blockIdx.x: one wave per
@@ -451,54 +433,95 @@ __global__ __launch_bounds__(kBlk) void k_adj_b(const double* __restrict__ X,
   }
 }
 
-// The geometry's terms of one reverse step, one thread.  geo: [0..5] indices of the particles
-// at the box's min (x, y, z) and max, [6..8] sum g_a, [9..11] sum g_a u_a, [12..14] dJ/dh'_b
-// through the kernel, [15..17] sum_n e_b E'_b (the centred difference's term is minus that over
-// h'_b; zero for the direct field).  dJ/dmin and dJ/dmax are added to
-// those particles' kick-point position adjoints, carried through the slice's first half map
-// as k_adj_b carries every particle's (lam already holds the step-start adjoint), with the
-// first half map's strength term into dk[sl.elem].
-__global__ void k_adj_geom(const double* __restrict__ X, double* __restrict__ lam,
-                           const Geom* __restrict__ g, Consts c, AdjSlice sl,
-                           const double* __restrict__ geo, double* __restrict__ dk) {
-  if (blockIdx.x != 0 || threadIdx.x != 0 || g->status) return;
-  const int64_t n = c.n;
-  const double nodes[3] = {(double)c.nx, (double)c.ny, (double)c.nz};
-  const double dhr[3] = {1.0, 1.0, c.gamma};  // d h'_a / d h_a
-  double dmin[3], dmax[3];
-  for (int a = 0; a < 3; ++a) {
-    const double dJ_do = -geo[6 + a];
-    const double dJ_dhr = geo[12 + a] - geo[15 + a] / g->h_rest[a];
-    const double dJ_dh = -geo[9 + a] + dJ_dhr * dhr[a];
-    const double m = nodes[a] - 3.5;
-    dmin[a] = dJ_do * (1.0 + 1.25 / m) - dJ_dh / m;
-    dmax[a] = -dJ_do * 1.25 / m + dJ_dh / m;
-  }
-  double acc = 0.0;
-  for (int q = 0; q < 6; ++q) {
-    const int a = q % 3;
-    const int64_t i = (int64_t)geo[q];
-    if (i < 0 || i >= n) continue;  // no particle (cannot happen for n >= 1)
-    double d[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    d[2 * a] = q < 3 ? dmin[a] : dmax[a];
-    if (sl.first.type == kHalfThinDrift) {
-      const double ell = sl.first.ell;
-      d[1] += ell * d[0];
-      d[3] += ell * d[2];
-      d[5] += ell * d[4] * c.inv_gamma2;
-      acc += -X[i] * d[1] + X[2 * n + i] * d[3];
-      d[0] -= sl.first.k * d[1];
-      d[2] += sl.first.k * d[3];
-    } else {
-      if (sl.dk_kind == kDkMatrix) {
-        const double v[4] = {X[i], X[n + i], X[2 * n + i], X[3 * n + i]};
-        acc += plane_form(d, sl.dfx, sl.dfy, v);
+// The end of a reverse step, one workgroup: the block partials' sums, and the geometry's terms.
+// Columns, a wave each in turn, lane l taking partials l, l + 64, ..., then a butterfly (the order
+// does not depend on timing; the extremes' merge, better value and lower index on a tie, is a total
+// order): the particles at the box's min (x, y, z) and max; sum g_a and sum g_a u_a; dJ/dh'_b
+// through the kernel; sum_n e_b E'_b (the centred difference's term is minus that over h'_b); the
+// first half map's strength term.  Then one lane per face: dJ/dmin and dJ/dmax are added to those
+// particles' kick-point position adjoints, carried through the slice's first half map as k_adj_b
+// carries every particle's (lam already holds the step-start adjoint), with the first half map's
+// strength term into dk[sl.elem].  Six launches, the last of a single thread's chain of loads, took
+// 44 us of a step at 1e6 particles, this 16.
+__global__ __launch_bounds__(1024) void k_adj_finish(const double* __restrict__ X, double* lam,
+                                                     const Geom* __restrict__ g, Consts c,
+                                                     AdjSlice sl, AdjParts in,
+                                                     double* __restrict__ dk) {
+  __shared__ double sum[16];
+  __shared__ int64_t face[6];
+  if (g->status) return;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int q = wave; q < 19; q += (int)blockDim.x >> 6) {
+    if (q < 6) {
+      double bv = q < 3 ? INFINITY : -INFINITY;
+      int64_t bi = INT64_MAX;
+      for (int b = lane; b < in.nblocks; b += 64)
+        ext_merge1(q < 3, bv, bi, in.ext[b * 12 + q], (int64_t)in.ext[b * 12 + 6 + q]);
+      for (int off = 32; off > 0; off >>= 1) {
+        const double v = __shfl_xor(bv, off);
+        const int64_t i = __shfl_xor(bi, off);
+        ext_merge1(q < 3, bv, bi, v, i);
       }
-      apply_half_T(sl.first, d, c.inv_gamma2);
+      if (lane == 0) face[q] = bi;
+      continue;
     }
-    for (int r = 0; r < 6; ++r) lam[r * n + i] += d[r];
+    const int r = q - 6;  // 0..5 sum g, g u; 6..8 kernel; 9..11 centred difference; 12 strength
+    const double* p = in.geo + r * (int64_t)in.nblocks;
+    int nb = in.nblocks, step = 1;
+    if (r >= 12) {
+      p = in.dk;
+    } else if (r >= 9) {
+      p = in.div + (r - 9) * (int64_t)in.ndiv;
+      nb = in.ndiv;
+    } else if (r >= 6) {
+      p = in.dot + (r - 6);
+      nb = in.ndots;
+      step = 3;
+    }
+    double t = 0.0;
+    for (int b = lane; b < nb; b += 64) t += p[b * step];
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
+    if (lane == 0) sum[r] = t;
   }
-  if (sl.dk_kind != kDkNone) dk[sl.elem] += acc;
+  __syncthreads();
+  if (wave != 0) return;
+  const int64_t n = c.n;
+  const int a = lane % 3;
+  double acc = 0.0;
+  if (lane < 6) {
+    const double nodes[3] = {(double)c.nx, (double)c.ny, (double)c.nz};
+    const double dhr = a == 2 ? c.gamma : 1.0;  // d h'_a / d h_a
+    const double dJ_do = -sum[a];
+    const double dJ_dhr = sum[6 + a] - sum[9 + a] / g->h_rest[a];
+    const double dJ_dh = -sum[3 + a] + dJ_dhr * dhr;
+    const double m = nodes[a] - 3.5;
+    const double dface = lane < 3 ? dJ_do * (1.0 + 1.25 / m) - dJ_dh / m
+                                  : -dJ_do * 1.25 / m + dJ_dh / m;
+    const int64_t i = face[lane];
+    if (i >= 0 && i < n) {  // else no particle (cannot happen for n >= 1)
+      double d[6];
+      for (int r = 0; r < 6; ++r) d[r] = r == 2 * a ? dface : 0.0;
+      if (sl.first.type == kHalfThinDrift) {
+        const double ell = sl.first.ell;
+        d[1] += ell * d[0];
+        d[3] += ell * d[2];
+        d[5] += ell * d[4] * c.inv_gamma2;
+        acc += -X[i] * d[1] + X[2 * n + i] * d[3];
+        d[0] -= sl.first.k * d[1];
+        d[2] += sl.first.k * d[3];
+      } else {
+        if (sl.dk_kind == kDkMatrix) {
+          const double v[4] = {X[i], X[n + i], X[2 * n + i], X[3 * n + i]};
+          acc += plane_form(d, sl.dfx, sl.dfy, v);
+        }
+        apply_half_T(sl.first, d, c.inv_gamma2);
+      }
+      // one particle may lie on several faces
+      for (int r = 0; r < 6; ++r) unsafeAtomicAdd(&lam[r * n + i], d[r]);
+    }
+  }
+  for (int off = 4; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  if (lane == 0 && sl.dk_kind != kDkNone) dk[sl.elem] += sum[12] + acc;
 }
 
 // dk[slot] += sum of the per-block partials: one wave, lane l sums partials l, l + 64, ...,
@@ -624,28 +647,23 @@ hipError_t launch_adj_dk_second(const double* Xnext, const double* lam, Consts c
 
 template <typename T>
 hipError_t launch_adj_a(const double* X, double* lam, const Geom* g, Consts c,
-                        const AdjSlice& sl, T* e, double* ext_partial, double* geo,
-                        hipStream_t s) {
+                        const AdjSlice& sl, T* e, AdjParts* parts, hipStream_t s) {
   const int nb = grid_for(c.n);
   if (c.shape == 1)
     hipLaunchKernelGGL((k_adj_a<1, T>), dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, e,
-                       ext_partial);
+                       parts->ext);
   else
     hipLaunchKernelGGL((k_adj_a<2, T>), dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, e,
-                       ext_partial);
-  PIC_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_ext_combine, dim3(6), dim3(64), 0, s, ext_partial, nb, geo);
+                       parts->ext);
   return hipGetLastError();
 }
 
 hipError_t launch_adj_stage(const double* X, double* lam, const Geom* g, Consts c,
-                            const AdjSlice& sl, double* P, AdjRecord* recs, double* ext_partial,
-                            double* geo, hipStream_t s) {
+                            const AdjSlice& sl, double* P, AdjRecord* recs, AdjParts* parts,
+                            hipStream_t s) {
   const int nb = grid_for(c.n);
   hipLaunchKernelGGL(k_adj_stage, dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, P, recs,
-                     ext_partial);
-  PIC_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_ext_combine, dim3(6), dim3(64), 0, s, ext_partial, nb, geo);
+                     parts->ext);
   return hipGetLastError();
 }
 
@@ -665,13 +683,12 @@ hipError_t launch_grid_dot(const T* a, const T* b, int64_t count, double* partia
 }
 
 template <typename T>
-hipError_t launch_field_dot(const T* e, const T* F, int64_t nodes, double* partial, double* out,
+hipError_t launch_field_dot(const T* e, const T* F, int64_t nodes, AdjParts* parts,
                             hipStream_t s) {
-  const int nb = grid_for(nodes);
-  hipLaunchKernelGGL((k_field_dot<T>), dim3(nb), dim3(kBlk), 0, s, e, (const Node4<T>*)F, nodes,
-                     partial);
-  PIC_TRY(hipGetLastError());
-  return launch_combine_cols(partial, nb, 1, nb, 3, out, s);
+  parts->ndiv = grid_for(nodes);
+  hipLaunchKernelGGL((k_field_dot<T>), dim3(parts->ndiv), dim3(kBlk), 0, s, e,
+                     (const Node4<T>*)F, nodes, parts->div);
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -694,9 +711,10 @@ hipError_t launch_pack_chi(const Geom* g, const T* chi, T* F, int64_t nodes, hip
   return hipGetLastError();
 }
 
-hipError_t launch_adj_geom(const double* X, double* lam, const Geom* g, Consts c,
-                           const AdjSlice& sl, const double* geo, double* dk, hipStream_t s) {
-  hipLaunchKernelGGL(k_adj_geom, dim3(1), dim3(64), 0, s, X, lam, g, c, sl, geo, dk);
+hipError_t launch_adj_finish(const double* X, double* lam, const Geom* g, Consts c,
+                             const AdjSlice& sl, const AdjParts& parts, double* dk,
+                             hipStream_t s) {
+  hipLaunchKernelGGL(k_adj_finish, dim3(1), dim3(1024), 0, s, X, lam, g, c, sl, parts, dk);
   return hipGetLastError();
 }
 
@@ -711,20 +729,16 @@ hipError_t launch_adj_div(const Geom* g, const T* e, T* psi, int nx, int ny, int
 
 template <typename T>
 hipError_t launch_adj_b(const double* X, double* lam, const Geom* g, Consts c, const AdjSlice& sl,
-                        const T* F, double* dk_partial, double* dk,
-                        double* geo_partial, double* geo, hipStream_t s) {
+                        const T* F, AdjParts* parts, hipStream_t s) {
   const int nb = grid_for(c.n);
+  parts->nblocks = nb;
   if (c.shape == 1)
     hipLaunchKernelGGL((k_adj_b<1, T>), dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl,
-                       (const Node4<T>*)F, dk_partial, geo_partial);
+                       (const Node4<T>*)F, parts->dk, parts->geo);
   else
     hipLaunchKernelGGL((k_adj_b<2, T>), dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl,
-                       (const Node4<T>*)F, dk_partial, geo_partial);
-  PIC_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_adj_dk_combine, dim3(1), dim3(64), 0, s, dk_partial, nb, dk, sl.elem);
-  PIC_TRY(hipGetLastError());
-  // geo_partial[q nb + b] (q = 0..5) summed over the blocks into geo[6 + q]
-  return launch_combine_cols(geo_partial, nb, 1, nb, 6, geo + 6, s);
+                       (const Node4<T>*)F, parts->dk, parts->geo);
+  return hipGetLastError();
 }
 
 hipError_t launch_obj_grad(const double* X, int64_t n, const double* mom, const double w[4],
@@ -751,19 +765,19 @@ hipError_t launch_dL(const double* lam, const double* xi, int64_t n, double* par
 }
 
 template hipError_t launch_adj_a<double>(const double*, double*, const Geom*, Consts,
-                                         const AdjSlice&, double*, double*, double*, hipStream_t);
+                                         const AdjSlice&, double*, AdjParts*, hipStream_t);
 template hipError_t launch_adj_a<float>(const double*, double*, const Geom*, Consts,
-                                        const AdjSlice&, float*, double*, double*, hipStream_t);
+                                         const AdjSlice&, float*, AdjParts*, hipStream_t);
 template hipError_t launch_grid_dot<double>(const double*, const double*, int64_t, double*, double*,
                                             hipStream_t);
-template hipError_t launch_field_dot<double>(const double*, const double*, int64_t, double*, double*,
+template hipError_t launch_field_dot<double>(const double*, const double*, int64_t, AdjParts*,
                                              hipStream_t);
 template hipError_t launch_pack_field<double>(const Geom*, const double*, const double*, double*, int, int,
                                               int, hipStream_t);
 template hipError_t launch_pack_chi<double>(const Geom*, const double*, double*, int64_t, hipStream_t);
 template hipError_t launch_grid_dot<float>(const float*, const float*, int64_t, double*, double*,
                                             hipStream_t);
-template hipError_t launch_field_dot<float>(const float*, const float*, int64_t, double*, double*,
+template hipError_t launch_field_dot<float>(const float*, const float*, int64_t, AdjParts*,
                                              hipStream_t);
 template hipError_t launch_pack_field<float>(const Geom*, const float*, const float*, float*, int, int,
                                               int, hipStream_t);
@@ -773,10 +787,8 @@ template hipError_t launch_adj_div<double>(const Geom*, const double*, double*, 
 template hipError_t launch_adj_div<float>(const Geom*, const float*, float*, int, int, int,
                                           hipStream_t);
 template hipError_t launch_adj_b<double>(const double*, double*, const Geom*, Consts,
-                                         const AdjSlice&, const double*, double*, double*,
-                                         double*, double*, hipStream_t);
+                                         const AdjSlice&, const double*, AdjParts*, hipStream_t);
 template hipError_t launch_adj_b<float>(const double*, double*, const Geom*, Consts,
-                                        const AdjSlice&, const float*, double*, double*, double*,
-                                        double*, hipStream_t);
+                                         const AdjSlice&, const float*, AdjParts*, hipStream_t);
 
 }  // namespace pic

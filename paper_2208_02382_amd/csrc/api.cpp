@@ -558,7 +558,7 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
 struct AdjLayout {
   size_t geoms, ckpt, segX, segE, segG, segQ, e, psi, chi, chi2, qhat, stage, dk, dk_part, dL_part,
       small;
-  size_t ext_part, geo_part, dot_part, geo, dc, dgd, dgh, total;
+  size_t ext_part, geo_part, dot_part, div_part, dc, dgd, dgh, total;
   int nseg;
 };
 
@@ -596,7 +596,7 @@ AdjLayout adj_layout(const pic_beam_desc* d, int n_steps, int ck) {
   A.ext_part = take(sizeof(double) * 12 * kAdjBlocks);
   A.geo_part = take(sizeof(double) * 6 * kAdjBlocks);
   A.dot_part = take(sizeof(double) * 3 * kAdjBlocks);
-  A.geo = take(sizeof(double) * 32);
+  A.div_part = take(sizeof(double) * 3 * kAdjBlocks);
   A.stage = take(6 * sizeof(double) * n);
   A.dk = take(sizeof(double) * kMaxLattice);
   A.dk_part = take(sizeof(double) * kAdjBlocks);
@@ -764,10 +764,10 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
   T* psi = (T*)(aw + A.psi);
   T* chi = (T*)(aw + A.chi);
   T* chi2 = (T*)(aw + A.chi2);
-  double* geo = (double*)(aw + A.geo);
-  double* ext_part = (double*)(aw + A.ext_part);
-  double* geo_part = (double*)(aw + A.geo_part);
   double* dot_part = (double*)(aw + A.dot_part);
+  const AdjParts no_parts{(double*)(aw + A.ext_part), (double*)(aw + A.geo_part),
+                          (double*)(aw + A.dk_part),  dot_part,
+                          (double*)(aw + A.div_part), 0, 0, 0};
   T* dgh = (T*)(aw + A.dgh);
   const size_t G1 = (size_t)(b->d.nx + 1) * (b->d.ny + 1) * (b->d.nz + 1);
   double* dk = (double*)(aw + A.dk);
@@ -827,6 +827,7 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
       // the vector deposit (all of them last read by the step before the fork)
       const T* Qj = segQ + ng * (size_t)q;
       bool dots = false;
+      AdjParts parts = no_parts;
       HIP_OK(hipEventRecord(b->ev_fork, s), "fork");
       HIP_OK(hipStreamWaitEvent(b->aux, b->ev_fork, 0), "fork");
       HIP_OK(launch_green_dh_spectra<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, direct,
@@ -844,7 +845,7 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
         // kick-point positions and deposit values (the records in XB, free here), their ranking,
         // then the binned vector deposit
         AdjRecord* recs = (AdjRecord*)b->XB;
-        HIP_OK(launch_adj_stage(Xs, lam, geom(j), b->c, el, P, recs, ext_part, geo, s),
+        HIP_OK(launch_adj_stage(Xs, lam, geom(j), b->c, el, P, recs, &parts, s),
                "adjoint");
         HIP_OK(launch_bin_perm(P, geom(j), b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks,
                                b->nchunks, b->perm, s),
@@ -853,10 +854,9 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
                                         b->nchunks, e, s),
                "adjoint");
       } else {
-        HIP_OK(launch_adj_a<T>(Xs, lam, geom(j), b->c, el, e, ext_part, geo, s), "adjoint");
+        HIP_OK(launch_adj_a<T>(Xs, lam, geom(j), b->c, el, e, &parts, s), "adjoint");
       }
       HIP_OK(hipStreamWaitEvent(s, b->ev_join, 0), "join");
-      int ndots = 0;
       if (direct) {  // transposed field convolutions, b->E as their scratch
         HIP_OK(launch_solve_field_T<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, e, b->W, b->W2,
                                        segG + G3 * (size_t)q, (T*)b->E, chi, s),
@@ -867,20 +867,16 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
         HIP_OK(launch_solve_ghost_dots<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, psi, b->W,
                                           segG + G3 * (size_t)q, chi,
                                           dots ? aw + A.qhat : nullptr, dgh, dot_part,
-                                          kAdjBlocks, &ndots, s),
+                                          kAdjBlocks, &parts.ndots, s),
                "adjoint");
       }
       T* F = segE + 4 * ng * (size_t)q;
       HIP_OK(launch_pack_chi<T>(geom(j), chi, F, ng, s), "adjoint");
-      HIP_OK(launch_adj_b<T>(Xs, lam, geom(j), b->c, el, F, (double*)(aw + A.dk_part), dk, geo_part,
-                             geo, s),
-             "adjoint");
+      HIP_OK(launch_adj_b<T>(Xs, lam, geom(j), b->c, el, F, &parts, s), "adjoint");
       // the geometry's terms: dJ/dh' through the kernel (the h-derivative kernels' convolution
-      // with the adjoint source, dotted with the step's charge) into geo[12..14], and through
-      // the centred difference sum_n e_b E'_b into geo[15..17] (zero for the direct field)
-      if (ndots)
-        HIP_OK(launch_combine_cols(dot_part, ndots, 3, 1, 3, geo + 12, s), "adjoint geometry");
-      for (int hb = 0; hb < 3 && !ndots; ++hb) {
+      // with the adjoint source, dotted with the step's charge), already there or formed here,
+      // and through the centred difference sum_n e_b E'_b (none for the direct field)
+      for (int hb = 0; hb < 3 && !dots; ++hb) {
         if (direct)
           HIP_OK(launch_solve_field_T<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, e, b->W,
                                          b->W2, dgh + 3 * G1 * (size_t)hb, (T*)b->E, chi2, s),
@@ -889,15 +885,11 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
           HIP_OK(launch_solve_ghost_source<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, psi,
                                               b->W, dgh + G1 * (size_t)hb, chi2, s),
                  "adjoint geometry");
-        HIP_OK(launch_grid_dot<T>(Qj, chi2, ng, dot_part, geo + 12 + hb, s),
-               "adjoint geometry");
+        HIP_OK(launch_grid_dot<T>(Qj, chi2, ng, parts.div, dot_part + hb, s), "adjoint geometry");
+        parts.ndots = 1;
       }
-      if (direct)
-        HIP_OK(launch_zero<double>(geo + 15, 3, s), "adjoint geometry");
-      else
-        HIP_OK(launch_field_dot<T>(e, F, ng, dot_part, geo + 15, s),
-               "adjoint geometry");
-      HIP_OK(launch_adj_geom(Xs, lam, geom(j), b->c, el, geo, dk, s), "adjoint geometry");
+      if (!direct) HIP_OK(launch_field_dot<T>(e, F, ng, &parts, s), "adjoint geometry");
+      HIP_OK(launch_adj_finish(Xs, lam, geom(j), b->c, el, parts, dk, s), "adjoint geometry");
     }
   }
   if (xi)

@@ -337,30 +337,36 @@ hipError_t launch_adj_dk_second(const double* Xnext, const double* lam, Consts c
 struct alignas(16) AdjRecord {
   double r[3], a[3];
 };
-// launch_adj_a and launch_adj_stage also find the particles at the box's min and max of the
-// kick-point positions (the first index for a tie): their indices into geo[0..5] (x, y, z min,
-// then max), ext_partial (12 doubles per block) as scratch
+// Block partials of a reverse step, which launch_adj_finish sums: per block of the particle kernels
+// (nblocks) ext [12] the particles at the box's min and max of the kick-point positions (the first
+// index for a tie), geo [6][nblocks] sum g_a and sum g_a u_a, dk the first half map's strength term;
+// dot [ndots][3] the geometry's sums through the kernel; div [3][ndiv] sum_n e_b E'_b (ndiv = 0:
+// none, direct field)
+struct AdjParts {
+  double *ext, *geo, *dk, *dot, *div;
+  int nblocks, ndots, ndiv;
+};
+// launch_adj_a and launch_adj_stage fill ext
 template <typename T>
 hipError_t launch_adj_a(const double* X, double* lam, const Geom* g, Consts c,
-                        const AdjSlice& sl, T* e, double* ext_partial, double* geo,
-                        hipStream_t s);
+                        const AdjSlice& sl, T* e, AdjParts* parts, hipStream_t s);
 hipError_t launch_adj_stage(const double* X, double* lam, const Geom* g, Consts c,
-                            const AdjSlice& sl, double* P, AdjRecord* recs, double* ext_partial,
-                            double* geo, hipStream_t s);
+                            const AdjSlice& sl, double* P, AdjRecord* recs, AdjParts* parts,
+                            hipStream_t s);
 // *out = sum_i a[i] b[i], i < count, in a fixed order; partial holds a double per block
 template <typename T>
 hipError_t launch_grid_dot(const T* a, const T* b, int64_t count, double* partial, double* out,
                            hipStream_t s);
-// out[c] = sum_i e[c nodes + i] F_i.c, c < 3; partial holds 3 doubles per block
+// sum_i e[c nodes + i] F_i.c, c < 3, into parts->div
 template <typename T>
-hipError_t launch_field_dot(const T* e, const T* F, int64_t nodes, double* partial, double* out,
+hipError_t launch_field_dot(const T* e, const T* F, int64_t nodes, AdjParts* parts,
                             hipStream_t s);
 // out[c] = sum_b partial[b sb + c sq], b < nblocks, c < ncols, in a fixed order
 hipError_t launch_combine_cols(const double* partial, int nblocks, int64_t sb, int64_t sq,
                                int ncols, double* out, hipStream_t s);
-// the geometry's terms of a reverse step from geo (see adjoint.hip) into lam and dk
-hipError_t launch_adj_geom(const double* X, double* lam, const Geom* g, Consts c,
-                           const AdjSlice& sl, const double* geo, double* dk, hipStream_t s);
+// the end of a reverse step (see adjoint.hip): into lam and dk[sl.elem]
+hipError_t launch_adj_finish(const double* X, double* lam, const Geom* g, Consts c,
+                             const AdjSlice& sl, const AdjParts& parts, double* dk, hipStream_t s);
 // vector deposit of the records through their ranking; an error if the three float64 windows exceed the LDS a workgroup may use
 template <typename T>
 hipError_t launch_vdeposit_tiles(const AdjRecord* recs, const uint32_t* perm,
@@ -369,12 +375,10 @@ hipError_t launch_vdeposit_tiles(const AdjRecord* recs, const uint32_t* perm,
 template <typename T>
 hipError_t launch_adj_div(const Geom* g, const T* e, T* psi, int nx, int ny, int nz,
                           hipStream_t s);
-// F: (E', chi) per node.  Also the per-block sums of g_a and g_a u_a (6 kAdjBlocks doubles of
-// geo_partial) into geo[6..11]
+// F: (E', chi) per node; fills geo and dk of parts
 template <typename T>
 hipError_t launch_adj_b(const double* X, double* lam, const Geom* g, Consts c, const AdjSlice& sl,
-                        const T* F, double* dk_partial, double* dk,
-                        double* geo_partial, double* geo, hipStream_t s);
+                        const T* F, AdjParts* parts, hipStream_t s);
 // (sigma_x, sigma_y, eps_x, eps_y) from the moments mom (mean 6, covariance upper 21) into
 // the device array out_m[4]
 hipError_t launch_objective(const double* mom, double* out_m, hipStream_t s);
