@@ -1235,7 +1235,7 @@ __global__ __launch_bounds__(kBlk) void k_prologue(const double* __restrict__ X,
 }
 
 // Bucket keys for the return to the caller's order: key = id >> shift (at most 4096 buckets of
-// consecutive original indices), with the block-privatised histogram of k_key_hist.
+// consecutive original indices), with a block-privatised histogram.
 __device__ __forceinline__ void id_hist_body(const uint32_t* __restrict__ ids, int64_t n,
                                                   int shift, int nbuckets,
                                                   uint32_t* __restrict__ keys,
@@ -1729,8 +1729,10 @@ hipError_t launch_gkd_tiles(double* B, const double* src, const uint32_t* perm,
   // With diagnostics each workgroup ends with a reduction of its 27 sums, so fewer, longer ones pay
   // although they balance less well.  Measured, us, at 512 / 768 / 2048 / 4096 workgroups:
   // 1e5 TSC 48^3 32 / 37 / 58 / 93; 1e6 TSC 64^3 70 / 71 / 89 / 117; 4e6 TSC 96^3 224 / 207 / 233 /
-  // 253; 1.25e7 TSC 128^3 590 / 533 / 580 / 576; 4e7 CIC 128^3 1584 / 1735 / 1781 / 1618.
-  const int diag_blocks = c.n <= (1 << 21) ? 512 : 768;
+  // 253; 1.25e7 TSC 128^3 590 / 533 / 580 / 576.  Beyond 2^25 the reduction is paid back in any
+  // workgroup and balance counts: 5e7 2494 (768) / 2523 (the plan's), 1e8 with 16384-particle work
+  // items 4491 / 4078.
+  const int diag_blocks = c.n <= (1 << 21) ? 512 : (c.n <= (1 << 25) ? 768 : sp.blocks);
   const dim3 grid((unsigned)(diag ? std::min(sp.blocks, diag_blocks) : sp.blocks)),
       block((unsigned)(diag ? std::min(sp.threads, kDiagThreads) : sp.threads));
   // the ids are optional, as a pair

@@ -1,11 +1,11 @@
 """The slice-step diagnostics against float64 moments of the state they describe, at a few particles,
-around a wavefront, and on both sides of the particle count where the workgroup count changes; a
+around a wavefront, and on both sides of the particle counts where the workgroup count changes; a
 second run on the same beam finds the accumulators of the first.
 
-Tolerance: the sums have at most n / (512 * 256) + 200 terms in a row, so each carries under 250
-rounding errors of 1.1e-16 relative to the sum of its terms' magnitudes, 3e-14; the shift (grid
+Tolerance: the sums have at most n / (512 * 256) + 200 terms in a row, so each carries under 460
+rounding errors of 1.1e-16 relative to the sum of its terms' magnitudes, 5e-14; the shift (grid
 centre, then the previous step's mean) lies within about an rms of the mean for these beams, which
-multiplies the centred products' terms by at most 4: 1.2e-13, and 1e-12 is asked of each entry
+multiplies the centred products' terms by at most 4: 2e-13, and 1e-12 is asked of each entry
 relative to its rms product."""
 import pytest
 import torch
@@ -16,7 +16,7 @@ import workloads
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [5, 63, 4097, 1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("n", [5, 63, 4097, 1 << 21, (1 << 21) + 1, 1 << 25, (1 << 25) + 1])
 def test_diagnostics_equal_the_moments_of_the_state(n):
     cfg = workloads.MEDIUM
     b = pic.Beam(n, cfg.qm_qeeV, cfg.charge_C, cfg.kin_energy_MeV, cfg.mass_MeV, 1, (32, 32, 32))
