@@ -298,13 +298,11 @@ __global__ __launch_bounds__(kBlk) void k_adj_a(const double* __restrict__ X,
 
 // Pass A for the binned vector deposit: lam <- (second half map)^T lam, and the particle's
 // kick-point position and a = (C L lam_px, C L lam_py, gamma C L lam_delta) written as a record for
-// the deposit, which reads them in another order; the positions also as the rows 0, 2, 4 of P,
-// which the ranking reads.
+// the deposit, which reads them in another order.
 __global__ __launch_bounds__(kBlk) void k_adj_stage(const double* __restrict__ X,
                                                     double* __restrict__ lam,
                                                     const Geom* __restrict__ g, Consts c,
-                                                    AdjSlice sl, double* __restrict__ P,
-                                                    AdjRecord* __restrict__ recs,
+                                                    AdjSlice sl, AdjRecord* __restrict__ recs,
                                                     double* __restrict__ ext_partial) {
   if (g->status) return;
   const int64_t n = c.n;
@@ -321,7 +319,6 @@ __global__ __launch_bounds__(kBlk) void k_adj_stage(const double* __restrict__ X
     apply_half_T(sl.second, lm, c.inv_gamma2);
     for (int q = 0; q < 6; ++q) lam[q * n + i] = lm[q];
     const double a[3] = {c.C * L * lm[1], c.C * L * lm[3], c.gamma * c.C * L * lm[5]};
-    for (int q = 0; q < 3; ++q) P[2 * q * n + i] = r[q];
     recs[i] = {{r[0], r[1], r[2]}, {a[0], a[1], a[2]}};
   }
   ext_block_partial(ex, ext_partial);
@@ -659,10 +656,9 @@ hipError_t launch_adj_a(const double* X, double* lam, const Geom* g, Consts c,
 }
 
 hipError_t launch_adj_stage(const double* X, double* lam, const Geom* g, Consts c,
-                            const AdjSlice& sl, double* P, AdjRecord* recs, AdjParts* parts,
-                            hipStream_t s) {
+                            const AdjSlice& sl, AdjRecord* recs, AdjParts* parts, hipStream_t s) {
   const int nb = grid_for(c.n);
-  hipLaunchKernelGGL(k_adj_stage, dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, P, recs,
+  hipLaunchKernelGGL(k_adj_stage, dim3(nb), dim3(kBlk), 0, s, X, lam, g, c, sl, recs,
                      parts->ext);
   return hipGetLastError();
 }

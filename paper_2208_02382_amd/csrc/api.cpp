@@ -556,8 +556,9 @@ pic_status track_sc(pic_beam b, const std::vector<SliceDev>& sl, int n_steps, do
 
 // ---- reverse sweep workspace (caller-owned, see pic_adjoint_workspace_bytes)
 struct AdjLayout {
-  size_t geoms, ckpt, segX, segE, segG, segQ, e, psi, chi, chi2, qhat, stage, dk, dk_part, dL_part,
-      small;
+  size_t geoms, ckpt, segX, segE, segG, segQ, perm, chunks, nchunks, e, psi, chi, chi2, qhat, dk,
+      dk_part, dL_part, small;
+  int64_t max_chunks;  // work-list entries per step
   size_t ext_part, geo_part, dot_part, div_part, dc, dgd, dgh, total;
   int nseg;
 };
@@ -582,6 +583,13 @@ AdjLayout adj_layout(const pic_beam_desc* d, int n_steps, int ck) {
   A.segE = take(4 * es * ng * (size_t)ck);  // the step's field and chi, packed per node
   A.segG = take(es * G3 * (size_t)ck * (d->direct_field ? 3 : 1));  // the step's kernel spectra
   A.segQ = take(es * ng * (size_t)ck);                                // the step's charge grid
+  // the step's ranking and work list
+  const SortPlan sp = make_sort_plan(d->nx, d->ny, d->nz, d->n, d->tile, d->chunk, d->blocks,
+                                     d->threads);
+  A.max_chunks = sp.max_chunks;
+  A.perm = take(sizeof(uint32_t) * n * (size_t)ck);
+  A.chunks = take(sizeof(int4) * (size_t)sp.max_chunks * ck);
+  A.nchunks = take(sizeof(uint32_t) * kNckWords * ck);
   A.e = take(3 * es * ng);
   A.psi = take(es * (nx + 2) * (ny + 2) * (nz + 2));
   A.chi = take(es * ng);
@@ -597,7 +605,6 @@ AdjLayout adj_layout(const pic_beam_desc* d, int n_steps, int ck) {
   A.geo_part = take(sizeof(double) * 6 * kAdjBlocks);
   A.dot_part = take(sizeof(double) * 3 * kAdjBlocks);
   A.div_part = take(sizeof(double) * 3 * kAdjBlocks);
-  A.stage = take(6 * sizeof(double) * n);
   A.dk = take(sizeof(double) * kMaxLattice);
   A.dk_part = take(sizeof(double) * kAdjBlocks);
   A.dL_part = take(sizeof(double) * 36 * kAdjBlocks);
@@ -693,14 +700,23 @@ pic_status expand_adjoint(const pic_element* lat, int n_el, std::vector<AdjSlice
   return PIC_OK;
 }
 
+// ranking and work list of a step's kick-point state (see launch_bin_perm)
+struct AdjBins {
+  uint32_t* perm;
+  int4* chunks;
+  uint32_t* nchunks;
+};
+
 // One step of the reverse sweep's forward pass, in the caller's particle order: from the state src
 // to the state dst (b->XA in between, which holds the kick-point state; dst == nullptr: no state,
-// only the grids), keeping the charge grid rho, the packed field F and the kernel spectra gh.  g is the
+// only the grids), keeping the charge grid rho, the packed field F, the kernel spectra gh and the
+// ranking and work list bins of the kick-point state.  g is the
 // step's geometry slot, computed when box is given.  The Green spectrum runs on the auxiliary
 // stream beside the binning and the deposit; what it writes was last read before the fork.
 template <typename T>
 pic_status forward_step_recorded(pic_beam b, const double* src, double* dst, Geom* g,
-                                 const AdjSlice& e, T* gh, T* F, T* rho, hipStream_t s, Box* box) {
+                                 const AdjSlice& e, T* gh, T* F, T* rho, const AdjBins& bins,
+                                 hipStream_t s, Box* box) {
   double* X = b->XA;
   HIP_OK(launch_half_box(src, X, e.first, b->c, box, s), "adjoint forward");
   if (box) HIP_OK(launch_geometry(box, g, b->c, s), "adjoint forward");
@@ -718,10 +734,10 @@ pic_status forward_step_recorded(pic_beam b, const double* src, double* dst, Geo
   // The deposit reads the caller's order through its ranking: a copy in tile order cost more at
   // every size (a sweep ranked / copied, ms: 20 steps of 1e5 CIC 32^3 6.2 / 8.2, of 1e6 CIC 64^3
   // 15.2 / 15.7, 6 steps of 4e6 TSC 64^3 19.7 / 20.9; with AdjRecord of 1e7 CIC 128^3 27.5 / 28.8).
-  HIP_OK(launch_bin_perm(X, g, b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks, b->nchunks,
-                         b->perm, s),
+  HIP_OK(launch_bin_perm(X, g, b->c, b->sp, b->keys, b->hist, b->cursor, bins.chunks,
+                         bins.nchunks, bins.perm, s),
          "adjoint forward");
-  HIP_OK(launch_deposit_tiles<T>(X, b->perm, g, b->c, b->sp, b->chunks, b->nchunks, rho, s,
+  HIP_OK(launch_deposit_tiles<T>(X, bins.perm, g, b->c, b->sp, bins.chunks, bins.nchunks, rho, s,
                                  b->tacc, b->tscale),
          "adjoint forward");
   HIP_OK(hipStreamWaitEvent(s, b->ev_join, 0), "join");
@@ -772,7 +788,11 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
   const size_t G1 = (size_t)(b->d.nx + 1) * (b->d.ny + 1) * (b->d.nz + 1);
   double* dk = (double*)(aw + A.dk);
   double* small = (double*)(aw + A.small);
-  double* P = (double*)(aw + A.stage);
+  auto bins = [&](int j) {
+    const size_t q = (size_t)(j % ck);
+    return AdjBins{(uint32_t*)(aw + A.perm) + n * q, (int4*)(aw + A.chunks) + A.max_chunks * q,
+                   (uint32_t*)(aw + A.nchunks) + kNckWords * q};
+  };
   // the binned vector deposit keeps three float64 windows of a tile in LDS (up to 156 KB)
   const int S = b->d.shape;
   const bool vtiles =
@@ -780,6 +800,8 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
   HIP_OK(launch_zero<uint32_t>((uint32_t*)(aw + A.geoms), (int64_t)(kGeomSlot / 4) * n_steps, s),
          "adjoint setup");
   HIP_OK(launch_zero<double>(dk, kMaxLattice, s), "adjoint setup");
+  HIP_OK(launch_zero<uint32_t>((uint32_t*)(aw + A.nchunks), (int64_t)kNckWords * ck, s),
+         "adjoint setup");
   // The state at the start of step j of the segment being swept: a segment's first in its
   // checkpoint, the others in segX; the final one in X.
   auto state = [&](int j) -> double* {
@@ -791,7 +813,7 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
     const size_t q = (size_t)(j % ck);
     return forward_step_recorded<T>(b, state(j), last ? nullptr : state(j + 1), geom(j),
                                     sl[j % nsl], segG + G3 * q, segE + 4 * ng * q, segQ + ng * q,
-                                    s, box);
+                                    bins(j), s, box);
   };
   // forward: the checkpoints and the geometry of every step kept, and all of the last segment
   // (the first to be swept, so it need not be computed again).  1e6 particles, 64^3, 20 steps, a
@@ -805,7 +827,8 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
         j < last_seg
             ? forward_step_recorded<T>(b, j % ck ? b->X : state(j), (j + 1) % ck ? b->X : state(j + 1),
                                        geom(j), sl[j % nsl], direct ? (T*)b->gh3 : (T*)b->Gh,
-                                       segE, (T*)b->rho, s, b->box)
+                                       segE, (T*)b->rho,
+                                       AdjBins{b->perm, b->chunks, b->nchunks}, s, b->box)
             : recorded_step(j, b->box, false);
     if (st != PIC_OK) return st;
   }
@@ -842,16 +865,13 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
              "adjoint");
       HIP_OK(launch_zero<T>(e, 3 * ng, s), "adjoint");
       if (vtiles) {
-        // kick-point positions and deposit values (the records in XB, free here), their ranking,
-        // then the binned vector deposit
+        // kick-point positions and deposit values as records (in XB, free here), then the binned
+        // vector deposit through the ranking that the forward pass kept
         AdjRecord* recs = (AdjRecord*)b->XB;
-        HIP_OK(launch_adj_stage(Xs, lam, geom(j), b->c, el, P, recs, &parts, s),
-               "adjoint");
-        HIP_OK(launch_bin_perm(P, geom(j), b->c, b->sp, b->keys, b->hist, b->cursor, b->chunks,
-                               b->nchunks, b->perm, s),
-               "adjoint");
-        HIP_OK(launch_vdeposit_tiles<T>(recs, b->perm, geom(j), b->c, b->sp, b->chunks,
-                                        b->nchunks, e, s),
+        const AdjBins bj = bins(j);
+        HIP_OK(launch_adj_stage(Xs, lam, geom(j), b->c, el, recs, &parts, s), "adjoint");
+        HIP_OK(launch_vdeposit_tiles<T>(recs, bj.perm, geom(j), b->c, b->sp, bj.chunks, bj.nchunks,
+                                        e, s),
                "adjoint");
       } else {
         HIP_OK(launch_adj_a<T>(Xs, lam, geom(j), b->c, el, e, &parts, s), "adjoint");

@@ -351,8 +351,7 @@ template <typename T>
 hipError_t launch_adj_a(const double* X, double* lam, const Geom* g, Consts c,
                         const AdjSlice& sl, T* e, AdjParts* parts, hipStream_t s);
 hipError_t launch_adj_stage(const double* X, double* lam, const Geom* g, Consts c,
-                            const AdjSlice& sl, double* P, AdjRecord* recs, AdjParts* parts,
-                            hipStream_t s);
+                            const AdjSlice& sl, AdjRecord* recs, AdjParts* parts, hipStream_t s);
 // *out = sum_i a[i] b[i], i < count, in a fixed order; partial holds a double per block
 template <typename T>
 hipError_t launch_grid_dot(const T* a, const T* b, int64_t count, double* partial, double* out,
