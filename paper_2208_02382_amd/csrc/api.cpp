@@ -834,6 +834,27 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
   }
   HIP_OK(launch_moments(b->X, b->d.n, b->mom_partial, b->mom_out, s), "adjoint objective");
   HIP_OK(launch_obj_grad(b->X, b->d.n, b->mom_out, w, lam, small, s), "adjoint objective");
+  // The h-derivatives' spectra of step j and its charge grid's transform, on the auxiliary stream
+  // beside the vector deposit of this step.  Up to 2^22 particles they start where the step after
+  // it has read its own spectra, beside the rest of that step too; beyond, k_adj_b's reads then
+  // lose more than that hides.  From there / from that step's end, ms: 20 steps of 1e6 CIC 64^3
+  // 12.80 / 13.16, of 1e6 CIC 128^3 30.6 / 31.4; 6 steps of 4e6 TSC 64^3 12.91 / 12.95, of 1e7 CIC
+  // 128^3 27.1 / 26.0.
+  bool dots = false;
+  const bool fork_early = b->c.n <= (1 << 22);
+  auto fork_geometry = [&](int j) -> pic_status {
+    HIP_OK(hipEventRecord(b->ev_fork, s), "fork");
+    HIP_OK(hipStreamWaitEvent(b->aux, b->ev_fork, 0), "fork");
+    HIP_OK(launch_green_dh_spectra<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, direct,
+                                      (double2*)(aw + A.dc), (double*)(aw + A.dgd), dgh, b->aux),
+           "adjoint geometry");
+    if (!direct)
+      HIP_OK(launch_charge_spectrum<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz,
+                                       segQ + ng * (size_t)(j % ck), aw + A.qhat, &dots, b->aux),
+             "adjoint geometry");
+    HIP_OK(hipEventRecord(b->ev_join, b->aux), "join");
+    return PIC_OK;
+  };
   // reverse, one checkpoint segment at a time
   for (int seg = A.nseg - 1; seg >= 0; --seg) {
     const int c0 = seg * ck, c1 = std::min(c0 + ck, n_steps);
@@ -841,26 +862,15 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
       pic_status st = recorded_step(j, nullptr, j + 1 == c1);
       if (st != PIC_OK) return st;
     }
+    pic_status fst = fork_geometry(c1 - 1);
+    if (fst != PIC_OK) return fst;
     for (int j = c1 - 1; j >= c0; --j) {
       const int q = j - c0;
       const AdjSlice& el = sl[j % nsl];
       const double* Xs = state(j);
       const double* Xn = state(j + 1);
-      // The h-derivatives' spectra and the charge grid's transform on the auxiliary stream beside
-      // the vector deposit (all of them last read by the step before the fork)
       const T* Qj = segQ + ng * (size_t)q;
-      bool dots = false;
       AdjParts parts = no_parts;
-      HIP_OK(hipEventRecord(b->ev_fork, s), "fork");
-      HIP_OK(hipStreamWaitEvent(b->aux, b->ev_fork, 0), "fork");
-      HIP_OK(launch_green_dh_spectra<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, direct,
-                                        (double2*)(aw + A.dc), (double*)(aw + A.dgd), dgh, b->aux),
-             "adjoint geometry");
-      if (!direct)
-        HIP_OK(launch_charge_spectrum<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, Qj,
-                                         aw + A.qhat, &dots, b->aux),
-               "adjoint geometry");
-      HIP_OK(hipEventRecord(b->ev_join, b->aux), "join");
       HIP_OK(launch_adj_dk_second(Xn, lam, b->c, el, (double*)(aw + A.dk_part), dk, s),
              "adjoint");
       HIP_OK(launch_zero<T>(e, 3 * ng, s), "adjoint");
@@ -890,13 +900,19 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
                                           kAdjBlocks, &parts.ndots, s),
                "adjoint");
       }
+      const bool summed = dots;  // the spectra have been read
+      const bool forked = summed && fork_early;
+      if (forked && j > c0) {
+        fst = fork_geometry(j - 1);
+        if (fst != PIC_OK) return fst;
+      }
       T* F = segE + 4 * ng * (size_t)q;
       HIP_OK(launch_pack_chi<T>(geom(j), chi, F, ng, s), "adjoint");
       HIP_OK(launch_adj_b<T>(Xs, lam, geom(j), b->c, el, F, &parts, s), "adjoint");
       // the geometry's terms: dJ/dh' through the kernel (the h-derivative kernels' convolution
       // with the adjoint source, dotted with the step's charge), already there or formed here,
       // and through the centred difference sum_n e_b E'_b (none for the direct field)
-      for (int hb = 0; hb < 3 && !dots; ++hb) {
+      for (int hb = 0; hb < 3 && !summed; ++hb) {
         if (direct)
           HIP_OK(launch_solve_field_T<T>(geom(j), b->plan, b->d.nx, b->d.ny, b->d.nz, e, b->W,
                                          b->W2, dgh + 3 * G1 * (size_t)hb, (T*)b->E, chi2, s),
@@ -909,6 +925,10 @@ pic_status track_adjoint(pic_beam b, const std::vector<AdjSlice>& sl, int n_el, 
         parts.ndots = 1;
       }
       if (!direct) HIP_OK(launch_field_dot<T>(e, F, ng, &parts, s), "adjoint geometry");
+      if (!forked && j > c0) {
+        fst = fork_geometry(j - 1);
+        if (fst != PIC_OK) return fst;
+      }
       HIP_OK(launch_adj_finish(Xs, lam, geom(j), b->c, el, parts, dk, s), "adjoint geometry");
     }
   }
