@@ -421,7 +421,8 @@ pic_status expand_lattice(const pic_element* lat, int n_el, std::vector<SliceDev
 
 hipError_t call_setup(pic_beam b, hipStream_t s) {
   return launch_call_setup(b->box, b->tacc,
-                           (int64_t)b->sp.ntiles * tile_window_nodes(b->sp, b->d.shape), s);
+                           (int64_t)b->sp.ntiles * tile_window_nodes(b->sp, b->d.shape), b->hist,
+                           b->nchunks, s);
 }
 
 // Green spectrum of the current geometry on the auxiliary stream (joined before the solve)
@@ -1096,8 +1097,6 @@ pic_status pic_beam_create(const pic_beam_desc* d, double* d_X, void* d_work, si
   for (int a = 0; a < 3 && e == hipSuccess; ++a)
     e = launch_twiddles((double2*)b->plan.tw[a], (float2*)b->plan.twf[a], b->plan.full[a].M, s);
   if (e == hipSuccess) e = call_setup(b, s);
-  if (e == hipSuccess) e = launch_zero<uint32_t>(b->hist, kMaxTiles, s);
-  if (e == hipSuccess) e = launch_zero<uint32_t>(b->nchunks, kNckWords, s);
   if (e == hipSuccess) e = launch_clear_status(b->geom, s);
   if (e == hipSuccess) e = make_aux(&b->aux, &b->ev_fork, &b->ev_join, &b->done.ev);
   if (e != hipSuccess) {

@@ -185,9 +185,11 @@ int record_hip_failure(hipError_t e, const char* where);
   } while (0)
 
 // ---- launch wrappers (particles.hip)
-// empties the box and zeroes the deposit's integer windows: once per call (the geometry kernel
-// and each deposit leave them so; a call that ended in an error may not)
-hipError_t launch_call_setup(Box* box, unsigned long long* tacc, int64_t count, hipStream_t s);
+// empties the box and zeroes the deposit's integer windows, the tile histogram and the work list's
+// words: once per call (the geometry kernel, each deposit and each ranking leave them so; a call
+// that ended in an error may not)
+hipError_t launch_call_setup(Box* box, unsigned long long* tacc, int64_t count, uint32_t* hist,
+                             uint32_t* nchunks, hipStream_t s);
 hipError_t launch_box(const double* X, int64_t n, Box* box, hipStream_t s);
 hipError_t launch_geometry(Box* box, Geom* g, Consts c, hipStream_t s);
 hipError_t launch_init_normals(double* X, const double* xi, int64_t n, Chol L, hipStream_t s);

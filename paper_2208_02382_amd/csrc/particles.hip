@@ -24,17 +24,23 @@ int grid_for(int64_t n) {
 // ---------------------------------------------------------------------------- box and geometry
 
 __device__ __forceinline__ void call_setup_body(Box* box, unsigned long long* __restrict__ tacc,
-                                                int64_t count, int blk, int nblk) {
+                                                int64_t count, uint32_t* __restrict__ hist,
+                                                uint32_t* __restrict__ nchunks, int blk,
+                                                int nblk) {
   if (blk == 0 && threadIdx.x < kBoxSlots) box_slot_reset(box->slot + threadIdx.x);
   if (blk == 0 && threadIdx.x == 0) box->done = 0u;
+  if (blk == 0 && threadIdx.x < kNckWords) nchunks[threadIdx.x] = 0u;
+  for (int t = blk * kBlock + (int)threadIdx.x; t < kMaxTiles; t += nblk * kBlock) hist[t] = 0u;
   for (int64_t i = blk * (int64_t)kBlock + threadIdx.x; i < count; i += (int64_t)nblk * kBlock)
     tacc[i] = 0ull;
 }
 
 __global__ __launch_bounds__(kBlock) void k_call_setup(Box* box,
                                                        unsigned long long* __restrict__ tacc,
-                                                       int64_t count) {
-  call_setup_body(box, tacc, count, blockIdx.x, gridDim.x);
+                                                       int64_t count,
+                                                       uint32_t* __restrict__ hist,
+                                                       uint32_t* __restrict__ nchunks) {
+  call_setup_body(box, tacc, count, hist, nchunks, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(kBlock) void k_box(const double* __restrict__ X, int64_t n, Box* box) {
@@ -369,7 +375,7 @@ __global__ __launch_bounds__(kBlock) void k_call_setup_batch(const BeamDev* __re
   const BeamDev& d = beams[blockIdx.y];
   const int S = d.c.shape;
   const int64_t count = (int64_t)d.sp.ntiles * (d.sp.T[0] + S) * (d.sp.T[1] + S) * (d.sp.T[2] + S);
-  call_setup_body(d.box, d.tacc, count, blockIdx.x, gridDim.x);
+  call_setup_body(d.box, d.tacc, count, d.hist, d.nchunks, blockIdx.x, gridDim.x);
 }
 
 }  // namespace
@@ -381,8 +387,10 @@ hipError_t launch_batch_call_setup(const BeamDev* beams, int nb, hipStream_t s) 
   return hipGetLastError();
 }
 
-hipError_t launch_call_setup(Box* box, unsigned long long* tacc, int64_t count, hipStream_t s) {
-  hipLaunchKernelGGL(k_call_setup, dim3(grid_for(count)), dim3(kBlock), 0, s, box, tacc, count);
+hipError_t launch_call_setup(Box* box, unsigned long long* tacc, int64_t count, uint32_t* hist,
+                             uint32_t* nchunks, hipStream_t s) {
+  hipLaunchKernelGGL(k_call_setup, dim3(grid_for(count)), dim3(kBlock), 0, s, box, tacc, count,
+                     hist, nchunks);
   return hipGetLastError();
 }
 

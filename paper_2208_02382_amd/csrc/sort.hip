@@ -107,9 +107,12 @@ constexpr int kNck = 0, kTicket = 1, kOverflow = 2;
 // NT threads; lh: kMaxTiles words of LDS.  Thread t takes tiles t, t + NT, ..., so that the dense
 // tiles in the middle of the grid, whose chunks are many, are spread over the threads.  The
 // counts are read with agent-scope atomic loads: other workgroups of the same launch may have
-// added to them.
+// added to them.  Counts that do not hold every one of the n particles once, or a list that would
+// not fit (neither can be with a histogram that started at zero), are a fault of the library: no
+// list is written and the status says so, on which the passes behind it do nothing.
 template <int NT>
-__device__ __forceinline__ void build_chunks_body(const SortPlan& sp, uint32_t* __restrict__ hist,
+__device__ __forceinline__ void build_chunks_body(const Geom* g, int64_t n, const SortPlan& sp,
+                                                  uint32_t* __restrict__ hist,
                                                   uint32_t* __restrict__ cursor,
                                                   int4* __restrict__ chunks,
                                                   uint32_t* __restrict__ nchunks, uint32_t* lh) {
@@ -128,7 +131,7 @@ __device__ __forceinline__ void build_chunks_body(const SortPlan& sp, uint32_t* 
     }
   }
   __syncthreads();
-  block_exclusive_scan_lds<NT>(lh, sp.ntiles);
+  const uint32_t tot_c = block_exclusive_scan_lds<NT>(lh, sp.ntiles);
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int t = q * NT + threadIdx.x;
@@ -140,10 +143,11 @@ __device__ __forceinline__ void build_chunks_body(const SortPlan& sp, uint32_t* 
   }
   over = __syncthreads_or(over);
   const uint32_t tot_k = block_exclusive_scan_lds<NT>(lh, sp.ntiles);
+  const bool fault = tot_c != (uint32_t)n || (int64_t)tot_k > sp.max_chunks;
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int t = q * NT + threadIdx.x;
-    if (t < sp.ntiles) {
+    if (t < sp.ntiles && !fault) {
       int4* out = chunks + lh[t];
       const uint32_t end = off[q] + cnt[q];
       for (uint32_t b = off[q]; b < end; b += sp.chunk)
@@ -151,13 +155,14 @@ __device__ __forceinline__ void build_chunks_body(const SortPlan& sp, uint32_t* 
     }
   }
   if (threadIdx.x == 0) {
-    nchunks[kNck] = tot_k;
+    if (fault) atomicCAS(const_cast<int*>(&g->status), 0, -7);
+    nchunks[kNck] = fault ? 0u : tot_k;
     nchunks[kTicket] = 0u;
     nchunks[kOverflow] = over ? 1u : 0u;
   }
 }
 
-__global__ __launch_bounds__(1024) void k_build_chunks(const Geom* __restrict__ g, SortPlan sp,
+__global__ __launch_bounds__(1024) void k_build_chunks(const Geom* g, int64_t n, SortPlan sp,
                                                        uint32_t* __restrict__ hist,
                                                        uint32_t* __restrict__ cursor,
                                                        int4* __restrict__ chunks,
@@ -167,7 +172,7 @@ __global__ __launch_bounds__(1024) void k_build_chunks(const Geom* __restrict__ 
     if (threadIdx.x == 0) nchunks[kNck] = 0u;
     return;
   }
-  build_chunks_body<1024>(sp, hist, cursor, chunks, nchunks, lh);
+  build_chunks_body<1024>(g, n, sp, hist, cursor, chunks, nchunks, lh);
 }
 
 // Keys, ranks, sort offsets and work list of the particles in X (see the list at the top of the
@@ -178,8 +183,8 @@ __global__ __launch_bounds__(1024) void k_build_chunks(const Geom* __restrict__ 
 // on hist have returned (their results are in LDS, and the barrier stands between), and the
 // counts are read and changed by agent-scope atomics alone, so the last one reads them whole.
 template <int S, int PER>
-__device__ __forceinline__ void key_rank_body(const double* __restrict__ X,
-                                              const Geom* __restrict__ g, const Consts& c,
+__device__ __forceinline__ void key_rank_body(const double* __restrict__ X, const Geom* g,
+                                              const Consts& c,
                                               const SortPlan& sp, uint32_t* __restrict__ keys,
                                               uint32_t* __restrict__ hist,
                                               uint32_t* __restrict__ cursor,
@@ -238,12 +243,12 @@ __device__ __forceinline__ void key_rank_body(const double* __restrict__ X,
     if (i < n) keys[i] = ((rank[k] + lh[key[k]]) << sp.kbits) | key[k];
   }
   __syncthreads();
-  if (s_last) build_chunks_body<kBlk>(sp, hist, cursor, chunks, nchunks, lh);
+  if (s_last) build_chunks_body<kBlk>(g, n, sp, hist, cursor, chunks, nchunks, lh);
 }
 
 template <int S, int PER>
 __global__ __launch_bounds__(kBlk) void k_key_rank(const double* __restrict__ X,
-                                                   const Geom* __restrict__ g, Consts c,
+                                                   const Geom* g, Consts c,
                                                    SortPlan sp, uint32_t* __restrict__ keys,
                                                    uint32_t* __restrict__ hist,
                                                    uint32_t* __restrict__ cursor,
@@ -1235,12 +1240,15 @@ __global__ __launch_bounds__(kBlk) void k_prologue(const double* __restrict__ X,
 }
 
 // Bucket keys for the return to the caller's order: key = id >> shift (at most 4096 buckets of
-// consecutive original indices), with a block-privatised histogram.
-__device__ __forceinline__ void id_hist_body(const uint32_t* __restrict__ ids, int64_t n,
+// consecutive original indices), with a block-privatised histogram.  After a device error nothing:
+// the pass that takes the counts out of hist again does not run then.
+__device__ __forceinline__ void id_hist_body(const Geom* __restrict__ g,
+                                                  const uint32_t* __restrict__ ids, int64_t n,
                                                   int shift, int nbuckets,
                                                   uint32_t* __restrict__ keys,
                                                   uint32_t* __restrict__ hist, int blk, int nblk) {
   __shared__ uint32_t lh[kMaxTiles];
+  if (g->status) return;
   for (int t = threadIdx.x; t < nbuckets; t += kBlk) lh[t] = 0u;
   __syncthreads();
   const int64_t base = (int64_t)blk * kItems;
@@ -1258,11 +1266,12 @@ __device__ __forceinline__ void id_hist_body(const uint32_t* __restrict__ ids, i
     if (lh[t]) atomicAdd(&hist[t], lh[t]);
 }
 
-__global__ __launch_bounds__(kBlk) void k_id_hist(const uint32_t* __restrict__ ids, int64_t n,
+__global__ __launch_bounds__(kBlk) void k_id_hist(const Geom* __restrict__ g,
+                                                  const uint32_t* __restrict__ ids, int64_t n,
                                                   int shift, int nbuckets,
                                                   uint32_t* __restrict__ keys,
                                                   uint32_t* __restrict__ hist) {
-  id_hist_body(ids, n, shift, nbuckets, keys, hist, blockIdx.x, gridDim.x);
+  id_hist_body(g, ids, n, shift, nbuckets, keys, hist, blockIdx.x, gridDim.x);
 }
 
 // Back to the caller's order: X[r][id[i]] = A[r][i].  After the bucket pass, the particles a
@@ -1484,7 +1493,7 @@ __global__ __launch_bounds__(kBlk) void k_id_hist_batch(const BeamDev* __restric
   if ((int64_t)blockIdx.x * kItems >= d.c.n) return;
   int sh, nb;
   bucket_plan(d.c.n, 0, &sh, &nb);
-  id_hist_body(cur_id(d, parity), d.c.n, sh, nb, d.keys, d.hist, blockIdx.x, gridDim.x);
+  id_hist_body(d.geom, cur_id(d, parity), d.c.n, sh, nb, d.keys, d.hist, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(1024) void k_bucket_chunks_batch(const BeamDev* __restrict__ beams) {
@@ -1493,7 +1502,8 @@ __global__ __launch_bounds__(1024) void k_bucket_chunks_batch(const BeamDev* __r
   if (d.geom->status) return;
   int sh, nb;
   bucket_plan(d.c.n, 0, &sh, &nb);
-  build_chunks_body<1024>(bucket_sort_plan(nb), d.hist, d.cursor, d.chunks, d.nchunks, lh);
+  build_chunks_body<1024>(d.geom, d.c.n, bucket_sort_plan(nb), d.hist, d.cursor, d.chunks,
+                          d.nchunks, lh);
 }
 
 __global__ __launch_bounds__(kBlk) void k_bucket_scatter_batch(const BeamDev* __restrict__ beams,
@@ -1801,11 +1811,11 @@ hipError_t launch_unpermute(const double* A, const uint32_t* idA, int64_t n, dou
   int shift, nb;
   bucket_plan(n, kMinShift, &shift, &nb);
   const SortPlan bp = bucket_sort_plan(nb);
-  hipLaunchKernelGGL(k_id_hist, dim3(grid_items(n)), dim3(kBlk), 0, s, idA, n, shift, nb, keys,
+  hipLaunchKernelGGL(k_id_hist, dim3(grid_items(n)), dim3(kBlk), 0, s, g, idA, n, shift, nb, keys,
                      hist);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_build_chunks, dim3(1), dim3(1024), 0, s, g, bp, hist, cursor, chunks,
+  hipLaunchKernelGGL(k_build_chunks, dim3(1), dim3(1024), 0, s, g, n, bp, hist, cursor, chunks,
                      nchunks);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
