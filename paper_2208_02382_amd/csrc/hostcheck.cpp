@@ -1,8 +1,37 @@
 // Host build of the device arithmetic of the integrated Green's function (ddmath.hpp,
-// igf_antideriv.hpp), exported for CPU unit tests of the kernels' math.  Not used by libpic.so.
+// igf_antideriv.hpp) and of the register transforms' butterflies (fft_reg.hpp), exported for CPU
+// unit tests of the kernels' math.  Not used by libpic.so.
+#include "fft_reg.hpp"
 #include "igf_antideriv.hpp"
 
+namespace {
+template <int R>
+void dft_rows(int dir, int count, float* v) {
+  for (int k = 0; k < count; ++k) {
+    pic::Cx<float>* row = reinterpret_cast<pic::Cx<float>*>(v) + (size_t)k * R;
+    if (dir < 0)
+      pic::dft<float, -1, R>(row);
+    else
+      pic::dft<float, +1, R>(row);
+  }
+}
+}  // namespace
+
 extern "C" {
+
+// float32 radix-R DFTs in place of `count` rows of R complex values
+void pic_hostcheck_dft(int R, int dir, int count, float* v) {
+  switch (R) {
+    case 2: return dft_rows<2>(dir, count, v);
+    case 3: return dft_rows<3>(dir, count, v);
+    case 4: return dft_rows<4>(dir, count, v);
+    case 6: return dft_rows<6>(dir, count, v);
+    case 8: return dft_rows<8>(dir, count, v);
+    case 9: return dft_rows<9>(dir, count, v);
+    case 12: return dft_rows<12>(dir, count, v);
+    case 16: return dft_rows<16>(dir, count, v);
+  }
+}
 
 // double-double log / atan / sqrt of (hi, lo) pairs: in[2k], in[2k+1] -> out[2k], out[2k+1]
 void pic_hostcheck_dd(int fn, int count, const double* in, double* out) {
