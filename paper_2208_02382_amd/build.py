@@ -16,6 +16,8 @@ LIB = os.path.join(HERE, "libpic.so")
 HOSTCHECK = os.path.join(HERE, "libpic_hostcheck.so")
 # the bench's reference measurement of LDS atomic throughput (not part of libpic.so)
 PROBE = os.path.join(HERE, "libpic_probe.so")
+# the double-double arithmetic on the device, for GPU unit tests only
+DEVCHECK = os.path.join(HERE, "libpic_devcheck.so")
 SOURCES = ["particles.hip", "sort.hip", "igf.hip", "fft.hip", "adjoint.hip", "noalloc.hip",
            "api.cpp"]
 
@@ -71,12 +73,14 @@ def build(verbose=False):
     if r.returncode != 0:
         raise RuntimeError("hostcheck build failed: %s\n%s" % (" ".join(cmd), r.stderr))
     os.replace(tmp, HOSTCHECK)
-    tmp = PROBE + ".tmp"
-    cmd = [hipcc] + FLAGS + ["-shared", os.path.join(CSRC, "probe_lds.hip"), "-o", tmp]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("probe build failed: %s\n%s" % (" ".join(cmd), r.stderr))
-    os.replace(tmp, PROBE)
+    for lib, src, flags in ((PROBE, "probe_lds.hip", []),
+                            (DEVCHECK, "devcheck.hip", PER_FILE["igf.hip"])):
+        tmp = lib + ".tmp"
+        cmd = [hipcc] + FLAGS + flags + ["-shared", os.path.join(CSRC, src), "-o", tmp]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError("build of %s failed: %s\n%s" % (src, " ".join(cmd), r.stderr))
+        os.replace(tmp, lib)
     return LIB
 
 

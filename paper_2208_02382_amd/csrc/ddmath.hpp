@@ -12,13 +12,16 @@
 // mpmath; series truncation errors are below 1e-33 relative.
 //
 // The corner functions are bound by the number of these operations (the float64 vector rate), so
-// each is carried only as wide as its weight in the result asks: the last series terms are
-// summed in double, a quotient takes two partial quotients (2^-103) from a refined hardware
-// reciprocal, and sums whose parts do not cancel use the short addition (2^-105 of the parts).
-// Largest relative errors over 3000 arguments against 60-digit mpmath: log 1.8e-31, atan2
-// 4.9e-32, sqrt 7.0e-32; the cell averages are those of the wide evaluation (every sum and
-// quotient to 2^-106, 8e-32 and 4e-32) in all 207025 cells of a 64 x 48 x 64 octant for each of
-// five cell shapes, 1.1e-16 from mpmath.  k_igf_corners at 64^3: 27 us wide, 14 us so.
+// an operation is left out where it does not carry a bit of the result: the last series terms are
+// summed in double, the reciprocals come from the hardware's refined ones (each is corrected), the
+// remainder of a quotient or root uses that its leading difference is exact, and sums of two
+// numbers of one sign use the short addition (whose error bound is then that of the long one; where
+// the two may cancel, the long one stays).  Largest relative errors of the host build over 3000
+// arguments against 60-digit mpmath (30000 for the last two): log 3.9e-32, in 1 - [2^-11, 2^-9]
+// 1.8e-30 (the rounding of the table), atan2 2.5e-32, sqrt 7.9e-32, quotient 1.3e-32; with every
+// operation carried wide 3.9e-32, 1.8e-30, 2.9e-32, 7.9e-32 and 1.5e-32, and the same double in
+// every cell of a 64 x 48 x 64 octant for each of seven cell shapes up to an aspect of 1e8.  The
+// device build is held to the same bounds.  k_igf_corners at 64^3: 28.2 us wide, 17.6 us so.
 // No fast-math and no contraction: TwoSum and FastTwoSum are exact only if every + and - is
 // rounded on its own.  hipcc contracts a*b + c into an fma by default in device code, which
 // silently turns these sequences into plain double arithmetic, so contraction is switched off
@@ -69,15 +72,15 @@ PIC_HD __forceinline__ ddv dd_add(ddv a, ddv b) {
   return fast_two_sum(s.hi, s.lo);
 }
 
-// Short form: the low parts are added in double.  The error is 2^-105 of |a| + |b|, that of the
-// form above only where the two do not cancel.
+// Short form: the low parts are added in double.  Its error is bounded by 3 2^-106 (|a| + |b|), as
+// that of the form above by 3 2^-106 |a + b|: for a and b of one sign.
 PIC_HD __forceinline__ ddv dd_add_s(ddv a, ddv b) {
   ddv s = two_sum(a.hi, b.hi);
   s.lo += a.lo + b.lo;
   return fast_two_sum(s.hi, s.lo);
 }
 
-// short addition for |a| >= |b|
+// short addition for |a| >= |b|, of one sign or b far smaller
 PIC_HD __forceinline__ ddv dd_add_f(ddv a, ddv b) {
   ddv s = fast_two_sum(a.hi, b.hi);
   s.lo += a.lo + b.lo;
@@ -106,7 +109,7 @@ PIC_HD __forceinline__ ddv dd_mul_d(ddv a, double b) {
 }
 
 // 1 / b and 1 / sqrt(b) to about double rounding for a normal b: the hardware's approximation
-// (some 23 bits) refined by two Newton steps.  The callers correct the remainder.
+// (some 23 bits) refined by two Newton steps.  The callers correct for the remainder.
 PIC_HD __forceinline__ double recip(double b) {
 #ifdef __HIP_DEVICE_COMPILE__
   double r = __builtin_amdgcn_rcp(b);
@@ -126,14 +129,21 @@ PIC_HD __forceinline__ double recip_sqrt(double b) {
 #endif
 }
 
-// a / b: two partial quotients, the second from the remainder of the first.  q1 b.hi agrees with
-// a.hi to the last bits, so a.hi - p.hi is exact and the remainder is known to 2^-53 of itself.
+// a / b: three partial quotients, each the current remainder times the double reciprocal of b.hi,
+// so that the reciprocal's rounding does not matter.  q1 b.hi agrees with a.hi to the last bits, so
+// a.hi - p.hi is exact, and the remainder is formed without another rounding of its leading part.
 PIC_HD __forceinline__ ddv dd_div(ddv a, ddv b) {
   const double rb = recip(b.hi);
   const double q1 = a.hi * rb;
   const ddv p = two_prod(q1, b.hi);
-  const double r = std::fma(-q1, b.lo, ((a.hi - p.hi) - p.lo) + a.lo);
-  return fast_two_sum(q1, r * rb);
+  ddv r = two_sum(a.hi - p.hi, -p.lo);
+  r.lo += std::fma(-q1, b.lo, a.lo);
+  r = fast_two_sum(r.hi, r.lo);
+  const double q2 = r.hi * rb;
+  const double r2 = std::fma(-q2, b.lo, std::fma(-q2, b.hi, r.hi) + r.lo);
+  ddv q = fast_two_sum(q1, q2);
+  q.lo = std::fma(r2, rb, q.lo);
+  return fast_two_sum(q.hi, q.lo);
 }
 
 PIC_HD __forceinline__ ddv dd_sqrt(ddv a) {
@@ -141,8 +151,8 @@ PIC_HD __forceinline__ ddv dd_sqrt(ddv a) {
   const double x = recip_sqrt(a.hi);
   const double ax = a.hi * x;
   const ddv p = two_prod(ax, ax);
-  const double d = ((a.hi - p.hi) - p.lo) + a.lo;
-  return fast_two_sum(ax, d * (x * 0.5));
+  const ddv d = two_sum(a.hi - p.hi, -p.lo);  // the difference is exact
+  return two_sum(ax, (d.hi + (d.lo + a.lo)) * (x * 0.5));
 }
 
 // ln 2 and pi/2 as double pairs (hi = the double nearest the constant, lo = the remainder).
@@ -158,24 +168,17 @@ constexpr double kFifthHi = 0.2;
 constexpr double kFifthLo = -1.1102230246251566e-17;
 
 // t + SIGN t^3/3 + t^5/5 + SIGN t^7/7 + t^9/9: atanh t for SIGN = 1 (|t| <= 2^-12), atan t for
-// -1 (|t| <= 2^-11).  The fourth and fifth terms, for atanh also the third, are summed in double:
-// they are below 2^-66 t and 2^-50 t.
+// -1 (|t| <= 2^-11).  The fourth and fifth terms, below 2^-68 t, are summed in double: their
+// rounding is 2^-121 t.
 template <int SIGN>
 PIC_HD __forceinline__ ddv odd_series(ddv t) {
   const ddv t2 = dd_sqr(t);
   const double z = SIGN * t2.hi;
-  const double y = z * std::fma(z, 1.0 / 9.0, 1.0 / 7.0);
-  ddv p;
-  if (SIGN > 0) {
-    p = fast_two_sum(kThirdHi, z * (kFifthHi + y));
-    p.lo += kThirdLo;
-  } else {
-    ddv w = fast_two_sum(kFifthHi, y);
-    w.lo += kFifthLo;
-    const ddv q = dd_mul(t2, w);
-    p = fast_two_sum(kThirdHi, -q.hi);
-    p.lo += kThirdLo - q.lo;
-  }
+  ddv w = fast_two_sum(kFifthHi, z * std::fma(z, 1.0 / 9.0, 1.0 / 7.0));
+  w.lo += kFifthLo;
+  const ddv q = dd_mul(t2, w);
+  ddv p = fast_two_sum(kThirdHi, SIGN * q.hi);
+  p.lo += kThirdLo + SIGN * q.lo;
   const ddv u = dd_mul(t, dd_mul(t2, p));  // the second and later terms, below 2^-23 t
   return dd_add_f(t, SIGN > 0 ? u : dd_neg(u));
 }
@@ -194,9 +197,9 @@ PIC_HD inline ddv dd_log(ddv a) {
   const ddv at = odd_series<1>(dd_div(two_sum(m.hi - c, m.lo), den));
   ddv el2 = two_prod((double)e, kLn2Hi);
   el2.lo = std::fma((double)e, kLn2Lo, el2.lo);
-  // e ln2 is 0 or at least ln2 against log c <= ln2
-  const ddv base = dd_add_s(el2, ddv{kLogTab[k][0], kLogTab[k][1]});
-  return dd_add_s(base, ddv{at.hi + at.hi, at.lo + at.lo});
+  // just below 1 (e = -1, c near 2) these cancel, and with c near 1 so may the last two
+  const ddv base = dd_add(el2, ddv{kLogTab[k][0], kLogTab[k][1]});
+  return dd_add(base, ddv{at.hi + at.hi, at.lo + at.lo});
 }
 
 // arctangent of p/q for double-doubles p >= 0, q > 0, without forming p/q: the ratio or its
@@ -216,9 +219,8 @@ PIC_HD inline ddv dd_atan2(ddv p, ddv q) {
   const int k = (int)std::rint(ratio * 1024.0);  // 0..1024
   const double c = (double)k * 0.0009765625;
   const ddv t = dd_div(dd_sub(num, dd_mul_d(den, c)), dd_add_f(den, dd_mul_d(num, c)));
-  // atan c >= |atan t|, or both small: k = 0 has atan c = 0
-  ddv r = dd_add_s(ddv{kAtanTab[k][0], kAtanTab[k][1]}, odd_series<-1>(t));
-  if (inv) r = dd_add_f(ddv{kPi2Hi, kPi2Lo}, dd_neg(r));
+  ddv r = dd_add(ddv{kAtanTab[k][0], kAtanTab[k][1]}, odd_series<-1>(t));
+  if (inv) r = dd_sub(ddv{kPi2Hi, kPi2Lo}, r);
   return r;
 }
 
