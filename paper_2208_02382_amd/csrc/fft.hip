@@ -747,9 +747,12 @@ __device__ __forceinline__ void zconv_reg(const FftArgs& a, Cx<T>* buf, int blk)
   Cx<T>* obase = (Cx<T>*)a.W2 + g;
   const T* grow = (const T*)a.gh + (int64_t)fold(ky, My) * Kx + kx;
   const int64_t gplane = (int64_t)(a.ny + 1) * Kx;
-  // signs of the folded spectrum past the Nyquist index: of this line, and along it.  As factors:
-  // a divergent `if (...) s = -s` here lost its negation in the compiled code (the lanes of one
-  // butterfly kept the unflipped sign)
+  // signs of the folded spectrum past the Nyquist index: of this line, and along it.  As factors: of
+  // `if (flip_y || (odd == 2 && p > n_z)) s = -s` clang 22 (ROCm 7.2) drops the negation where two
+  // branches lead to it.  Its LLVM IR still has it; in the machine code -s is computed ahead of the
+  // branches into the register that the other branch then overwrites with s, and the block that
+  // negates is left empty (`s_and_saveexec` followed by the `s_or` that undoes it).  The z component
+  // was then 1 to 30 % off at every z length whose last radix is even.
   const T sign_y = IMAG && a.odd == 1 && ky > a.ny ? T(-1) : T(1);
   const T sign_z = IMAG && a.odd == 2 ? T(-1) : T(1);
   const auto* tw = tw_arg<T>(a, 2);
