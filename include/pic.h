@@ -89,9 +89,12 @@ typedef struct {
                               loads; default
                               max(4, ceil(n_a/16)) */
   int chunk;               /* max particles per work item of a tile, 256..2^20; default n/6144
-                              rounded down to a power of two, 512..8192 (2048 in a batch) */
+                              rounded down to a power of two, 512..8192 (at least 2048 in a
+                              batch) */
   int blocks;              /* workgroups of the binned deposit and gather, 1..65535; default
-                              min(work items, 4096) */
+                              min(work items, 4096).  With slice-step diagnostics the gather runs
+                              at most 512 of them up to 2^21 particles and at most 768 up to
+                              2^25, since each ends with a reduction of its moment sums */
   int threads;             /* threads per workgroup of the binned deposit and gather: a
                               multiple of 64 in 64..1024; default 256 */
   int direct_field;        /* 0: E' = -grad phi by centred differences of the integrated-Green's-
@@ -274,7 +277,10 @@ pic_status pic_track_batch(pic_batch bt, int n_steps, void* stream);
 pic_status pic_batch_destroy(pic_batch bt);
 
 /* Workspace bytes of pic_track_adjoint for n_steps steps with a checkpoint every ckpt_every
- * steps (0 on invalid arguments). */
+ * steps (0 on invalid arguments).  Besides the checkpoints (48 n bytes each) these hold, for each
+ * of the ckpt_every steps of a segment, the particles' state (48 n, not the first's) and ranking
+ * (4 n) with its work list, the field with chi (four grid elements a node), the charge grid and the
+ * kernel spectra. */
 size_t pic_adjoint_workspace_bytes(const pic_beam_desc* d, int n_steps, int ckpt_every);
 
 /* Reverse sweep (discrete adjoint) of n_steps steps of pic_track_n_steps.  The paper gives no
@@ -343,7 +349,10 @@ pic_status pic_get_geometry(pic_beam b, double out[9], void* stream);
  * caller's stream; pic_profile_read synchronises those events, writes the summed milliseconds
  * and the number of launches per stage, and stops recording.  Stages:
  *   PIC_STAGE_PROLOGUE  thin quad + half drift of the first step, with the box reduction
- *   PIC_STAGE_GEOMETRY  grid geometry from the box
+ *   PIC_STAGE_GEOMETRY  grid geometry from the box, where it is a launch of its own (from the
+ *                       second step on when the gather falls back to global loads; otherwise the
+ *                       last workgroup of the prologue or gather-kick computes it, nothing is
+ *                       counted here and its time is in those stages)
  *   PIC_STAGE_GREEN     integrated Green's function and its forward FFT
  *   PIC_STAGE_DEPOSIT   the charge-deposition kernel alone
  *   PIC_STAGE_SOLVE     zero padding, forward FFT, spectral product, inverse FFT, gradient
