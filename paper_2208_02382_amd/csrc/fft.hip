@@ -1241,7 +1241,7 @@ hipError_t kernel_spectrum(const Geom* g, const FftPlan& p, int nx, int ny, int 
   const double scale = green_scale(nx, ny, nz);
   const int64_t total = (int64_t)ex * ey * ez;
   for (int a = 0; a < 3; ++a) {
-    int na, planes, LB, NT;
+    int na, planes, LB;
     green_lines(a, nx, ny, nz, &na, &planes);
     const int ncx = (na + 1) / 2;  // complex lines (two real lines each)
     size_t lds;

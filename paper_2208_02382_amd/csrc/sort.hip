@@ -599,14 +599,14 @@ __device__ __forceinline__ void add_global(T* p, T v) {
 // integer atomic each, exact in any order); the tile's exponent goes to tscale[t], and
 // k_tile_reduce forms the grid, which then depends neither on the order of the particles nor
 // on that of the atomics.
-template <int S, typename T, bool PERM>
+template <int S, bool PERM>
 __device__ __forceinline__ void deposit_tiles_body(const double* __restrict__ B,
                                                         const uint32_t* __restrict__ perm,
                                                         const Geom* __restrict__ g, Consts c,
                                                         SortPlan sp,
                                                         const int4* __restrict__ chunks,
                                                         const uint32_t* __restrict__ nchunks,
-                                                        T* __restrict__ rho, int blk, int nblk,
+                                                        int blk, int nblk,
                                                         unsigned long long* __restrict__ tacc,
                                                         int* __restrict__ tscale) {
   extern __shared__ unsigned char smem_raw[];
@@ -853,24 +853,23 @@ __global__ __launch_bounds__(kMaxThreads) void k_vdeposit_tiles(const AdjRecord*
   vdeposit_tiles_body<S, T>(recs, perm, g, c, sp, chunks, nchunks, e, blockIdx.x, gridDim.x);
 }
 
-template <int S, typename T>
+template <int S>
 __global__ __launch_bounds__(kMaxThreads) void k_deposit_tiles(const double* __restrict__ B,
                                                         const uint32_t* __restrict__ perm,
                                                         const Geom* __restrict__ g, Consts c,
                                                         SortPlan sp,
                                                         const int4* __restrict__ chunks,
                                                         const uint32_t* __restrict__ nchunks,
-                                                        T* __restrict__ rho,
                                                         unsigned long long* __restrict__ tacc,
                                                         int* __restrict__ tscale) {
   // the permutation's presence as a template argument: a uniform branch around its loads
   // inside the loop would make the join wait for all of the wave's loads
   if (perm)
-    deposit_tiles_body<S, T, true>(B, perm, g, c, sp, chunks, nchunks, rho, blockIdx.x,
-                                   gridDim.x, tacc, tscale);
+    deposit_tiles_body<S, true>(B, perm, g, c, sp, chunks, nchunks, blockIdx.x, gridDim.x, tacc,
+                                tscale);
   else
-    deposit_tiles_body<S, T, false>(B, nullptr, g, c, sp, chunks, nchunks, rho, blockIdx.x,
-                                    gridDim.x, tacc, tscale);
+    deposit_tiles_body<S, false>(B, nullptr, g, c, sp, chunks, nchunks, blockIdx.x, gridDim.x,
+                                 tacc, tscale);
 }
 
 // Fused second half of step j and first half of step j+1 on the sorted array, one chunk per
@@ -1431,13 +1430,13 @@ __global__ __launch_bounds__(kBlk) void k_scatter_batch(const BeamDev* __restric
 }
 
 // PERM: the step's input cur_X through the ranking; else nxt_X, in slot order
-template <int S, typename T, bool PERM>
+template <int S, bool PERM>
 __global__ __launch_bounds__(kBlk) void k_deposit_tiles_batch(const BeamDev* __restrict__ beams,
                                                               int parity) {
   const BeamDev& d = beams[blockIdx.y];
-  deposit_tiles_body<S, T, PERM>(PERM ? cur_X(d, parity) : nxt_X(d, parity),
-                                 PERM ? d.perm : nullptr, d.geom, d.c, d.sp, d.chunks,
-                                 d.nchunks, (T*)d.rho, blockIdx.x, gridDim.x, d.tacc, d.tscale);
+  deposit_tiles_body<S, PERM>(PERM ? cur_X(d, parity) : nxt_X(d, parity), PERM ? d.perm : nullptr,
+                              d.geom, d.c, d.sp, d.chunks, d.nchunks, blockIdx.x, gridDim.x,
+                              d.tacc, d.tscale);
 }
 
 template <int S, typename T>
@@ -1678,21 +1677,19 @@ hipError_t launch_deposit_tiles(const double* B, const uint32_t* perm, const Geo
   int rb = (int)((nodes + 255) / 256);
   if (rb > 16384) rb = 16384;
   if (S == 1) {
-    PIC_TRY_LDS((k_deposit_tiles<1, T>), lds);
-    hipLaunchKernelGGL((k_deposit_tiles<1, T>), grid, block, lds, s, B, perm, g, c, sp, chunks,
-                       nchunks, rho, tacc, tscale);
+    PIC_TRY_LDS(k_deposit_tiles<1>, lds);
+    hipLaunchKernelGGL(k_deposit_tiles<1>, grid, block, lds, s, B, perm, g, c, sp, chunks, nchunks,
+                       tacc, tscale);
     PIC_TRY(hipGetLastError());
-    if (tacc)
-      hipLaunchKernelGGL((k_tile_reduce<1, T>), dim3(rb), dim3(256), 0, s, g, c, sp, tacc, tscale,
-                         rho);
+    hipLaunchKernelGGL((k_tile_reduce<1, T>), dim3(rb), dim3(256), 0, s, g, c, sp, tacc, tscale,
+                       rho);
   } else {
-    PIC_TRY_LDS((k_deposit_tiles<2, T>), lds);
-    hipLaunchKernelGGL((k_deposit_tiles<2, T>), grid, block, lds, s, B, perm, g, c, sp, chunks,
-                       nchunks, rho, tacc, tscale);
+    PIC_TRY_LDS(k_deposit_tiles<2>, lds);
+    hipLaunchKernelGGL(k_deposit_tiles<2>, grid, block, lds, s, B, perm, g, c, sp, chunks, nchunks,
+                       tacc, tscale);
     PIC_TRY(hipGetLastError());
-    if (tacc)
-      hipLaunchKernelGGL((k_tile_reduce<2, T>), dim3(rb), dim3(256), 0, s, g, c, sp, tacc, tscale,
-                         rho);
+    hipLaunchKernelGGL((k_tile_reduce<2, T>), dim3(rb), dim3(256), 0, s, g, c, sp, tacc, tscale,
+                       rho);
   }
   return hipGetLastError();
 }
@@ -1874,8 +1871,8 @@ hipError_t launch_batch_deposit(const BeamDev* beams, int nb, const BatchDims& b
   if (rb > 16384) rb = 16384;
 #define PIC_DEP_BATCH(SS, PP)                                                                 \
   do {                                                                                        \
-    PIC_TRY_LDS((k_deposit_tiles_batch<SS, T, PP>), bd.dep_lds);                              \
-    hipLaunchKernelGGL((k_deposit_tiles_batch<SS, T, PP>), grid, dim3(kBlk), bd.dep_lds, s,   \
+    PIC_TRY_LDS((k_deposit_tiles_batch<SS, PP>), bd.dep_lds);                                 \
+    hipLaunchKernelGGL((k_deposit_tiles_batch<SS, PP>), grid, dim3(kBlk), bd.dep_lds, s,      \
                        beams, parity);                                                        \
     PIC_TRY(hipGetLastError());                                                               \
     hipLaunchKernelGGL((k_tile_reduce_batch<SS, T>), dim3(rb, nb), dim3(256), 0, s, beams);   \
