@@ -89,8 +89,8 @@ typedef struct {
                               loads; default
                               max(4, ceil(n_a/16)) */
   int chunk;               /* max particles per work item of a tile, 256..2^20; default n/6144
-                              rounded down to a power of two, 512..8192 (at least 2048 in a
-                              batch) */
+                              rounded down to a power of two, 512..8192, more on grids of
+                              few tiles (at least 2048 in a batch) */
   int blocks;              /* workgroups of the binned deposit and gather, 1..65535; default
                               min(work items, 4096).  With slice-step diagnostics the gather runs
                               at most 512 of them up to 2^21 particles and at most 768 up to

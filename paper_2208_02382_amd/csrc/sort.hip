@@ -1582,9 +1582,18 @@ int grid_stride(int64_t n) {
 // 1e5 TSC (48^3), 112 and 71 at 1e6 CIC and 186 and 88 at 1e6 TSC (64^3), 416 and 221 at 3e6 TSC
 // (96^3), 776 and 671 at 1.25e7 TSC and 2259 and 2220 at 4e7 TSC (128^3).  The results do not
 // depend on it.
-int default_chunk(int64_t n) {
+// On a grid of few tiles (64 at 16^3) so small an item flushes its window into one that hundreds of
+// others flush into, all atomics on a few hundred addresses: there an item holds n / (32 tiles), as
+// long as 768 items, three per CU, are left, and at most 4096.  A binned step of 6e6 CIC particles,
+// us, by n alone (512) and so: 570 and 315 on 12^3 (27 tiles; 331 with 8192), 433 and 405 on 8^3, 392
+// and 328 on 16^3; of 2e6 232 and 160 on 12^3, 225 and 172 (TSC) on 4^3.  From 24^3 (216 tiles) on it
+// is the rule by n.
+int default_chunk(int64_t n, int ntiles) {
+  const int64_t by_n = std::min<int64_t>(n / 6144, 8192);
+  const int64_t by_tiles = std::min<int64_t>(std::min(n / (32 * (int64_t)ntiles), n / 768), 4096);
+  const int64_t most = std::max(by_n, by_tiles);
   int c = 512;
-  while (c < 8192 && 2 * (int64_t)c <= n / 6144) c *= 2;
+  while (2 * (int64_t)c <= most) c *= 2;
   return c;
 }
 
@@ -1601,7 +1610,7 @@ SortPlan make_sort_plan(int nx, int ny, int nz, int64_t n, const int tile[3], in
   sp.ntiles = sp.NT[0] * sp.NT[1] * sp.NT[2];
   sp.kbits = 1;
   while ((1 << sp.kbits) < sp.ntiles) ++sp.kbits;
-  sp.chunk = chunk > 0 ? chunk : default_chunk(n);
+  sp.chunk = chunk > 0 ? chunk : default_chunk(n, sp.ntiles);
   // every tile adds at most one partial work item
   const int64_t items = (int64_t)(n / sp.chunk) + sp.ntiles + 1;
   sp.max_chunks = items;

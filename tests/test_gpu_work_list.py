@@ -30,3 +30,13 @@ def test_every_item_is_in_the_list(n, nodes, tile):
     g = torch.Generator(device="cuda").manual_seed(n)
     X = torch.rand((6, n), generator=g, dtype=torch.float64, device="cuda") - 0.5
     assert torch.equal(_rho(X, nodes, tile, 256), _rho(X, nodes, tile, 1 << 20))
+
+
+@pytest.mark.parametrize("n,nodes", [(786_431, (4, 4, 4)), (786_432, (4, 4, 4)),
+                                     (884_735, (12, 12, 12)), (884_736, (12, 12, 12)),
+                                     (3_200_000, (8, 12, 16))])
+def test_default_items_on_grids_of_few_tiles(n, nodes):
+    """Around the counts where the default items grow from 512 on 1 and 27 tiles, and on 24 tiles."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = 1e-3 * torch.randn((6, n), generator=g, dtype=torch.float64, device="cuda")
+    assert torch.equal(_rho(X, nodes, (0, 0, 0), 0), _rho(X, nodes, (0, 0, 0), 8192))
