@@ -7,21 +7,23 @@
 //           + 2 atanh(t), t = (m - c)/(m + c), |t| <= 1/4096, atanh by 5 series terms.
 //   atan -- a > 1 uses pi/2 - atan(1/a); c = k/1024 nearest the argument x in [0, 1];
 //           atan x = atan c + atan(t), t = (x - c)/(1 + x c), |t| <= 1/2048, 5 series terms.
-//   sqrt -- Karp-Markstein: one correction of the double reciprocal square root.
+//   sqrt -- from the double reciprocal square root, one correction in double and one beyond it.
 // The tables log(1 + k/1024) and atan(k/1024) (dd_tables.hpp) are double pairs from 60-digit
 // mpmath; series truncation errors are below 1e-33 relative.
 //
 // The corner functions are bound by the number of these operations (the float64 vector rate), so
 // an operation is left out where it does not carry a bit of the result: the last series terms are
-// summed in double, the reciprocals come from the hardware's refined ones (each is corrected), the
-// remainder of a quotient or root uses that its leading difference is exact, and sums of two
-// numbers of one sign use the short addition (whose error bound is then that of the long one; where
-// the two may cancel, the long one stays).  Largest relative errors of the host build over 3000
-// arguments against 60-digit mpmath (30000 for the last two): log 3.9e-32, in 1 - [2^-11, 2^-9]
-// 1.8e-30 (the rounding of the table), atan2 2.5e-32, sqrt 7.9e-32, quotient 1.3e-32; with every
-// operation carried wide 3.9e-32, 1.8e-30, 2.9e-32, 7.9e-32 and 1.5e-32, and the same double in
-// every cell of a 64 x 48 x 64 octant for each of seven cell shapes up to an aspect of 1e8.  The
-// device build is held to the same bounds.  k_igf_corners at 64^3: 28.2 us wide, 17.6 us so.
+// summed in double and products inside the series are not renormalised, the reciprocals come from
+// the hardware's refined ones (each is corrected), the remainder of a quotient or root is one fma
+// (exact once the quotient or root is within an ulp), and sums of two numbers of one sign use the
+// short addition (whose error bound is then that of the long one; where the two may cancel, the long
+// one stays).  Largest relative errors of the host build over 3000 arguments against 60-digit mpmath
+// (30000 for the last two), and of the same with every operation carried wide: log 3.9e-32 and
+// 3.9e-32, in 1 - [2^-11, 2^-9] 1.8e-30 and 1.8e-30 (the rounding of the table), atan2 2.5e-32 and
+// 2.9e-32, sqrt 3.6e-32 and 7.9e-32, quotient 1.3e-32 and 1.5e-32; the corner function F as close or
+// closer on six cell shapes, and the same double in every cell of a 64 x 48 x 64 octant up to an aspect
+// of 1e5.  The device build is held to the same bounds.  k_igf_corners at 64^3: 28.2 us wide, 15.4 us
+// so.
 // No fast-math and no contraction: TwoSum and FastTwoSum are exact only if every + and - is
 // rounded on its own.  hipcc contracts a*b + c into an fma by default in device code, which
 // silently turns these sequences into plain double arithmetic, so contraction is switched off
@@ -87,6 +89,16 @@ PIC_HD __forceinline__ ddv dd_add_f(ddv a, ddv b) {
   return fast_two_sum(s.hi, s.lo);
 }
 
+// the long addition for |a| >= |b| or a = 0
+PIC_HD __forceinline__ ddv dd_add_o(ddv a, ddv b) {
+  ddv s = fast_two_sum(a.hi, b.hi);
+  ddv t = two_sum(a.lo, b.lo);
+  s.lo += t.hi;
+  s = fast_two_sum(s.hi, s.lo);
+  s.lo += t.lo;
+  return fast_two_sum(s.hi, s.lo);
+}
+
 PIC_HD __forceinline__ ddv dd_neg(ddv a) { return {-a.hi, -a.lo}; }
 PIC_HD __forceinline__ ddv dd_sub(ddv a, ddv b) { return dd_add(a, dd_neg(b)); }
 
@@ -94,6 +106,13 @@ PIC_HD __forceinline__ ddv dd_mul(ddv a, ddv b) {
   ddv p = two_prod(a.hi, b.hi);
   p.lo = std::fma(a.hi, b.lo, std::fma(a.lo, b.hi, p.lo));
   return fast_two_sum(p.hi, p.lo);
+}
+
+// the product left as it comes, its lo up to an ulp of hi
+PIC_HD __forceinline__ ddv dd_mul_u(ddv a, ddv b) {
+  ddv p = two_prod(a.hi, b.hi);
+  p.lo += std::fma(a.hi, b.lo, a.lo * b.hi);
+  return p;
 }
 
 PIC_HD __forceinline__ ddv dd_sqr(ddv a) {
@@ -108,12 +127,12 @@ PIC_HD __forceinline__ ddv dd_mul_d(ddv a, double b) {
   return fast_two_sum(p.hi, p.lo);
 }
 
-// 1 / b and 1 / sqrt(b) to about double rounding for a normal b: the hardware's approximation
-// (some 23 bits) refined by two Newton steps.  The callers correct for the remainder.
+// 1 / b to 2^-46 or better for a normal b: the hardware's approximation (some 23 bits) refined by a
+// Newton step; 1 / sqrt(b) to about double rounding, by two.  The callers correct for the remainder,
+// the quotient twice.
 PIC_HD __forceinline__ double recip(double b) {
 #ifdef __HIP_DEVICE_COMPILE__
-  double r = __builtin_amdgcn_rcp(b);
-  r = std::fma(std::fma(-b, r, 1.0), r, r);
+  const double r = __builtin_amdgcn_rcp(b);
   return std::fma(std::fma(-b, r, 1.0), r, r);
 #else
   return 1.0 / b;
@@ -130,29 +149,27 @@ PIC_HD __forceinline__ double recip_sqrt(double b) {
 }
 
 // a / b: three partial quotients, each the current remainder times the double reciprocal of b.hi,
-// so that the reciprocal's rounding does not matter.  q1 b.hi agrees with a.hi to the last bits, so
-// a.hi - p.hi is exact, and the remainder is formed without another rounding of its leading part.
+// so that the reciprocal's rounding does not matter.  The first is refined to within an ulp of
+// a.hi / b.hi: its remainder a.hi - q1 b.hi is then a double, which the fma gives exactly.
 PIC_HD __forceinline__ ddv dd_div(ddv a, ddv b) {
   const double rb = recip(b.hi);
-  const double q1 = a.hi * rb;
-  const ddv p = two_prod(q1, b.hi);
-  ddv r = two_sum(a.hi - p.hi, -p.lo);
-  r.lo += std::fma(-q1, b.lo, a.lo);
-  r = fast_two_sum(r.hi, r.lo);
+  const double q0 = a.hi * rb;
+  const double q1 = std::fma(std::fma(-q0, b.hi, a.hi), rb, q0);
+  const ddv r = two_sum(std::fma(-q1, b.hi, a.hi), std::fma(-q1, b.lo, a.lo));
   const double q2 = r.hi * rb;
   const double r2 = std::fma(-q2, b.lo, std::fma(-q2, b.hi, r.hi) + r.lo);
   ddv q = fast_two_sum(q1, q2);
   q.lo = std::fma(r2, rb, q.lo);
-  return fast_two_sum(q.hi, q.lo);
+  return q;
 }
 
 PIC_HD __forceinline__ ddv dd_sqrt(ddv a) {
   if (a.hi <= 0.0) return {0.0, 0.0};
-  const double x = recip_sqrt(a.hi);
-  const double ax = a.hi * x;
-  const ddv p = two_prod(ax, ax);
-  const ddv d = two_sum(a.hi - p.hi, -p.lo);  // the difference is exact
-  return two_sum(ax, (d.hi + (d.lo + a.lo)) * (x * 0.5));
+  const double x = recip_sqrt(a.hi), hx = 0.5 * x;
+  const double y0 = a.hi * x;
+  const double y = std::fma(std::fma(-y0, y0, a.hi), hx, y0);
+  // y is within an ulp of the root of a.hi, a.hi - y^2 a double
+  return fast_two_sum(y, (std::fma(-y, y, a.hi) + a.lo) * hx);
 }
 
 // ln 2 and pi/2 as double pairs (hi = the double nearest the constant, lo = the remainder).
@@ -176,10 +193,10 @@ PIC_HD __forceinline__ ddv odd_series(ddv t) {
   const double z = SIGN * t2.hi;
   ddv w = fast_two_sum(kFifthHi, z * std::fma(z, 1.0 / 9.0, 1.0 / 7.0));
   w.lo += kFifthLo;
-  const ddv q = dd_mul(t2, w);
+  const ddv q = dd_mul_u(t2, w);
   ddv p = fast_two_sum(kThirdHi, SIGN * q.hi);
   p.lo += kThirdLo + SIGN * q.lo;
-  const ddv u = dd_mul(t, dd_mul(t2, p));  // the second and later terms, below 2^-23 t
+  const ddv u = dd_mul_u(t, dd_mul_u(t2, p));  // the second and later terms, below 2^-23 t
   return dd_add_f(t, SIGN > 0 ? u : dd_neg(u));
 }
 
@@ -198,8 +215,8 @@ PIC_HD inline ddv dd_log(ddv a) {
   ddv el2 = two_prod((double)e, kLn2Hi);
   el2.lo = std::fma((double)e, kLn2Lo, el2.lo);
   // just below 1 (e = -1, c near 2) these cancel, and with c near 1 so may the last two
-  const ddv base = dd_add(el2, ddv{kLogTab[k][0], kLogTab[k][1]});
-  return dd_add(base, ddv{at.hi + at.hi, at.lo + at.lo});
+  const ddv base = dd_add_o(el2, ddv{kLogTab[k][0], kLogTab[k][1]});
+  return dd_add_o(base, ddv{at.hi + at.hi, at.lo + at.lo});
 }
 
 // arctangent of p/q for double-doubles p >= 0, q > 0, without forming p/q: the ratio or its
@@ -219,8 +236,8 @@ PIC_HD inline ddv dd_atan2(ddv p, ddv q) {
   const int k = (int)std::rint(ratio * 1024.0);  // 0..1024
   const double c = (double)k * 0.0009765625;
   const ddv t = dd_div(dd_sub(num, dd_mul_d(den, c)), dd_add_f(den, dd_mul_d(num, c)));
-  ddv r = dd_add(ddv{kAtanTab[k][0], kAtanTab[k][1]}, odd_series<-1>(t));
-  if (inv) r = dd_sub(ddv{kPi2Hi, kPi2Lo}, r);
+  ddv r = dd_add_o(ddv{kAtanTab[k][0], kAtanTab[k][1]}, odd_series<-1>(t));
+  if (inv) r = dd_add_o(ddv{kPi2Hi, kPi2Lo}, dd_neg(r));
   return r;
 }
 

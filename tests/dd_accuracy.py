@@ -3,8 +3,8 @@ host and device builds.
 
 Bars, u = 2^-53, in units of u^2 of the result: a sum or product rounds by up to 3.
  * a/b: the remainder's low part two roundings of at most 1, the last sum 1: 3; 4 asked.
- * sqrt: the reciprocal root is within 3.5 u, so that the one correction leaves 3.5^2 / 2 = 6 and its
-   own rounding 4 x 3.5 = 14: 20.
+ * sqrt: one correction of a root from a reciprocal root within 3.5 u leaves 3.5^2 / 2 = 6 and its own
+   rounding 4 x 3.5 = 14: 20 (two corrections leave less).
  * log: two sums (6), and of atanh t, a quotient (4) and a sum (3), what it is of the whole, at most
    all of it once: 13; 14 asked.  On top the error of the table entry and of e ln 2 as double pairs, which
    just below 1 (e = -1, table entry near ln 2) are large against the result.
