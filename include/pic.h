@@ -248,10 +248,10 @@ pic_status pic_track_n_steps_binned(pic_beam b, const pic_element* lattice, int 
  * and after every step j the moments of the particles at the end of that step go to the device
  * array d_diag[27*j .. 27*j+26] (27 * n_steps doubles, 8-byte aligned, caller-owned): the six
  * means of (x, px, y, py, z, delta), then the 21 centred second moments <d_a d_b> with 1/n, for
- * a <= b in row-major order of the upper triangle.  Each step then runs its gather-kick to
- * the end of the step and applies the next step's first half map in a separate pass (about
- * 190 B more HBM traffic per particle and step).  Results equal pic_track_n_steps' to rounding;
- * the moments of step j use the same reduction as pic_moments. */
+ * a <= b in row-major order of the upper triangle.  The gather-kick sums them as it goes, about the
+ * previous step's means (where it falls back to global loads, separate passes take the moments and
+ * apply the next step's first half map, about 190 B more HBM traffic per particle and step).
+ * Results equal pic_track_n_steps' to rounding, the moments pic_moments' of the same state. */
 pic_status pic_track_n_steps_diag(pic_beam b, const pic_element* lattice, int n_el, int n_steps,
                                   double* d_diag, void* stream);
 
