@@ -1585,7 +1585,7 @@ int grid_stride(int64_t n) {
 // On a grid of few tiles (64 at 16^3) so small an item flushes its window into one that hundreds of
 // others flush into, all atomics on a few hundred addresses: there an item holds n / (32 tiles), as
 // long as 768 items, three per CU, are left, and at most 4096.  A binned step of 6e6 CIC particles,
-// us, by n alone (512) and so: 570 and 315 on 12^3 (27 tiles; 331 with 8192), 433 and 405 on 8^3, 392
+// us, by n alone (512) and so: 570 and 319 on 12^3 (27 tiles; 331 with 8192), 433 and 410 on 8^3, 392
 // and 328 on 16^3; of 2e6 232 and 160 on 12^3, 225 and 172 (TSC) on 4^3.  From 24^3 (216 tiles) on it
 // is the rule by n.
 int default_chunk(int64_t n, int ntiles) {
